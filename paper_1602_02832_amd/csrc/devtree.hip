@@ -17,10 +17,10 @@
 //   3. node moments, bottom-up: one launch per level from the deepest up, one
 //      thread per node of that level adding its children's sums (or a leaf's
 //      particles) in order, then the means.
-//   4. lists: one work-group per group keeps the group's current cut through
-//      the tree as an ordered array; every pass replaces each undecided cell
-//      by its decision (the node, its particles, or its children), in place
-//      and in order, so the final array is the pre-order list.
+//   4. lists: one work-group per group goes down the tree a level at a time,
+//      visiting every cell once; the counts of list entries under each visited
+//      cell are then summed upwards and the entries placed on the way down
+//      again, so that the list comes out in pre-order.
 #include "htree_tree.h"
 #include "wave_ops.h"
 
@@ -78,7 +78,7 @@ struct Totals {           // written by the device after the prefix sums
 
 struct Counters {         // list phase
     unsigned long long staged;   // entries reserved in the staging array
-    int32_t max_cut;             // largest cut that did not fit a work-group's scratch
+    int32_t max_cut;             // most visited cells that did not fit a work-group's scratch
     int32_t pad;
 };
 
@@ -380,6 +380,45 @@ __global__ __launch_bounds__(kWG) void cells_kernel(int64_t n, int n_leaf, const
     }
 }
 
+// What the list walk needs to know about a node, in one 64-byte record: its
+// centre of mass, particle range, level and children (a single-particle child
+// as its particle index, a child node q as ~q, kNone past the last), so that
+// visiting a node is one access and opening it follows no chain of cells.
+struct alignas(64) NodeRec {
+    double x[3];
+    uint32_t begin_level;   // first particle (26 bits), level above it
+    uint32_t end;
+    int32_t kid[8];
+};
+constexpr int32_t kNone = INT32_MIN;
+constexpr int kBeginBits = 26;
+static_assert(sizeof(NodeRec) == 64, "node record");
+static_assert(kMaxN <= int64_t(1) << kBeginBits && kDeepest < 32, "begin and level share a word");
+
+// Every node's range, level and children (its centre of mass follows the moments).
+__global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const int32_t* __restrict__ node_cell,
+                                                        const Cell* __restrict__ cell, NodeRec* __restrict__ rec) {
+    const int32_t q = blockIdx.x * kWG + threadIdx.x;
+    if (q >= m_nodes) return;
+    const int32_t ci = node_cell[q];
+    const Cell c = cell[ci];
+    NodeRec r;
+    for (int d = 0; d < 3; ++d) r.x[d] = 0.0;
+    r.begin_level = static_cast<uint32_t>(c.begin) | static_cast<uint32_t>(c.level) << kBeginBits;
+    r.end = static_cast<uint32_t>(c.end);
+    int32_t ch = c.split ? ci + 1 : c.skip;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {   // a cell has at most eight children
+        r.kid[k] = kNone;
+        if (ch < c.skip) {
+            const Cell cc = cell[ch];
+            r.kid[k] = cc.node >= 0 ? ~cc.node : cc.begin;
+            ch = cc.skip;
+        }
+    }
+    rec[q] = r;
+}
+
 // Node moments, bottom-up, as the host builder defines them: a node's sums
 // S = (m, m x[3], m v[3], m a[3], m jerk[3]) start from zero and add, for a
 // split node, its children's S in key order (a single-particle child's S is
@@ -437,7 +476,7 @@ __global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t level, int32_t m
 __global__ __launch_bounds__(kWG) void node_means_kernel(int32_t m_nodes, const double* __restrict__ raw,
                                                          double* __restrict__ om, double* __restrict__ ox,
                                                          double* __restrict__ ov, double* __restrict__ oa,
-                                                         double* __restrict__ oj) {
+                                                         double* __restrict__ oj, NodeRec* __restrict__ rec) {
     const int32_t q = blockIdx.x * kWG + threadIdx.x;
     if (q >= m_nodes) return;
     const double* u = raw + 13 * int64_t(q);
@@ -448,6 +487,7 @@ __global__ __launch_bounds__(kWG) void node_means_kernel(int32_t m_nodes, const 
         ov[3 * q + d] = u[4 + d] / M;
         oa[3 * q + d] = u[7 + d] / M;
         oj[3 * q + d] = u[10 + d] / M;
+        rec[q].x[d] = u[1 + d] / M;
     }
 }
 #pragma clang fp contract(on)
@@ -456,9 +496,9 @@ __global__ __launch_bounds__(kWG) void node_means_kernel(int32_t m_nodes, const 
 struct ListArgs {
     int64_t n;
     int32_t n_groups;
+    int32_t m_nodes;
     int32_t cut_cap;
-    const Cell* cell;
-    const double* node_x;
+    const NodeRec* rec;
     const double* sx;
     const int64_t* group_first;
     int32_t* cut;             // per work-group: 4 arrays of cut_cap int32
@@ -471,7 +511,8 @@ struct ListArgs {
     double s2[kDeepest + 1];
 };
 
-enum : int32_t { kKeep = 0, kParticle = 1, kNode = 2, kParticles = 3, kChildren = 4 };
+constexpr int kVisits = 2;               // visited cells per thread and round, their records in flight together
+constexpr int kMaxLevels = kDeepest + 2; // levels of visited cells
 
 // Exclusive prefix sum over the work-group; returns the total.
 __device__ inline int32_t wg_scan(int32_t v, int32_t* excl, int32_t* s_wave) {
@@ -492,49 +533,46 @@ __device__ inline int32_t wg_scan(int32_t v, int32_t* excl, int32_t* s_wave) {
 
 #pragma clang fp contract(off)
 // The opening test of the host builder: accept a node iff side^2 < theta^2 d^2,
-// d the distance from its centre of mass to the group's box.
-__device__ inline int32_t decide(const ListArgs& A, int32_t c, int64_t gb, int64_t ge, const double* lo,
-                                 const double* hi, int32_t* cnt) {
-    const Cell cl = A.cell[c];
-    const bool overlaps = cl.begin < ge && gb < cl.end;
-    if (!overlaps) {
-        if (cl.end - cl.begin == 1) {
-            *cnt = 1;
-            return kParticle;
-        }
-        const double* X = A.node_x + 3 * int64_t(cl.node);
-        double gap[3];
-        for (int d = 0; d < 3; ++d) {
-            const double u = dmax(lo[d] - X[d], X[d] - hi[d]);
-            gap[d] = dmax(u, 0.0);
-        }
-        const double d2 = (gap[0] * gap[0] + gap[1] * gap[1]) + gap[2] * gap[2];
-        if (A.s2[cl.level] < A.theta2 * d2) {
-            *cnt = 1;
-            return kNode;
-        }
+// d the distance from its centre of mass to the group's box; a node that
+// overlaps the group never passes.
+__device__ inline bool accepts(const ListArgs& A, const double* s2, const NodeRec& r, int64_t gb, int64_t ge,
+                               const double* lo, const double* hi) {
+    const int64_t begin = r.begin_level & ((1u << kBeginBits) - 1);
+    if (begin < ge && gb < static_cast<int64_t>(r.end)) return false;
+    double gap[3];
+    for (int d = 0; d < 3; ++d) {
+        const double u = dmax(lo[d] - r.x[d], r.x[d] - hi[d]);
+        gap[d] = dmax(u, 0.0);
     }
-    if (cl.split) {
-        int32_t k = 0;
-        for (int32_t ch = c + 1; ch < cl.skip; ch = A.cell[ch].skip) ++k;
-        *cnt = k;
-        return kChildren;
-    }
-    *cnt = cl.end - cl.begin;
-    return kParticles;
+    const double d2 = (gap[0] * gap[0] + gap[1] * gap[1]) + gap[2] * gap[2];
+    return s2[r.begin_level >> kBeginBits] < A.theta2 * d2;
 }
 #pragma clang fp contract(on)
 
+// One work-group per group.  The visited cells are kept level by level in
+// memory, each level in key order: the cell (vid) and the number of list
+// entries under it (vcount).  Going down visits every cell once, and lists the
+// opened ones (their places in oat, their first children's places in the next
+// level in ofirst; the children of one level's opened cells follow each other).
+// Then the counts are summed upwards over the opened cells only, as negative
+// numbers to tell them apart, and on the way down again each opened cell hands
+// its children their places in the list.  The walk is bound by its chain of
+// dependent accesses, a few per level, so a thread keeps several in flight.
+// (Its predecessor kept the ordered cut itself and moved every decided entry
+// again in each of the up to 22 passes, with a chain of up to eight cells at
+// every opened one.)
 __global__ __launch_bounds__(kListWG) void lists_kernel(ListArgs A) {
     __shared__ int32_t s_wave[kListWG / 64];
-    __shared__ double s_box[6][kListWG];
-    __shared__ int32_t s_flag[2];
+    __shared__ double s_box[6][kListWG / 64];
+    __shared__ double s2[kDeepest + 1];
+    __shared__ int32_t s_level[kMaxLevels + 1], s_open[kMaxLevels + 1];   // where each level's cells and opened cells begin
     __shared__ unsigned long long s_off;
     const int t = threadIdx.x;
-    int32_t* bufA = A.cut + int64_t(blockIdx.x) * 4 * A.cut_cap;
-    int32_t* bufB = bufA + A.cut_cap;
-    int32_t* pos = bufB + A.cut_cap;
-    int32_t* dec = pos + A.cut_cap;
+    int32_t* vid = A.cut + static_cast<int64_t>(blockIdx.x) * 4 * A.cut_cap;
+    int32_t* vcount = vid + A.cut_cap;
+    int32_t* oat = vcount + A.cut_cap;
+    int32_t* ofirst = oat + A.cut_cap;
+    if (t <= kDeepest) s2[t] = A.s2[t];
     for (int32_t g = blockIdx.x; g < A.n_groups; g += gridDim.x) {
         const int64_t gb = A.group_first[g], ge = A.group_first[g + 1];
         // group box: componentwise min and max of the members' positions
@@ -546,102 +584,147 @@ __global__ __launch_bounds__(kListWG) void lists_kernel(ListArgs A) {
                 hi[d] = dmax(hi[d], A.sx[3 * k + d]);
             }
         for (int d = 0; d < 3; ++d) {
-            s_box[d][t] = lo[d];
-            s_box[3 + d][t] = hi[d];
+            lo[d] = wave_ops::tree<32, 1>(lo[d], [](double p, double q) { return dmin(p, q); });
+            hi[d] = wave_ops::tree<32, 1>(hi[d], [](double p, double q) { return dmax(p, q); });
+        }
+        if ((t & 63) == 0)
+            for (int d = 0; d < 3; ++d) {
+                s_box[d][t >> 6] = lo[d];
+                s_box[3 + d][t >> 6] = hi[d];
+            }
+        if (t == 0) {
+            vid[0] = A.m_nodes > 0 ? ~0 : 0;   // the root: node 0, or the only particle
+            s_level[0] = s_open[0] = 0;
         }
         __syncthreads();
-        for (int w = kListWG / 2; w > 0; w >>= 1) {
-            if (t < w)
-                for (int d = 0; d < 3; ++d) {
-                    s_box[d][t] = dmin(s_box[d][t], s_box[d][t + w]);
-                    s_box[3 + d][t] = dmax(s_box[3 + d][t], s_box[3 + d][t + w]);
-                }
-            __syncthreads();
-        }
         for (int d = 0; d < 3; ++d) {
             lo[d] = s_box[d][0];
             hi[d] = s_box[3 + d][0];
-        }
-        __syncthreads();
-
-        int32_t* cur = bufA;
-        int32_t* nxt = bufB;
-        if (t == 0) {
-            cur[0] = -1;   // the root cell, undecided
-            s_flag[0] = s_flag[1] = 0;
-        }
-        int32_t len = 1;
-        bool overflow = false;
-        __syncthreads();
-        for (int it = 0;; ++it) {
-            // pass 1: decisions and output counts, chunk by chunk with a running offset
-            int32_t carry = 0;
-            bool more = false;
-            for (int32_t s = 0; s < len; s += kListWG) {
-                const int32_t i = s + t;
-                int32_t cnt = 0;
-                if (i < len) {
-                    const int32_t v = cur[i];
-                    int32_t d = kKeep;
-                    if (v >= 0) {
-                        cnt = 1;
-                    } else {
-                        d = decide(A, -v - 1, gb, ge, lo, hi, &cnt);
-                        if (d == kChildren) more = true;
-                    }
-                    dec[i] = d;
-                }
-                int32_t excl;
-                const int32_t tot = wg_scan(cnt, &excl, s_wave);
-                if (i < len) pos[i] = carry + excl;
-                carry += tot;
+            for (int w = 1; w < kListWG / 64; ++w) {
+                lo[d] = dmin(lo[d], s_box[d][w]);
+                hi[d] = dmax(hi[d], s_box[3 + d][w]);
             }
-            if (more) s_flag[it & 1] = 1;
-            const int32_t new_len = carry;
-            if (new_len > A.cut_cap) {
-                if (t == 0) atomicMax(&A.ctr->max_cut, new_len);
+        }
+        // down: decide every visited cell; the children of the opened ones, in
+        // order, are the next level
+        int32_t begin = 0, end = 1, opened = 0;
+        int levels = 0;
+        bool overflow = false;
+        while (begin < end) {
+            int32_t fill = end;
+            for (int32_t s = begin; s < end; s += kListWG * kVisits) {
+                const int32_t i0 = s + kVisits * t;
+                int32_t id[kVisits], nk[kVisits], sums = 0;   // sums: children, and opened cells above bit 16
+                NodeRec r[kVisits];
+#pragma unroll
+                for (int u = 0; u < kVisits; ++u) id[u] = i0 + u < end ? vid[i0 + u] : 0;
+#pragma unroll
+                for (int u = 0; u < kVisits; ++u)
+                    if (id[u] < 0) r[u] = A.rec[~id[u]];
+#pragma unroll
+                for (int u = 0; u < kVisits; ++u) {
+                    nk[u] = 0;
+                    int32_t cnt = 1;
+                    if (id[u] < 0 && !accepts(A, s2, r[u], gb, ge, lo, hi)) {
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) nk[u] += r[u].kid[k] != kNone;
+                        if (nk[u] == 0)   // a leaf of several particles
+                            cnt = static_cast<int32_t>(r[u].end - (r[u].begin_level & ((1u << kBeginBits) - 1)));
+                        else
+                            sums += nk[u] + (1 << 16);
+                    }
+                    if (i0 + u < end) vcount[i0 + u] = cnt;
+                }
+                static_assert(kListWG * kVisits * 8 < 1 << 16, "a round's children fit below bit 16");
+                int32_t before;
+                const int32_t tot = wg_scan(sums, &before, s_wave);
+                int32_t at = fill + (before & 0xffff), ot = opened + (before >> 16);
+                fill += tot & 0xffff;
+                if (fill > A.cut_cap) continue;   // does not fit: the level is only counted
+                opened += tot >> 16;
+#pragma unroll
+                for (int u = 0; u < kVisits; ++u) {
+                    if (nk[u] == 0) continue;
+                    oat[ot] = i0 + u;
+                    ofirst[ot++] = at;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (k < nk[u]) vid[at + k] = r[u].kid[k];
+                    at += nk[u];
+                }
+            }
+            if (fill > A.cut_cap) {
+                if (t == 0) atomicMax(&A.ctr->max_cut, fill);
                 overflow = true;
                 break;
             }
-            __syncthreads();
-            // every thread has read the other flag slot (end of the previous pass) before this barrier
-            if (t == 0) s_flag[(it + 1) & 1] = 0;
-            // pass 2: write every element's output at its offset, in order
-            for (int32_t i = t; i < len; i += kListWG) {
-                const int32_t v = cur[i];
-                int32_t p = pos[i];
-                switch (dec[i]) {
-                    case kKeep: nxt[p] = v; break;
-                    case kParticle: nxt[p] = A.cell[-v - 1].begin; break;
-                    case kNode: nxt[p] = static_cast<int32_t>(A.n) + A.cell[-v - 1].node; break;
-                    case kParticles: {
-                        const Cell cl = A.cell[-v - 1];
-                        for (int32_t k = cl.begin; k < cl.end; ++k) nxt[p++] = k;
-                        break;
-                    }
-                    default: {
-                        const int32_t c = -v - 1;
-                        const int32_t stop = A.cell[c].skip;
-                        for (int32_t ch = c + 1; ch < stop; ch = A.cell[ch].skip) nxt[p++] = -ch - 1;
-                        break;
-                    }
-                }
+            begin = end;
+            end = fill;
+            ++levels;
+            if (t == 0) {
+                s_level[levels] = begin;
+                s_open[levels] = opened;
             }
             __syncthreads();
-            const bool again = s_flag[it & 1] != 0;
-            int32_t* tmp = cur;
-            cur = nxt;
-            nxt = tmp;
-            len = new_len;
-            if (!again) break;
         }
-        // stage the finished list
+        int32_t len = 0;
+        if (!overflow) {
+            // up: entries under every opened cell (the last level has none)
+            for (int l = levels - 2; l >= 0; --l) {
+                const int32_t o1 = s_open[l + 1], stop = s_level[l + 2];
+                for (int32_t o = s_open[l] + t; o < o1; o += kListWG) {
+                    const int32_t f = ofirst[o], k = (o + 1 < o1 ? ofirst[o + 1] : stop) - f;
+                    int32_t sum = 0;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) sum += c < k ? abs(vcount[f + c]) : 0;
+                    vcount[oat[o]] = -sum;
+                }
+                __syncthreads();
+            }
+            len = abs(vcount[0]);
+        }
+        __syncthreads();
         if (t == 0) s_off = overflow ? ~0ull : atomicAdd(&A.ctr->staged, static_cast<unsigned long long>(len));
         __syncthreads();
         const unsigned long long off = s_off;
         const bool fits = !overflow && off + static_cast<unsigned long long>(len) <= static_cast<unsigned long long>(A.stage_cap);
-        if (fits)
-            for (int32_t i = t; i < len; i += kListWG) A.stage[off + i] = cur[i];
+        if (fits) {
+            // down: the children's places in the list, and the entries
+            int32_t* out = A.stage + off;
+            auto entry = [&](int32_t id, int32_t cnt, int32_t p) {
+                if (cnt == 1) {
+                    out[p] = id < 0 ? static_cast<int32_t>(A.n) + ~id : id;
+                } else {   // a leaf: its particles
+                    const int32_t first = static_cast<int32_t>(A.rec[~id].begin_level & ((1u << kBeginBits) - 1));
+                    for (int32_t q = 0; q < cnt; ++q) out[p + q] = first + q;
+                }
+            };
+            if (t == 0) {
+                if (vcount[0] > 0) entry(vid[0], vcount[0], 0);
+                else vcount[0] = 0;
+            }
+            __syncthreads();
+            for (int l = 0; l + 1 < levels; ++l) {
+                const int32_t o1 = s_open[l + 1], stop = s_level[l + 2];
+                for (int32_t o = s_open[l] + t; o < o1; o += kListWG) {
+                    const int32_t f = ofirst[o], k = (o + 1 < o1 ? ofirst[o + 1] : stop) - f;
+                    int32_t p = vcount[oat[o]];
+                    int32_t id[8], cnt[8];
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        cnt[c] = c < k ? vcount[f + c] : 0;
+                        id[c] = c < k ? vid[f + c] : 0;
+                    }
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        if (cnt[c] < 0) vcount[f + c] = p;
+                        else if (cnt[c] > 0) entry(id[c], cnt[c], p);
+                        p += abs(cnt[c]);
+                    }
+                }
+                __syncthreads();
+            }
+        }
         if (t == 0) {
             A.glen[g] = overflow ? 0 : len;
             A.gstage[g] = fits ? static_cast<int64_t>(off) : -1;
@@ -714,6 +797,7 @@ struct htd_tree {
     DevBuf<double> nm, nx, nv, na, nj;
     DevBuf<int32_t> nlev, ncid;   // per node: level, cell index
     DevBuf<double> nraw;            // per node: the 13 sums of its moments
+    DevBuf<NodeRec> nrec;           // per node: what the list walk reads
     DevBuf<int64_t> nbeg, nend;
     // groups and lists
     DevBuf<int64_t> group_first, list_off, gstage, glen64;
@@ -774,6 +858,13 @@ int grow_particles(htd_tree* t, int64_t n) {
     return 0;
 }
 
+// Work-groups of the list walk: one per group up to n_list_wg, fewer (down to
+// 64) where their scratch would pass 32 GB.
+int list_wgs(const htd_tree* t) {
+    const int64_t fit = (int64_t(32) << 30) / (16 * static_cast<int64_t>(t->cut_cap));
+    return static_cast<int>(std::min<int64_t>(t->G, std::min<int64_t>(t->n_list_wg, std::max<int64_t>(fit, 64))));
+}
+
 int run_lists(htd_tree* t, const ListArgs& base, int32_t* max_cut, unsigned long long* staged) {
     ListArgs A = base;
     A.cut = t->cut.p;
@@ -782,8 +873,7 @@ int run_lists(htd_tree* t, const ListArgs& base, int32_t* max_cut, unsigned long
     A.stage_cap = t->stage.cap;
     A.ctr = t->ctr.p;
     HTD_HIP(hipMemsetAsync(t->ctr.p, 0, sizeof(Counters), t->stream));
-    const int wg = static_cast<int>(std::min<int64_t>(t->G, t->n_list_wg));
-    lists_kernel<<<wg, kListWG, 0, t->stream>>>(A);
+    lists_kernel<<<list_wgs(t), kListWG, 0, t->stream>>>(A);
     HTD_HIP(hipGetLastError());
     Counters c{};
     HTD_HIP(hipMemcpyAsync(&c, t->ctr.p, sizeof c, hipMemcpyDeviceToHost, t->stream));
@@ -835,7 +925,7 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
     const int64_t M1 = std::max<int64_t>(t->M, 1);
     if ((rc = t->cell.grow(t->C)) || (rc = t->nm.grow(M1)) || (rc = t->nx.grow(3 * M1)) ||
         (rc = t->nv.grow(3 * M1)) || (rc = t->na.grow(3 * M1)) || (rc = t->nj.grow(3 * M1)) ||
-        (rc = t->nlev.grow(M1)) || (rc = t->ncid.grow(M1)) || (rc = t->nraw.grow(13 * M1)) ||
+        (rc = t->nlev.grow(M1)) || (rc = t->ncid.grow(M1)) || (rc = t->nraw.grow(13 * M1)) || (rc = t->nrec.grow(M1)) ||
         (rc = t->nbeg.grow(M1)) || (rc = t->nend.grow(M1)))
         return rc;
     cells_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, n_leaf, t->key.p, t->lev.p, t->cbase.p, t->nbase.p,
@@ -846,11 +936,12 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
     // 3. node moments
     if (t->M > 0) {
         const int32_t Mi = static_cast<int32_t>(t->M);
+        node_recs_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->ncid.p, t->cell.p, t->nrec.p);
         for (int level = kDeepest; level >= 0; --level)
             node_sums_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(level, Mi, t->nlev.p, t->ncid.p, t->cell.p, t->sm.p,
                                                                  t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p);
         node_means_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->nraw.p, t->nm.p, t->nx.p, t->nv.p, t->na.p,
-                                                              t->nj.p);
+                                                              t->nj.p, t->nrec.p);
         HTD_HIP(hipGetLastError());
     }
     HTD_HIP(hipEventRecord(t->ev[4], s));
@@ -858,8 +949,8 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
     ListArgs A{};
     A.n = n;
     A.n_groups = static_cast<int32_t>(t->G);
-    A.cell = t->cell.p;
-    A.node_x = t->nx.p;
+    A.m_nodes = static_cast<int32_t>(t->M);
+    A.rec = t->nrec.p;
     A.sx = t->sx.p;
     A.group_first = t->group_first.p;
     A.glen = t->glen.p;
@@ -869,8 +960,7 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
         const double sl = std::ldexp(t->root_h.side, -l);
         A.s2[l] = sl * sl;
     }
-    const int wg = static_cast<int>(std::min<int64_t>(t->G, t->n_list_wg));
-    if ((rc = t->cut.grow(int64_t(wg) * 4 * t->cut_cap))) return rc;
+    if ((rc = t->cut.grow(list_wgs(t) * 4 * static_cast<int64_t>(t->cut_cap)))) return rc;
     if ((rc = t->stage.grow(std::max<int64_t>(t->stage.cap, 64 * n)))) return rc;
     for (int attempt = 0;; ++attempt) {
         int32_t max_cut = 0;
@@ -880,12 +970,14 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
             t->L = static_cast<int64_t>(staged);
             break;
         }
-        if (attempt >= 3) return fail(HTD_ERANGE, "interaction lists did not fit after %d attempts", attempt + 1);
-        if (max_cut > 0) {   // a group's cut outgrew the per-work-group scratch
+        if (attempt >= 32) return fail(HTD_ERANGE, "interaction lists did not fit after %d attempts", attempt + 1);
+        if (max_cut > 0) {
+            // a group's visited cells outgrew the per-work-group scratch.  They were counted up to
+            // the level that did not fit, so the next size at least doubles, up to all cells at once.
             if (int64_t(max_cut) > INT32_MAX / 2) return fail(HTD_ERANGE, "a group's list exceeds 2^30 entries");
-            t->cut_cap = std::max<int32_t>(t->cut_cap, max_cut + max_cut / 4);
+            t->cut_cap = static_cast<int32_t>(std::min<int64_t>(t->C, 2 * int64_t(max_cut)));
             t->cut.release();
-            if ((rc = t->cut.grow(int64_t(wg) * 4 * t->cut_cap))) return rc;
+            if ((rc = t->cut.grow(list_wgs(t) * 4 * static_cast<int64_t>(t->cut_cap)))) return rc;
         }
         if (staged > static_cast<unsigned long long>(t->stage.cap)) {
             t->stage.release();
@@ -959,7 +1051,7 @@ int htd_destroy(htd_tree* t) {
     t->ncell.release(); t->cbase.release(); t->nnode.release(); t->nbase.release(); t->gflag.release();
     t->gbase.release(); t->tmp.release(); t->part.release(); t->root.release(); t->tot.release();
     t->cell.release(); t->nm.release(); t->nx.release(); t->nv.release(); t->na.release(); t->nj.release();
-    t->nlev.release(); t->ncid.release(); t->nraw.release(); t->nbeg.release();
+    t->nlev.release(); t->ncid.release(); t->nraw.release(); t->nrec.release(); t->nbeg.release();
     t->nend.release(); t->group_first.release(); t->list_off.release(); t->gstage.release(); t->glen64.release();
     t->glen.release(); t->cut.release(); t->stage.release(); t->entries.release(); t->ctr.release();
     delete t;
@@ -1053,7 +1145,7 @@ int htd_device_bytes(const htd_tree* t, size_t* bytes) {
     add(t->sx), add(t->sv), add(t->sa), add(t->sj), add(t->sm), add(t->lev);
     add(t->ncell), add(t->cbase), add(t->nnode), add(t->nbase), add(t->gflag), add(t->gbase);
     add(t->tmp), add(t->part), add(t->root), add(t->tot), add(t->cell);
-    add(t->nm), add(t->nx), add(t->nv), add(t->na), add(t->nj), add(t->nlev), add(t->ncid), add(t->nraw);
+    add(t->nm), add(t->nx), add(t->nv), add(t->na), add(t->nj), add(t->nlev), add(t->ncid), add(t->nraw), add(t->nrec);
     add(t->nbeg), add(t->nend), add(t->group_first), add(t->list_off), add(t->gstage), add(t->glen64);
     add(t->glen), add(t->cut), add(t->stage), add(t->entries), add(t->ctr);
     *bytes = b;
