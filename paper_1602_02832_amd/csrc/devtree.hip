@@ -18,7 +18,7 @@
 //      thread per node of that level adding its children's sums (or a leaf's
 //      particles) in order, then the means.
 //   4. lists: one work-group per group goes down the tree a level at a time,
-//      visiting every cell once; the counts of list entries under each visited
+//      visiting every cell once; the counts of list entries under each opened
 //      cell are then summed upwards and the entries placed on the way down
 //      again, so that the list comes out in pre-order.
 #include "htree_tree.h"
@@ -41,7 +41,7 @@ constexpr int kAxisBits = 21;      // bits per axis of the key
 constexpr int kDeepest = 21;       // deepest cell level
 constexpr int kNoCellLevel = 22;   // L_k of a particle whose key equals its predecessor's
 constexpr int kWG = 256;
-constexpr int kListWG = 256;
+constexpr int kListWG = 512;
 constexpr int64_t kMaxN = int64_t(1) << 26;   // every cell count fits in int32 (<= 22 N)
 
 thread_local std::string g_err;
@@ -78,7 +78,7 @@ struct Totals {           // written by the device after the prefix sums
 
 struct Counters {         // list phase
     unsigned long long staged;   // entries reserved in the staging array
-    int32_t max_cut;             // most visited cells that did not fit a work-group's scratch
+    int32_t max_cut;             // most opened cells that did not fit a work-group's scratch
     int32_t pad;
 };
 
@@ -384,16 +384,24 @@ __global__ __launch_bounds__(kWG) void cells_kernel(int64_t n, int n_leaf, const
 // centre of mass, particle range, level and children (a single-particle child
 // as its particle index, a child node q as ~q, kNone past the last), so that
 // visiting a node is one access and opening it follows no chain of cells.
-struct alignas(64) NodeRec {
+struct alignas(32) NodeTest {
     double x[3];
     uint32_t begin_level;   // first particle (26 bits), level above it
     uint32_t end;
+};
+struct alignas(64) NodeRec : NodeTest {
     int32_t kid[8];
 };
 constexpr int32_t kNone = INT32_MIN;
 constexpr int kBeginBits = 26;
-static_assert(sizeof(NodeRec) == 64, "node record");
+static_assert(sizeof(NodeTest) == 32 && sizeof(NodeRec) == 64, "node record");
 static_assert(kMaxN <= int64_t(1) << kBeginBits && kDeepest < 32, "begin and level share a word");
+
+__device__ inline int32_t first_of(const NodeTest& r) {
+    return static_cast<int32_t>(r.begin_level & ((1u << kBeginBits) - 1));
+}
+__device__ inline int32_t size_of(const NodeTest& r) { return static_cast<int32_t>(r.end) - first_of(r); }
+__device__ inline bool is_node(int32_t kid) { return kid < 0 && kid != kNone; }
 
 // Every node's range, level and children (its centre of mass follows the moments).
 __global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const int32_t* __restrict__ node_cell,
@@ -501,7 +509,7 @@ struct ListArgs {
     const NodeRec* rec;
     const double* sx;
     const int64_t* group_first;
-    int32_t* cut;             // per work-group: 4 arrays of cut_cap int32
+    int32_t* cut;             // per work-group: walk_words(cut_cap) int32
     int32_t* stage;
     int64_t stage_cap;
     int32_t* glen;
@@ -511,34 +519,13 @@ struct ListArgs {
     double s2[kDeepest + 1];
 };
 
-constexpr int kVisits = 2;               // visited cells per thread and round, their records in flight together
-constexpr int kMaxLevels = kDeepest + 2; // levels of visited cells
-
-// Exclusive prefix sum over the work-group; returns the total.
-__device__ inline int32_t wg_scan(int32_t v, int32_t* excl, int32_t* s_wave) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int32_t x = wave_ops::scan_inclusive(v);
-    if (lane == 63) s_wave[wave] = x;
-    __syncthreads();
-    int32_t before = 0, total = 0;
-    for (int w = 0; w < kListWG / 64; ++w) {
-        const int32_t s = s_wave[w];
-        if (w < wave) before += s;
-        total += s;
-    }
-    *excl = before + x - v;
-    __syncthreads();
-    return total;
-}
-
 #pragma clang fp contract(off)
 // The opening test of the host builder: accept a node iff side^2 < theta^2 d^2,
 // d the distance from its centre of mass to the group's box; a node that
 // overlaps the group never passes.
-__device__ inline bool accepts(const ListArgs& A, const double* s2, const NodeRec& r, int64_t gb, int64_t ge,
+__device__ inline bool accepts(const ListArgs& A, const double* s2, const NodeTest& r, int64_t gb, int64_t ge,
                                const double* lo, const double* hi) {
-    const int64_t begin = r.begin_level & ((1u << kBeginBits) - 1);
-    if (begin < ge && gb < static_cast<int64_t>(r.end)) return false;
+    if (first_of(r) < ge && gb < static_cast<int64_t>(r.end)) return false;
     double gap[3];
     for (int d = 0; d < 3; ++d) {
         const double u = dmax(lo[d] - r.x[d], r.x[d] - hi[d]);
@@ -549,30 +536,180 @@ __device__ inline bool accepts(const ListArgs& A, const double* s2, const NodeRe
 }
 #pragma clang fp contract(on)
 
-// One work-group per group.  The visited cells are kept level by level in
-// memory, each level in key order: the cell (vid) and the number of list
-// entries under it (vcount).  Going down visits every cell once, and lists the
-// opened ones (their places in oat, their first children's places in the next
-// level in ofirst; the children of one level's opened cells follow each other).
-// Then the counts are summed upwards over the opened cells only, as negative
-// numbers to tell them apart, and on the way down again each opened cell hands
-// its children their places in the list.  The walk is bound by its chain of
-// dependent accesses, a few per level, so a thread keeps several in flight.
-// (Its predecessor kept the ordered cut itself and moved every decided entry
-// again in each of the up to 22 passes, with a chain of up to eight cells at
-// every opened one.)
-__global__ __launch_bounds__(kListWG) void lists_kernel(ListArgs A) {
-    __shared__ int32_t s_wave[kListWG / 64];
-    __shared__ double s_box[6][kListWG / 64];
-    __shared__ double s2[kDeepest + 1];
-    __shared__ int32_t s_level[kMaxLevels + 1], s_open[kMaxLevels + 1];   // where each level's cells and opened cells begin
-    __shared__ unsigned long long s_off;
+// A group's walk: the opened cells level by level, each level in key order.
+// onode: the node; ofirst: its first opened child (the opened children of a
+// cell follow each other in the next level); okids: which children are opened
+// (8 bits) and how many there are (0: a leaf of several particles); ocount:
+// the list entries under it, later its place in the list.
+struct Walk {
+    int32_t *onode, *ofirst, *ocount;
+    uint16_t* okids;
+    int32_t cap;
+};
+constexpr int32_t kLdsOpened = 5600;   // 77 KB: two work-groups per CU
+__host__ __device__ inline int64_t walk_words(int64_t cap) { return 3 * cap + (cap + 1) / 2; }
+
+constexpr int kAhead = 2;                     // opened cells per eight lanes and round, their children in flight together
+constexpr int kListWaves = kListWG / 64;
+constexpr int kPerRound = kListWG / 8;        // opened cells that the work-group's lanes cover once
+
+struct WalkShared {
+    double s2[kDeepest + 1];
+    int32_t open[kDeepest + 4];               // where each level's opened cells begin
+    int32_t count[2][kAhead * kListWaves];    // opened cells by slot and wave, of this round and the last
+    unsigned long long off;
+};
+
+// Visits the children of every opened cell of group [gb, ge) with box
+// [lo, hi], eight lanes to a cell, and writes the group's list: down the
+// levels, then the counts up, then the places down.  Returns false, with *need
+// opened cells counted, if the walk does not fit w.
+__device__ __forceinline__ bool walk_group(const ListArgs& A, int32_t g, int64_t gb, int64_t ge, const double* lo,
+                                           const double* hi, const Walk& w, WalkShared& S, int32_t* need) {
+    const int t = threadIdx.x, c = t & 7, lane = t & 63, wave = t >> 6;
+    const uint64_t below = (1ull << lane) - 1ull, before8 = (1ull << (lane & 56)) - 1ull;
+    if (t == 0) {
+        w.onode[0] = 0;   // the root overlaps every group
+        S.open[0] = 0;
+        S.open[1] = 1;
+    }
+    __syncthreads();
+    int levels = 0, round = 0;
+    for (int32_t o0 = 0, o1 = 1; o0 < o1; ++levels) {
+        int32_t fill = o1;
+        for (int32_t s = o0; s < o1; s += kPerRound * kAhead, round ^= 1) {
+            int32_t q[kAhead], kid[kAhead];
+            NodeTest r[kAhead];
+            uint64_t opened[kAhead], kids[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int32_t o = s + u * kPerRound + (t >> 3);
+                q[u] = o < o1 ? w.onode[o] : -1;
+                kid[u] = q[u] >= 0 ? A.rec[q[u]].kid[c] : kNone;
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (is_node(kid[u])) r[u] = A.rec[~kid[u]];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                opened[u] = __ballot(is_node(kid[u]) && !accepts(A, S.s2, r[u], gb, ge, lo, hi));
+                kids[u] = __ballot(kid[u] != kNone);
+                if (lane == 0) S.count[round][u * kListWaves + wave] = __popcll(opened[u]);
+            }
+            __syncthreads();
+            int32_t at[kAhead];
+            for (int u = 0; u < kAhead; ++u)
+                for (int k = 0; k < kListWaves; ++k) {
+                    if (k == wave) at[u] = fill;
+                    fill += S.count[round][u * kListWaves + k];
+                }
+            if (fill > w.cap) continue;   // does not fit: the level is only counted
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (q[u] < 0) continue;
+                if ((opened[u] >> lane) & 1) w.onode[at[u] + __popcll(opened[u] & below)] = ~kid[u];
+                if (c != 0) continue;
+                const int32_t o = s + u * kPerRound + (t >> 3);
+                const uint32_t n = __popc(static_cast<uint32_t>(kids[u] >> lane) & 0xffu);
+                w.ofirst[o] = at[u] + __popcll(opened[u] & before8);
+                w.okids[o] = static_cast<uint16_t>((static_cast<uint32_t>(opened[u] >> lane) & 0xffu) | n << 8);
+                if (n == 0) w.ocount[o] = size_of(A.rec[q[u]]);
+            }
+        }
+        if (fill > w.cap) {
+            *need = fill;
+            return false;
+        }
+        o0 = o1;
+        o1 = fill;
+        if (t == 0) S.open[levels + 2] = fill;
+        __syncthreads();
+    }
+    // up: entries under every opened cell
+    for (int l = levels - 1; l >= 0; --l) {
+        const int32_t o1 = S.open[l + 1];
+        for (int32_t o = S.open[l] + t; o < o1; o += kListWG) {
+            const uint32_t m = w.okids[o], n = m >> 8, k = __popc(m & 0xffu);
+            if (n == 0) continue;   // a leaf: counted on the way down
+            const int32_t f = w.ofirst[o];
+            int32_t sum = static_cast<int32_t>(n - k);
+            for (uint32_t i = 0; i < k; ++i) sum += w.ocount[f + i];
+            w.ocount[o] = sum;
+        }
+        __syncthreads();
+    }
+    const int32_t len = w.ocount[0];
+    __syncthreads();
+    if (t == 0) {
+        S.off = atomicAdd(&A.ctr->staged, static_cast<unsigned long long>(len));
+        w.ocount[0] = 0;
+    }
+    __syncthreads();
+    const unsigned long long off = S.off;
+    const bool fits = off + static_cast<unsigned long long>(len) <= static_cast<unsigned long long>(A.stage_cap);
+    if (t == 0) {
+        A.glen[g] = len;
+        A.gstage[g] = fits ? static_cast<int64_t>(off) : -1;
+    }
+    if (!fits) return true;
+    // down: the opened children's places in the list, and the entries
+    int32_t* out = A.stage + off;
+    for (int l = 0; l < levels; ++l) {
+        const int32_t o1 = S.open[l + 1];
+        for (int32_t s = S.open[l]; s < o1; s += kPerRound) {
+            const int32_t o = s + (t >> 3);
+            const bool on = o < o1;   // every lane takes part in the lane exchanges
+            const int32_t q = on ? w.onode[o] : 0, kid = on ? A.rec[q].kid[c] : kNone;
+            const uint32_t m = on ? w.okids[o] : 0u;
+            const int32_t p0 = on ? w.ocount[o] : 0;
+            const bool opened = (m >> c) & 1;
+            const int32_t mine = on ? w.ofirst[o] + __popc(m & ((1u << c) - 1u)) : 0;
+            const int32_t cnt = kid == kNone ? 0 : opened ? w.ocount[mine] : 1;
+            int32_t x = cnt, y;   // inclusive prefix sum over the cell's eight lanes
+            y = wave_ops::below_in_row<1>(x);
+            x += c >= 1 ? y : 0;
+            y = wave_ops::below_in_row<2>(x);
+            x += c >= 2 ? y : 0;
+            y = wave_ops::below_in_row<4>(x);
+            x += c >= 4 ? y : 0;
+            const int32_t p = p0 + x - cnt;
+            if (opened) w.ocount[mine] = p;
+            else if (kid != kNone) out[p] = kid < 0 ? static_cast<int32_t>(A.n) + ~kid : kid;
+            if (on && m >> 8 == 0) {   // a leaf: its particles
+                const NodeTest r = A.rec[q];
+                for (int32_t k = c; k < size_of(r); k += 8) out[p0 + k] = first_of(r) + k;
+            }
+        }
+        __syncthreads();
+    }
+    return true;
+}
+
+// One work-group per group.  The walk is bound by its chain of dependent
+// accesses, a few per level: what it keeps is in LDS where it fits, in memory
+// otherwise (a store and the load after the barrier cost about 1500 cycles
+// there, under load).  Only opened cells are kept, a fifth of the visited
+// ones, so that the lists of 2^20 particles (8700 entries in the mean, 15000
+// at most) fit.  An earlier form kept the ordered cut itself in memory and
+// moved every decided entry again in each of the up to 22 passes, with a chain
+// of up to eight cells at every opened one: 1740 us at 2^20 particles, against
+// 366 us.
+__global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
+    __shared__ int32_t s_onode[kLdsOpened], s_ofirst[kLdsOpened], s_ocount[kLdsOpened];
+    __shared__ uint16_t s_okids[kLdsOpened];
+    __shared__ WalkShared S;
+    __shared__ double s_box[6][kListWaves];
     const int t = threadIdx.x;
-    int32_t* vid = A.cut + static_cast<int64_t>(blockIdx.x) * 4 * A.cut_cap;
-    int32_t* vcount = vid + A.cut_cap;
-    int32_t* oat = vcount + A.cut_cap;
-    int32_t* ofirst = oat + A.cut_cap;
-    if (t <= kDeepest) s2[t] = A.s2[t];
+    if (t <= kDeepest) S.s2[t] = A.s2[t];
+    if (A.m_nodes == 0) {   // a single particle
+        if (t == 0 && blockIdx.x == 0) {
+            const unsigned long long off = atomicAdd(&A.ctr->staged, 1ull);
+            if (off < static_cast<unsigned long long>(A.stage_cap)) A.stage[off] = 0;
+            A.glen[0] = 1;
+            A.gstage[0] = static_cast<int64_t>(off);
+        }
+        return;
+    }
     for (int32_t g = blockIdx.x; g < A.n_groups; g += gridDim.x) {
         const int64_t gb = A.group_first[g], ge = A.group_first[g + 1];
         // group box: componentwise min and max of the members' positions
@@ -592,142 +729,26 @@ __global__ __launch_bounds__(kListWG) void lists_kernel(ListArgs A) {
                 s_box[d][t >> 6] = lo[d];
                 s_box[3 + d][t >> 6] = hi[d];
             }
-        if (t == 0) {
-            vid[0] = A.m_nodes > 0 ? ~0 : 0;   // the root: node 0, or the only particle
-            s_level[0] = s_open[0] = 0;
-        }
         __syncthreads();
         for (int d = 0; d < 3; ++d) {
             lo[d] = s_box[d][0];
             hi[d] = s_box[3 + d][0];
-            for (int w = 1; w < kListWG / 64; ++w) {
+            for (int w = 1; w < kListWaves; ++w) {
                 lo[d] = dmin(lo[d], s_box[d][w]);
                 hi[d] = dmax(hi[d], s_box[3 + d][w]);
             }
         }
-        // down: decide every visited cell; the children of the opened ones, in
-        // order, are the next level
-        int32_t begin = 0, end = 1, opened = 0;
-        int levels = 0;
-        bool overflow = false;
-        while (begin < end) {
-            int32_t fill = end;
-            for (int32_t s = begin; s < end; s += kListWG * kVisits) {
-                const int32_t i0 = s + kVisits * t;
-                int32_t id[kVisits], nk[kVisits], sums = 0;   // sums: children, and opened cells above bit 16
-                NodeRec r[kVisits];
-#pragma unroll
-                for (int u = 0; u < kVisits; ++u) id[u] = i0 + u < end ? vid[i0 + u] : 0;
-#pragma unroll
-                for (int u = 0; u < kVisits; ++u)
-                    if (id[u] < 0) r[u] = A.rec[~id[u]];
-#pragma unroll
-                for (int u = 0; u < kVisits; ++u) {
-                    nk[u] = 0;
-                    int32_t cnt = 1;
-                    if (id[u] < 0 && !accepts(A, s2, r[u], gb, ge, lo, hi)) {
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) nk[u] += r[u].kid[k] != kNone;
-                        if (nk[u] == 0)   // a leaf of several particles
-                            cnt = static_cast<int32_t>(r[u].end - (r[u].begin_level & ((1u << kBeginBits) - 1)));
-                        else
-                            sums += nk[u] + (1 << 16);
-                    }
-                    if (i0 + u < end) vcount[i0 + u] = cnt;
-                }
-                static_assert(kListWG * kVisits * 8 < 1 << 16, "a round's children fit below bit 16");
-                int32_t before;
-                const int32_t tot = wg_scan(sums, &before, s_wave);
-                int32_t at = fill + (before & 0xffff), ot = opened + (before >> 16);
-                fill += tot & 0xffff;
-                if (fill > A.cut_cap) continue;   // does not fit: the level is only counted
-                opened += tot >> 16;
-#pragma unroll
-                for (int u = 0; u < kVisits; ++u) {
-                    if (nk[u] == 0) continue;
-                    oat[ot] = i0 + u;
-                    ofirst[ot++] = at;
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        if (k < nk[u]) vid[at + k] = r[u].kid[k];
-                    at += nk[u];
-                }
-            }
-            if (fill > A.cut_cap) {
-                if (t == 0) atomicMax(&A.ctr->max_cut, fill);
-                overflow = true;
-                break;
-            }
-            begin = end;
-            end = fill;
-            ++levels;
-            if (t == 0) {
-                s_level[levels] = begin;
-                s_open[levels] = opened;
-            }
+        int32_t need = 0;
+        if (!walk_group(A, g, gb, ge, lo, hi, Walk{s_onode, s_ofirst, s_ocount, s_okids, kLdsOpened}, S, &need)) {
             __syncthreads();
-        }
-        int32_t len = 0;
-        if (!overflow) {
-            // up: entries under every opened cell (the last level has none)
-            for (int l = levels - 2; l >= 0; --l) {
-                const int32_t o1 = s_open[l + 1], stop = s_level[l + 2];
-                for (int32_t o = s_open[l] + t; o < o1; o += kListWG) {
-                    const int32_t f = ofirst[o], k = (o + 1 < o1 ? ofirst[o + 1] : stop) - f;
-                    int32_t sum = 0;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) sum += c < k ? abs(vcount[f + c]) : 0;
-                    vcount[oat[o]] = -sum;
-                }
-                __syncthreads();
+            int32_t* m = A.cut + static_cast<int64_t>(blockIdx.x) * walk_words(A.cut_cap);
+            const Walk w{m, m + A.cut_cap, m + 2 * static_cast<int64_t>(A.cut_cap),
+                         reinterpret_cast<uint16_t*>(m + 3 * static_cast<int64_t>(A.cut_cap)), A.cut_cap};
+            if (!walk_group(A, g, gb, ge, lo, hi, w, S, &need) && t == 0) {
+                atomicMax(&A.ctr->max_cut, need);
+                A.glen[g] = 0;
+                A.gstage[g] = -1;
             }
-            len = abs(vcount[0]);
-        }
-        __syncthreads();
-        if (t == 0) s_off = overflow ? ~0ull : atomicAdd(&A.ctr->staged, static_cast<unsigned long long>(len));
-        __syncthreads();
-        const unsigned long long off = s_off;
-        const bool fits = !overflow && off + static_cast<unsigned long long>(len) <= static_cast<unsigned long long>(A.stage_cap);
-        if (fits) {
-            // down: the children's places in the list, and the entries
-            int32_t* out = A.stage + off;
-            auto entry = [&](int32_t id, int32_t cnt, int32_t p) {
-                if (cnt == 1) {
-                    out[p] = id < 0 ? static_cast<int32_t>(A.n) + ~id : id;
-                } else {   // a leaf: its particles
-                    const int32_t first = static_cast<int32_t>(A.rec[~id].begin_level & ((1u << kBeginBits) - 1));
-                    for (int32_t q = 0; q < cnt; ++q) out[p + q] = first + q;
-                }
-            };
-            if (t == 0) {
-                if (vcount[0] > 0) entry(vid[0], vcount[0], 0);
-                else vcount[0] = 0;
-            }
-            __syncthreads();
-            for (int l = 0; l + 1 < levels; ++l) {
-                const int32_t o1 = s_open[l + 1], stop = s_level[l + 2];
-                for (int32_t o = s_open[l] + t; o < o1; o += kListWG) {
-                    const int32_t f = ofirst[o], k = (o + 1 < o1 ? ofirst[o + 1] : stop) - f;
-                    int32_t p = vcount[oat[o]];
-                    int32_t id[8], cnt[8];
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        cnt[c] = c < k ? vcount[f + c] : 0;
-                        id[c] = c < k ? vid[f + c] : 0;
-                    }
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        if (cnt[c] < 0) vcount[f + c] = p;
-                        else if (cnt[c] > 0) entry(id[c], cnt[c], p);
-                        p += abs(cnt[c]);
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        if (t == 0) {
-            A.glen[g] = overflow ? 0 : len;
-            A.gstage[g] = fits ? static_cast<int64_t>(off) : -1;
         }
         __syncthreads();
     }
@@ -861,7 +882,7 @@ int grow_particles(htd_tree* t, int64_t n) {
 // Work-groups of the list walk: one per group up to n_list_wg, fewer (down to
 // 64) where their scratch would pass 32 GB.
 int list_wgs(const htd_tree* t) {
-    const int64_t fit = (int64_t(32) << 30) / (16 * static_cast<int64_t>(t->cut_cap));
+    const int64_t fit = (int64_t(32) << 30) / (4 * walk_words(t->cut_cap));
     return static_cast<int>(std::min<int64_t>(t->G, std::min<int64_t>(t->n_list_wg, std::max<int64_t>(fit, 64))));
 }
 
@@ -960,7 +981,7 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
         const double sl = std::ldexp(t->root_h.side, -l);
         A.s2[l] = sl * sl;
     }
-    if ((rc = t->cut.grow(list_wgs(t) * 4 * static_cast<int64_t>(t->cut_cap)))) return rc;
+    if ((rc = t->cut.grow(list_wgs(t) * walk_words(t->cut_cap)))) return rc;
     if ((rc = t->stage.grow(std::max<int64_t>(t->stage.cap, 64 * n)))) return rc;
     for (int attempt = 0;; ++attempt) {
         int32_t max_cut = 0;
@@ -972,12 +993,12 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
         }
         if (attempt >= 32) return fail(HTD_ERANGE, "interaction lists did not fit after %d attempts", attempt + 1);
         if (max_cut > 0) {
-            // a group's visited cells outgrew the per-work-group scratch.  They were counted up to
-            // the level that did not fit, so the next size at least doubles, up to all cells at once.
+            // a group's opened cells outgrew the per-work-group scratch.  They were counted up to
+            // the level that did not fit, so the next size at least doubles, up to all nodes.
             if (int64_t(max_cut) > INT32_MAX / 2) return fail(HTD_ERANGE, "a group's list exceeds 2^30 entries");
-            t->cut_cap = static_cast<int32_t>(std::min<int64_t>(t->C, 2 * int64_t(max_cut)));
+            t->cut_cap = static_cast<int32_t>(std::min<int64_t>(t->M, 2 * int64_t(max_cut)));
             t->cut.release();
-            if ((rc = t->cut.grow(list_wgs(t) * 4 * static_cast<int64_t>(t->cut_cap)))) return rc;
+            if ((rc = t->cut.grow(list_wgs(t) * walk_words(t->cut_cap)))) return rc;
         }
         if (staged > static_cast<unsigned long long>(t->stage.cap)) {
             t->stage.release();
