@@ -14,9 +14,9 @@
 //      particle k are those of levels L_k ... E_k, and pre-order is the order
 //      of (first particle, level).  Per-particle counts and three prefix sums
 //      give every cell, node and group its pre-order number directly.
-//   3. node moments, bottom-up: one launch per level from the deepest up, one
-//      thread per node of that level adding its children's sums (or a leaf's
-//      particles) in order, then the means.
+//   3. node moments, bottom-up in one launch: 16 lanes to a node, one for each
+//      sum, add its children's sums (or a leaf's particles) in order; the last
+//      child of a node to be done goes on with the node.
 //   4. lists: one work-group per group goes down the tree a level at a time,
 //      visiting every cell once; the counts of list entries under each opened
 //      cell are then summed upwards and the entries placed on the way down
@@ -405,7 +405,8 @@ __device__ inline bool is_node(int32_t kid) { return kid < 0 && kid != kNone; }
 
 // Every node's range, level and children (its centre of mass follows the moments).
 __global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const int32_t* __restrict__ node_cell,
-                                                        const Cell* __restrict__ cell, NodeRec* __restrict__ rec) {
+                                                        const Cell* __restrict__ cell, NodeRec* __restrict__ rec,
+                                                        int32_t* __restrict__ parent, int32_t* __restrict__ arrived) {
     const int32_t q = blockIdx.x * kWG + threadIdx.x;
     if (q >= m_nodes) return;
     const int32_t ci = node_cell[q];
@@ -421,81 +422,94 @@ __global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const i
         if (ch < c.skip) {
             const Cell cc = cell[ch];
             r.kid[k] = cc.node >= 0 ? ~cc.node : cc.begin;
+            if (cc.node >= 0) parent[cc.node] = q;
             ch = cc.skip;
         }
     }
     rec[q] = r;
+    arrived[q] = 0;
+    if (q == 0) parent[0] = -1;
 }
 
 // Node moments, bottom-up, as the host builder defines them: a node's sums
 // S = (m, m x[3], m v[3], m a[3], m jerk[3]) start from zero and add, for a
 // split node, its children's S in key order (a single-particle child's S is
 // 0 + its rounded products), otherwise its particles' rounded products in
-// ascending order.  No fused multiply-add anywhere, so the bits match.  A
-// child is one level deeper than its parent, so one launch per level, from
-// the deepest up, sums every node of that level (at most eight children
-// each, or the particles of a leaf).  raw holds S, 13 doubles per node.
+// ascending order; the means are the sums divided by the mass.  No fused
+// multiply-add anywhere, so the bits match.  raw holds S, 13 doubles per node.
+//
+// Sixteen lanes (a DPP row) to a node, lane r < 13 for sum r.  The rows of the
+// nodes without node children begin; a row that has stored its node's sums
+// takes a ticket of the parent, and the one that takes the last goes on with
+// the parent, up to the root.  The sums go through to where every XCD sees
+// them (agent-scope stores and loads, which pass the L2s that are not coherent
+// with each other), and the ticket is taken once they are there.  The launch
+// is bound by that chain, a few dependent accesses per level, and at the large
+// sizes by the rows it keeps waiting.  At 2^20 and 20011 particles one launch
+// per level from the deepest up took 336 and 124 us, with 28 and 4 us for the
+// means after them; this one takes 254 and 41 us.  (Rows that take a new node
+// when they are done: 350 and 46 us.  Whole subtrees in LDS first, tickets for
+// the nodes above them: 237 and 97 us.)
 #pragma clang fp contract(off)
-__device__ inline void add_products(int64_t k, const double* __restrict__ sm, const double* __restrict__ sx,
-                                    const double* __restrict__ sv, const double* __restrict__ sa,
-                                    const double* __restrict__ sj, double (&u)[13]) {
-    const double mk = sm[k];
-    u[0] = u[0] + mk;
-    for (int d = 0; d < 3; ++d) {
-        u[1 + d] = u[1 + d] + mk * sx[3 * k + d];
-        u[4 + d] = u[4 + d] + mk * sv[3 * k + d];
-        u[7 + d] = u[7 + d] + mk * sa[3 * k + d];
-        u[10 + d] = u[10 + d] + mk * sj[3 * k + d];
-    }
-}
-
-__global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t level, int32_t m_nodes,
-                                                        const int32_t* __restrict__ node_level,
-                                                        const int32_t* __restrict__ node_cell,
-                                                        const Cell* __restrict__ cell, const double* __restrict__ sm,
+struct NodeOut {
+    double *m, *x, *v, *a, *j;
+};
+__global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t m_nodes, const int32_t* __restrict__ parent,
+                                                        int32_t* __restrict__ arrived, const double* __restrict__ sm,
                                                         const double* __restrict__ sx, const double* __restrict__ sv,
                                                         const double* __restrict__ sa, const double* __restrict__ sj,
-                                                        double* __restrict__ raw) {
-    const int32_t q = blockIdx.x * kWG + threadIdx.x;
-    if (q >= m_nodes || node_level[q] != level) return;
-    const int32_t ci = node_cell[q];
-    const Cell c = cell[ci];
-    double s[13];
-    for (int r = 0; r < 13; ++r) s[r] = 0.0;
-    if (c.split) {
-        for (int32_t ch = ci + 1; ch < c.skip;) {
-            const Cell cc = cell[ch];
-            double u[13];
-            if (cc.node >= 0) {
-                for (int r = 0; r < 13; ++r) u[r] = raw[13 * int64_t(cc.node) + r];
-            } else {
-                for (int r = 0; r < 13; ++r) u[r] = 0.0;
-                add_products(cc.begin, sm, sx, sv, sa, sj, u);
-            }
-            for (int r = 0; r < 13; ++r) s[r] = s[r] + u[r];
-            ch = cc.skip;
-        }
-    } else {
-        for (int64_t k = c.begin; k < c.end; ++k) add_products(k, sm, sx, sv, sa, sj, s);
-    }
-    for (int r = 0; r < 13; ++r) raw[13 * int64_t(q) + r] = s[r];
-}
-
-__global__ __launch_bounds__(kWG) void node_means_kernel(int32_t m_nodes, const double* __restrict__ raw,
-                                                         double* __restrict__ om, double* __restrict__ ox,
-                                                         double* __restrict__ ov, double* __restrict__ oa,
-                                                         double* __restrict__ oj, NodeRec* __restrict__ rec) {
-    const int32_t q = blockIdx.x * kWG + threadIdx.x;
+                                                        double* __restrict__ raw, NodeRec* rec, NodeOut o) {
+    const int r = threadIdx.x & 15;
+    int32_t q = static_cast<int32_t>((blockIdx.x * int64_t(kWG) + threadIdx.x) >> 4);
     if (q >= m_nodes) return;
-    const double* u = raw + 13 * int64_t(q);
-    const double M = u[0];
-    om[q] = M;
-    for (int d = 0; d < 3; ++d) {
-        ox[3 * q + d] = u[1 + d] / M;
-        ov[3 * q + d] = u[4 + d] / M;
-        oa[3 * q + d] = u[7 + d] / M;
-        oj[3 * q + d] = u[10 + d] / M;
-        rec[q].x[d] = u[1 + d] / M;
+    int32_t kid[8];
+    for (int c = 0; c < 8; ++c) kid[c] = rec[q].kid[c];
+    for (int c = 0; c < 8; ++c)
+        if (is_node(kid[c])) return;   // begun by the last of its children
+    const int d = (r + 2) % 3;         // component of the vector that lane r >= 1 sums
+    const double* src = r == 0 ? sm : (r < 4 ? sx : r < 7 ? sv : r < 10 ? sa : sj) + d;
+    double* dst = r == 0 ? o.m : (r < 4 ? o.x : r < 7 ? o.v : r < 10 ? o.a : o.j) + d;
+    auto product = [&](double mk, double f) { return r == 0 ? mk : mk * f; };
+    for (;;) {
+        double s = 0.0;
+        if (kid[0] == kNone) {   // a leaf of several particles
+            const int64_t e = rec[q].end;
+            for (int64_t k = first_of(rec[q]); k < e; ++k) s = s + product(sm[k], src[r == 0 ? k : 3 * k]);
+        } else {
+            double f[8], mk[8];   // every child's loads in flight before the first is added
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                f[c] = mk[c] = 0.0;
+                if (is_node(kid[c])) {
+                    if (r < 13)
+                        f[c] = __hip_atomic_load(raw + 13 * int64_t(~kid[c]) + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else if (kid[c] != kNone) {
+                    mk[c] = sm[kid[c]];
+                    f[c] = src[r == 0 ? int64_t(kid[c]) : 3 * int64_t(kid[c])];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (kid[c] != kNone) s = s + (is_node(kid[c]) ? f[c] : 0.0 + product(mk[c], f[c]));
+        }
+        if (r < 13) __hip_atomic_store(raw + 13 * int64_t(q) + r, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double M = wave_ops::first_of_row(s);
+        if (r < 13) {
+            const double mean = r == 0 ? M : s / M;
+            dst[r == 0 ? int64_t(q) : 3 * int64_t(q)] = mean;
+            if (r >= 1 && r < 4) rec[q].x[d] = mean;
+        }
+        const int32_t p = parent[q];
+        if (p < 0) return;
+        int32_t below = 0;   // node children of the parent
+        for (int c = 0; c < 8; ++c) kid[c] = rec[p].kid[c];
+        for (int c = 0; c < 8; ++c) below += is_node(kid[c]);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the sums are where every XCD sees them
+        int32_t ticket = 0;
+        if (r == 0) ticket = __hip_atomic_fetch_add(arrived + p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (wave_ops::first_of_row(ticket) != below - 1) return;   // a sibling is still on its way
+        asm volatile("" ::: "memory");                             // the children's sums are read after the ticket
+        q = p;
     }
 }
 #pragma clang fp contract(on)
@@ -819,6 +833,7 @@ struct htd_tree {
     DevBuf<int32_t> nlev, ncid;   // per node: level, cell index
     DevBuf<double> nraw;            // per node: the 13 sums of its moments
     DevBuf<NodeRec> nrec;           // per node: what the list walk reads
+    DevBuf<int32_t> npar, narr;     // per node: parent, children whose sums are done
     DevBuf<int64_t> nbeg, nend;
     // groups and lists
     DevBuf<int64_t> group_first, list_off, gstage, glen64;
@@ -947,6 +962,7 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
     if ((rc = t->cell.grow(t->C)) || (rc = t->nm.grow(M1)) || (rc = t->nx.grow(3 * M1)) ||
         (rc = t->nv.grow(3 * M1)) || (rc = t->na.grow(3 * M1)) || (rc = t->nj.grow(3 * M1)) ||
         (rc = t->nlev.grow(M1)) || (rc = t->ncid.grow(M1)) || (rc = t->nraw.grow(13 * M1)) || (rc = t->nrec.grow(M1)) ||
+        (rc = t->npar.grow(M1)) || (rc = t->narr.grow(M1)) ||
         (rc = t->nbeg.grow(M1)) || (rc = t->nend.grow(M1)))
         return rc;
     cells_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, n_leaf, t->key.p, t->lev.p, t->cbase.p, t->nbase.p,
@@ -957,12 +973,10 @@ int build(htd_tree* t, int64_t n, const double* x, const double* v, const double
     // 3. node moments
     if (t->M > 0) {
         const int32_t Mi = static_cast<int32_t>(t->M);
-        node_recs_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->ncid.p, t->cell.p, t->nrec.p);
-        for (int level = kDeepest; level >= 0; --level)
-            node_sums_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(level, Mi, t->nlev.p, t->ncid.p, t->cell.p, t->sm.p,
-                                                                 t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p);
-        node_means_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->nraw.p, t->nm.p, t->nx.p, t->nv.p, t->na.p,
-                                                              t->nj.p, t->nrec.p);
+        node_recs_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->ncid.p, t->cell.p, t->nrec.p, t->npar.p, t->narr.p);
+        node_sums_kernel<<<blocks_for(16 * int64_t(Mi), kWG), kWG, 0, s>>>(
+            Mi, t->npar.p, t->narr.p, t->sm.p, t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p, t->nrec.p,
+            NodeOut{t->nm.p, t->nx.p, t->nv.p, t->na.p, t->nj.p});
         HTD_HIP(hipGetLastError());
     }
     HTD_HIP(hipEventRecord(t->ev[4], s));
@@ -1072,7 +1086,8 @@ int htd_destroy(htd_tree* t) {
     t->ncell.release(); t->cbase.release(); t->nnode.release(); t->nbase.release(); t->gflag.release();
     t->gbase.release(); t->tmp.release(); t->part.release(); t->root.release(); t->tot.release();
     t->cell.release(); t->nm.release(); t->nx.release(); t->nv.release(); t->na.release(); t->nj.release();
-    t->nlev.release(); t->ncid.release(); t->nraw.release(); t->nrec.release(); t->nbeg.release();
+    t->nlev.release(); t->ncid.release(); t->nraw.release(); t->nrec.release(); t->npar.release();
+    t->narr.release(); t->nbeg.release();
     t->nend.release(); t->group_first.release(); t->list_off.release(); t->gstage.release(); t->glen64.release();
     t->glen.release(); t->cut.release(); t->stage.release(); t->entries.release(); t->ctr.release();
     delete t;
@@ -1167,6 +1182,7 @@ int htd_device_bytes(const htd_tree* t, size_t* bytes) {
     add(t->ncell), add(t->cbase), add(t->nnode), add(t->nbase), add(t->gflag), add(t->gbase);
     add(t->tmp), add(t->part), add(t->root), add(t->tot), add(t->cell);
     add(t->nm), add(t->nx), add(t->nv), add(t->na), add(t->nj), add(t->nlev), add(t->ncid), add(t->nraw), add(t->nrec);
+    add(t->npar), add(t->narr);
     add(t->nbeg), add(t->nend), add(t->group_first), add(t->list_off), add(t->gstage), add(t->glen64);
     add(t->glen), add(t->cut), add(t->stage), add(t->entries), add(t->ctr);
     *bytes = b;

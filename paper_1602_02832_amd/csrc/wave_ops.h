@@ -62,6 +62,13 @@ __device__ __forceinline__ V read_lane(V v, int l) {
     return by_halves(v, [l](uint32_t u) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(u, l)); });
 }
 
+// The value of the first lane of the same 16-lane row (all lanes of the row
+// must be active).
+template <class V>
+__device__ __forceinline__ V first_of_row(V v) {
+    return by_halves(v, [](uint32_t u) { return __builtin_amdgcn_update_dpp(0u, u, 0x150, 0xf, 0xf, true); });   // row_newbcast:0
+}
+
 // Pairwise tree over a wave, lane k combining with lane k + OFF for OFF =
 // FIRST, FIRST / 2, ..., LAST: with FIRST = 32 and LAST = 1 lane 0 ends with
 // the whole wave's reduction.
