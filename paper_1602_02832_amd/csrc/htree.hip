@@ -924,8 +924,7 @@ struct SchedEntry {
     int64_t n, chunk;
     int32_t nb, first_block;
     DevOut* out;
-    int32_t* active_host;     // nullptr: no host copy (device loop)
-    const int32_t* halt;      // device loop: nonzero once the loop has stopped; else nullptr
+    int32_t* active_host;
 };
 
 __device__ __forceinline__ const SchedEntry& sched_entry(const SchedEntry& e0, const SchedEntry* tab, int n_tab,
@@ -946,7 +945,6 @@ __global__ __launch_bounds__(kWG) void sched_min_kernel(SchedEntry e0, const Sch
     __shared__ double red[4];
     int b;
     const SchedEntry& e = sched_entry(e0, tab, n_tab, b);
-    if (e.halt && *e.halt) return;
     const int64_t lo = b * e.chunk, hi = lo + e.chunk < e.n ? lo + e.chunk : e.n;
     double v = HUGE_VAL;
     for (int64_t i = lo + threadIdx.x; i < hi; i += kWG) v = fmin(v, e.t0[i] + e.dt[i]);
@@ -961,7 +959,6 @@ __global__ __launch_bounds__(kWG) void sched_count_kernel(SchedEntry e0, const S
     __shared__ int cnt[4];
     int b;
     const SchedEntry& e = sched_entry(e0, tab, n_tab, b);
-    if (e.halt && *e.halt) return;
     double v = HUGE_VAL;
     for (int k = threadIdx.x; k < e.nb; k += kWG) v = fmin(v, e.bmin[k]);
     const double t_next = block_min(v, red);
@@ -985,7 +982,6 @@ __global__ __launch_bounds__(kWG) void sched_write_kernel(SchedEntry e0, const S
     __shared__ int wsum[4];
     int b;
     const SchedEntry& e = sched_entry(e0, tab, n_tab, b);
-    if (e.halt && *e.halt) return;
     if (e.bcount[b] == 0 && b != e.nb - 1) return;   // nothing due here (the last block reports the count)
     double v = HUGE_VAL;
     for (int k = threadIdx.x; k < e.nb; k += kWG) v = fmin(v, e.bmin[k]);
@@ -1021,7 +1017,7 @@ __global__ __launch_bounds__(kWG) void sched_write_kernel(SchedEntry e0, const S
             for (int w = 0; w < wave; ++w) at += wsum[w];
             if (due) {
                 e.active[at] = static_cast<int32_t>(i);
-                if (e.active_host) e.active_host[at] = static_cast<int32_t>(i);
+                e.active_host[at] = static_cast<int32_t>(i);
             }
             pos += wsum[0] + wsum[1] + wsum[2] + wsum[3];
         }
@@ -1054,45 +1050,59 @@ __device__ __forceinline__ double dev_quantise(double cap, double t1) {
     return jj >= -40 ? ldexp(1.0, jj) : 0.0;
 }
 
+// The step of particle i with acc, jerk and pot F at t1; the new state, potential
+// and j-record are written.  Returns the new block step (0 below the floor).
+template <class P>
+__device__ __forceinline__ double correct_particle(const DevState& s, void* rec_base, int32_t i, double t1, double eta,
+                                                   double dt_tree, const double* F) {
+#pragma clang fp contract(off)
+    const double D = t1 - s.t0[i];
+    const double h2 = 0.5 * D, h3 = D / 3.0;
+    const double D2 = D * D, D3 = D2 * D, D4 = D2 * D2, D5 = D4 * D;
+    double s2[3], s3[3], s2n[3], a1[3], j1[3];
+    for (int d = 0; d < 3; ++d) {
+        const int64_t k = 3 * static_cast<int64_t>(i) + d;
+        a1[d] = F[d];
+        j1[d] = F[3 + d];
+        const double xp = s.x[k] + D * (s.v[k] + h2 * (s.a[k] + h3 * s.j[k]));
+        const double vp = s.v[k] + D * (s.a[k] + h2 * s.j[k]);
+        const double diff = s.a[k] - a1[d];
+        s2[d] = (-6.0 * diff - D * (4.0 * s.j[k] + 2.0 * j1[d])) / D2;
+        s3[d] = (12.0 * diff + 6.0 * D * (s.j[k] + j1[d])) / D3;
+        s.x[k] = xp + s2[d] * (D4 / 24.0) + s3[d] * (D5 / 120.0);
+        s.v[k] = vp + s2[d] * (D3 / 6.0) + s3[d] * (D4 / 24.0);
+        s.a[k] = a1[d];
+        s.j[k] = j1[d];
+        s2n[d] = s2[d] + D * s3[d];
+    }
+    const double na = dev_len3(a1[0], a1[1], a1[2]), nj = dev_len3(j1[0], j1[1], j1[2]);
+    const double n2 = dev_len3(s2n[0], s2n[1], s2n[2]), n3 = dev_len3(s3[0], s3[1], s3[2]);
+    const double den = nj * n3 + n2 * n2;
+    const double raw = den > 0.0 ? sqrt(eta * (na * n2 + nj * nj) / den) : dt_tree;
+    double cap = dt_tree < raw ? dt_tree : raw;   // std::min(raw, dt_tree), then with 2 dt_old
+    cap = 2.0 * s.dt[i] < cap ? 2.0 * s.dt[i] : cap;
+    const double h = dev_quantise(cap, t1);
+    s.t0[i] = t1;
+    s.dt[i] = h;
+    s.pot[i] = F[6];
+    const int64_t k = 3 * static_cast<int64_t>(i);
+    store_rec<P>(static_cast<typename P::Rec*>(rec_base), i, t1, s.m[i], s.x + k, s.v + k, s.a + k, s.j + k);
+    return h;
+}
+
 // One context in a corrector launch: its state and records, its active set
 // (rows first_row .. first_row + n_active - 1 of the launch) and parameters.
-// Device loop state (ht_dev_run): the step in progress and the counts so far.
-struct DevLoop {
-    double t_cur;        // block time of the step in progress
-    int64_t n_corr;      // particles the corrector takes this step (0 once stopped)
-    int64_t steps, psteps, pairs;
-    int32_t halt;        // nonzero: every later kernel of the loop does nothing
-    int32_t stop_after;  // the step in progress is at the stop time
-    int32_t err;         // the device plan did not fit the context
-    int32_t pad;
-    // the call's parameters, so that the captured launches never change
-    double t_stop, eta, dt_tree;
-    int64_t max_steps;
-};
-
 struct CorrEntry {
     DevState s;
     void* rec;
     DevOut* out;
     int64_t n_active, first_row;
     double t1, eta, dt_tree;
-    const DevLoop* loop;   // device loop: count and block time read from it; else nullptr
-    // device loop: the split partials are summed here (in split order, as
-    // reduce_kernel does) instead of in a launch of their own.  qmap[q] is the
-    // split tile of active position q, or -1 when the force wrote q directly.
-    const int32_t* qmap;
-    const RTile* rtiles;
-    const double* partial;
 };
-
-constexpr int kCorrBatch = 8;   // split partials loaded together by the corrector
 
 template <class P>
 __global__ __launch_bounds__(kWG) void dev_correct_kernel(CorrEntry e0, const CorrEntry* tab, int n_tab,
-                                                          int64_t total, const int64_t* d_total) {
-#pragma clang fp contract(off)
-    // device loops: the row count is the loop's (one entry) or the batch table's (d_total)
-    if (total < 0) total = d_total ? *d_total : e0.loop->n_corr;
+                                                          int64_t total) {
     for (int64_t r = blockIdx.x * static_cast<int64_t>(kWG) + threadIdx.x; r < total;
          r += static_cast<int64_t>(gridDim.x) * kWG) {
         const CorrEntry* ep = &e0;
@@ -1105,118 +1115,78 @@ __global__ __launch_bounds__(kWG) void dev_correct_kernel(CorrEntry e0, const Co
             ep = tab + lo;
         }
         const CorrEntry& e = *ep;
-        const DevState& s = e.s;
-        typename P::Rec* rec = static_cast<typename P::Rec*>(e.rec);
         const int64_t q = r - e.first_row;
-        const double t1 = e.loop ? e.loop->t_cur : e.t1;
-        const int32_t i = s.active[q];
-        const double D = t1 - s.t0[i];
-        const double h2 = 0.5 * D, h3 = D / 3.0;
-        const double D2 = D * D, D3 = D2 * D, D4 = D2 * D2, D5 = D4 * D;
-        double s2[3], s3[3], s2n[3], a1[3], j1[3];
-        double fp = s.fpot[q];
-        const int32_t rq = e.qmap ? e.qmap[q] : -1;
-        if (rq >= 0) {   // the split partials of q, summed in split order
-            const RTile rt = e.rtiles[rq];
-            const int64_t slot = q - rt.act_begin;
-            double A[kOut];
-            const double* p0 = e.partial + (rt.pbase + slot) * kOut;
-            for (int u = 0; u < kOut; ++u) A[u] = p0[u];
-            // kCorrBatch splits' loads in flight at once, then added in split order
-            int b = 1;
-            for (; b + kCorrBatch <= rt.nsplit; b += kCorrBatch) {
-                double v[kCorrBatch][kOut];
-                for (int w = 0; w < kCorrBatch; ++w) {
-                    const double* pb = e.partial + (rt.pbase + static_cast<int64_t>(b + w) * rt.n_i + slot) * kOut;
-                    for (int u = 0; u < kOut; ++u) v[w][u] = pb[u];
-                }
-                for (int w = 0; w < kCorrBatch; ++w)
-                    for (int u = 0; u < kOut; ++u) A[u] += v[w][u];
-            }
-            for (; b < rt.nsplit; ++b) {
-                const double* pb = e.partial + (rt.pbase + static_cast<int64_t>(b) * rt.n_i + slot) * kOut;
-                for (int u = 0; u < kOut; ++u) A[u] += pb[u];
-            }
-            for (int d = 0; d < 3; ++d) {
-                s.acc[3 * q + d] = A[d];
-                s.jerk[3 * q + d] = A[3 + d];
-            }
-            fp = A[6];
-        }
+        double F[kOut];
         for (int d = 0; d < 3; ++d) {
-            const int64_t k = 3 * static_cast<int64_t>(i) + d;
-            a1[d] = s.acc[3 * q + d];
-            j1[d] = s.jerk[3 * q + d];
-            const double xp = s.x[k] + D * (s.v[k] + h2 * (s.a[k] + h3 * s.j[k]));
-            const double vp = s.v[k] + D * (s.a[k] + h2 * s.j[k]);
-            const double diff = s.a[k] - a1[d];
-            s2[d] = (-6.0 * diff - D * (4.0 * s.j[k] + 2.0 * j1[d])) / D2;
-            s3[d] = (12.0 * diff + 6.0 * D * (s.j[k] + j1[d])) / D3;
-            s.x[k] = xp + s2[d] * (D4 / 24.0) + s3[d] * (D5 / 120.0);
-            s.v[k] = vp + s2[d] * (D3 / 6.0) + s3[d] * (D4 / 24.0);
-            s.a[k] = a1[d];
-            s.j[k] = j1[d];
-            s2n[d] = s2[d] + D * s3[d];
+            F[d] = e.s.acc[3 * q + d];
+            F[3 + d] = e.s.jerk[3 * q + d];
         }
-        const double na = dev_len3(a1[0], a1[1], a1[2]), nj = dev_len3(j1[0], j1[1], j1[2]);
-        const double n2 = dev_len3(s2n[0], s2n[1], s2n[2]), n3 = dev_len3(s3[0], s3[1], s3[2]);
-        const double den = nj * n3 + n2 * n2;
-        const double eta = e.loop ? e.loop->eta : e.eta, dt_tree = e.loop ? e.loop->dt_tree : e.dt_tree;
-        const double raw = den > 0.0 ? sqrt(eta * (na * n2 + nj * nj) / den) : dt_tree;
-        double cap = dt_tree < raw ? dt_tree : raw;   // std::min(raw, dt_tree), then with 2 dt_old
-        cap = 2.0 * s.dt[i] < cap ? 2.0 * s.dt[i] : cap;
-        const double h = dev_quantise(cap, t1);
-        if (h == 0.0) e.out->below_floor = 1;
-        s.t0[i] = t1;
-        s.dt[i] = h;
-        s.pot[i] = fp;
-        const int64_t k = 3 * static_cast<int64_t>(i);
-        store_rec<P>(rec, i, t1, s.m[i], s.x + k, s.v + k, s.a + k, s.j + k);
+        F[6] = e.s.fpot[q];
+        if (correct_particle<P>(e.s, e.rec, e.s.active[q], e.t1, e.eta, e.dt_tree, F) == 0.0) e.out->below_floor = 1;
     }
+}
+
+constexpr int kSumBatch = 8;   // split partials loaded together
+
+// F = the sum of n split partials, kOut values each, `step` values apart, in
+// split order; kSumBatch splits' loads are in flight at once (one at a time,
+// each add waited on its own loads).
+__device__ __forceinline__ void sum_splits(const double* p, int64_t step, int n, double* F) {
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) F[u] = p[u];
+    int b = 1;
+    for (; b + kSumBatch <= n; b += kSumBatch) {
+        double v[kSumBatch][kOut];
+#pragma unroll
+        for (int w = 0; w < kSumBatch; ++w)
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) v[w][u] = p[(b + w) * step + u];
+#pragma unroll
+        for (int w = 0; w < kSumBatch; ++w)
+#pragma unroll
+            for (int u = 0; u < kOut; ++u) F[u] += v[w][u];
+    }
+    for (; b < n; ++b)
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) F[u] += p[b * step + u];
 }
 
 // ------------------------------------------------------------------------------------------------
-// Device loop (ht_dev_run): block steps queued back to back with no host
-// round trip.  Per step: the three scheduler passes, dev_plan_kernel (which
-// first takes the step or stops the loop), the force kernel (fixed grid, counts
-// read from the plan) and the corrector (count and block time read from the
-// loop; it also sums the split partials, so the step needs no reduce launch).
+// Device loops (ht_dev_run for one context, ht_batch_dev_run for many): block
+// steps queued back to back with no host round trip, three launches a step:
+//   loop_select_kernel   step 2 and the work plan: every scheduler block finds
+//                        the earliest block time from the blocks' earliest
+//                        times and lists its due particles; the last due block
+//                        of a context to be done takes the context's step (or
+//                        stops its loop) and plans it; the last context places
+//                        all contexts' items in one launch.
+//   force_kernel         fixed grid, the item count read from memory
+//   loop_correct_kernel  step 6 by scheduler blocks: split partials summed,
+//                        due particles corrected, the block's earliest next
+//                        time renewed.
+// A step is bound by its chain of dependent accesses and launches, not by
+// bytes.  With the scheduler in three launches, the planner (and for a batch
+// the placing of the items) in one each, six and seven a step, a step of
+// 16384 particles took 45 us and one of eight clusters of 4096 to 65536
+// particles 85 us of kernels; in three, 35 and 65 us.
+//
+// What one block hands to the block that plans (or one context to the one that
+// places the items) goes through agent-scope stores and loads, which every XCD
+// sees, and a ticket is taken once the stores are done; everything else passes
+// at a launch's end.
 
-// Take the step if its block time is at most the stop time, else stop the
-// loop (and every later kernel with it).
-__device__ inline void loop_gate(DevLoop* L, const DevOut* o) {
-    const double t_stop = L->t_stop;
-    const int64_t max_steps = L->max_steps;
-    if (L->halt) {
-        L->n_corr = 0;
-        return;
-    }
-    const double t = o->t_next;
-    const int64_t na = o->n_active;
-    if (L->stop_after || o->below_floor || !(t <= t_stop) || L->steps >= max_steps || na < 1) {
-        L->halt = 1;
-        L->n_corr = 0;
-        return;
-    }
-    L->t_cur = t;
-    L->n_corr = na;
-    L->steps += 1;
-    L->psteps += na;
-    if (t == t_stop) L->stop_after = 1;
-}
-
-// Start of a device-loop call: its parameters, counts cleared.
-__global__ void loop_init_kernel(DevLoop* L, DevOut* o, double t_stop, int64_t max_steps, double eta,
-                                 double dt_tree) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    DevLoop z{};
-    z.t_stop = t_stop;
-    z.max_steps = max_steps;
-    z.eta = eta;
-    z.dt_tree = dt_tree;
-    *L = z;
-    *o = DevOut{};
-}
+struct DevLoop {
+    double t_cur;        // block time of the step in progress
+    int64_t n_corr;      // particles the corrector takes this step (0 once stopped)
+    int64_t steps, psteps, pairs;
+    int32_t halt;        // nonzero: every later kernel of the loop does nothing
+    int32_t stop_after;  // the step in progress is at the stop time
+    int32_t err;         // the device plan did not fit the context
+    int32_t ticket;      // due blocks done in this step
+    // the call's parameters, so that the captured launches never change
+    double t_stop, eta, dt_tree;
+    int64_t max_steps;
+};
 
 // One tile of the device plan.
 struct DTile {
@@ -1225,6 +1195,122 @@ struct DTile {
     int32_t tl, pad;
     double cost;
 };
+
+// Where the corrector finds the force of an active position: split s of nsplit
+// is partial slot first + s * stride; first < 0: the force kernel's output.
+struct QSum {
+    int64_t first;
+    int32_t stride, nsplit;
+};
+
+// One context in a device loop (a table in device memory).
+struct LoopEntry {
+    DevState s;
+    void* rec;
+    DevLoop* loop;
+    DevOut* dout;
+    double* brest;        // per scheduler block: earliest next time of the particles not due
+    int32_t* boff;        // per due block: its first active position
+    uint64_t* due;        // per particle slot of a block: its due particles, (group << 32) | index
+    int64_t n;
+    int32_t chunk, nb, first_block;   // scheduler blocks of chunk particles; the first one in the launches
+    // planner
+    const int32_t* pgroup;     // [N] group of every particle
+    const int64_t* loff;       // [groups + 1] list offsets
+    QSum* qsum;                // out: [active positions]
+    int32_t* qk;               // scratch: first active position of each active group, then n_active
+    int32_t* qg;               // scratch: group of each active group
+    DTile* tiles;              // scratch
+    Item* items;               // out
+    int64_t items_max, partial_max;
+    double gather_cost, target_items;
+    Desc d;                    // the context's descriptor (t is set here)
+    int8_t first_tile[257];
+};
+
+// What a context's planner hands to the placing of the items.
+struct LoopSum {
+    int64_t items, rows;   // this step's work items and active particles
+    int64_t running;       // the context takes part in the next step
+};
+
+// Device words of a loop call.
+struct LoopCounts {
+    int64_t items, rows;   // this step: work items and active particles of all contexts
+    int64_t step;          // steps in which some context stepped
+    int64_t expect;        // contexts that run this step
+    int32_t ticket, pad;   // contexts planned in this step
+};
+
+// Per-call parameters of one context (pinned host memory, read by the first kernel).
+struct LoopParams {
+    double t_stop, eta, dt_tree;
+    int64_t max_steps;
+};
+static_assert(sizeof(LoopParams) == 4 * 8, "LoopParams is 4 words");
+
+// What a call reports per context (pinned host memory, written by the results kernel).
+struct LoopResult {
+    int64_t steps, psteps, pairs;
+    double t_cur;
+    int32_t err, below_floor;
+};
+
+template <class V>
+__device__ __forceinline__ V agent_load(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class V>
+__device__ __forceinline__ void agent_store(V* p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// All of the wave's stores so far have reached the scope they were made for.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+constexpr int kPlanWG = 512;
+constexpr int kPlanWaves = kPlanWG / 64;
+static_assert(kSchedBlocks <= 2 * kPlanWG && kMaxBatch <= 2 * kPlanWG, "two blocks or contexts a thread");
+
+// Start of a call: every context's loop state from its parameters, counts cleared.
+__global__ __launch_bounds__(kWG) void loop_init_kernel(const LoopEntry* __restrict__ tab, int n_tab,
+                                                        const LoopParams* prm, LoopSum* sums, LoopCounts* cnt) {
+    __shared__ int s_run;
+    if (threadIdx.x == 0) s_run = 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n_tab; k += kWG) {
+        const uint64_t* w = reinterpret_cast<const uint64_t*>(prm + k);
+        DevLoop z{};
+        z.t_stop = __builtin_bit_cast(double, host_word(w));
+        z.eta = __builtin_bit_cast(double, host_word(w + 1));
+        z.dt_tree = __builtin_bit_cast(double, host_word(w + 2));
+        z.max_steps = static_cast<int64_t>(host_word(w + 3));
+        z.halt = z.max_steps < 1;   // a context that sits out this call: no kernel touches its state
+        *tab[k].loop = z;
+        *tab[k].dout = DevOut{};
+        sums[k] = LoopSum{};
+        if (!z.halt) atomicAdd(&s_run, 1);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        LoopCounts z{};
+        z.expect = s_run;
+        *cnt = z;
+    }
+}
+
+// Then the earliest next time of every scheduler block.
+__global__ __launch_bounds__(kWG) void loop_min_kernel(const LoopEntry* __restrict__ tab,
+                                                       const uint16_t* __restrict__ block_ctx, int n_tab) {
+    __shared__ double red[4];
+    const LoopEntry& e = tab[n_tab > 1 ? block_ctx[blockIdx.x] : 0];
+    if (e.loop->halt) return;
+    const int b = blockIdx.x - e.first_block;
+    const int64_t lo = static_cast<int64_t>(b) * e.chunk, hi = lo + e.chunk < e.n ? lo + e.chunk : e.n;
+    double v = HUGE_VAL;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kWG) v = fmin(v, e.s.t0[i] + e.s.dt[i]);
+    v = block_min(v, red);
+    if (threadIdx.x == 0) e.s.bmin[b] = v;
+}
 
 // The group of every particle, from the group offsets (after each change of the lists).
 __global__ __launch_bounds__(kWG) void group_of_kernel(int64_t n, const int64_t* __restrict__ gfirst, int32_t n_groups,
@@ -1239,96 +1325,149 @@ __global__ __launch_bounds__(kWG) void group_of_kernel(int64_t n, const int64_t*
     pgroup[i] = lo;
 }
 
-struct PlanArgs {
-    DevLoop* loop;
-    const DevOut* dout;        // the scheduler's results (block time, count)
-    const int32_t* active;     // this step's active particles, ascending (the scheduler's list)
-    const int32_t* pgroup;     // [N] group of every particle
-    const int64_t* loff;       // [groups + 1] list offsets
-    int32_t* qmap;             // out: split tile of each active position or -1
-    int32_t* qk;               // scratch: first active position of each active group, then n_active
-    int32_t* qg;               // scratch: group of each active group
-    DTile* tiles;              // scratch
-    Entry* tab;                // out: the launch table (one entry)
-    Item* items;               // out
-    RTile* rtiles;             // out
-    int64_t items_max, partial_max;
-    double gather_cost, target_items;
-    Desc d;                    // the context's descriptor (t, active and outputs set here)
-    int8_t first_tile[257];
+struct PlanLds {
+    double wd[kPlanWaves];
+    int64_t w64[3][kPlanWaves];
+    int32_t boff[2 * kPlanWG];   // first active position of every scheduler block
+    // up to kPlanWG active particles (the common small step): the active groups and
+    // the tiles stay in LDS instead of going through memory between the phases
+    int32_t qk[kPlanWG + 1], qg[kPlanWG];
+    DTile tiles[kPlanWG];
+    int32_t g[kPlanWG];
+    int32_t g_last, go, last;
+    int8_t ft[260];              // the tile table, indexed per thread
 };
 
-constexpr int kPlanWG = 512;
-
-// Exclusive prefix sum over the work-group (kPlanWG threads); returns the total.
-template <class V>
-__device__ inline V plan_scan(V v, V* excl, V* s_wave) {
+// Exclusive prefix sums over the work-group (kPlanWG threads) of K values at
+// once; v becomes the sums before the thread's own, total the totals.
+template <int K>
+__device__ inline void plan_scan(int64_t (&v)[K], int64_t (&total)[K], PlanLds& S) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const V x = wave_ops::scan_inclusive(v);
-    if (lane == 63) s_wave[wave] = x;
-    __syncthreads();
-    V before = 0, total = 0;
-    for (int w = 0; w < kPlanWG / 64; ++w) {
-        const V sw = s_wave[w];
-        if (w < wave) before += sw;
-        total += sw;
+    int64_t x[K];
+    for (int k = 0; k < K; ++k) {
+        x[k] = wave_ops::scan_inclusive(v[k]);
+        if (lane == 63) S.w64[k][wave] = x[k];
     }
-    *excl = before + x - v;
     __syncthreads();
-    return total;
+    for (int k = 0; k < K; ++k) {
+        int64_t before = 0, all = 0;
+        for (int w = 0; w < kPlanWaves; ++w) {
+            const int64_t sw = S.w64[k][w];
+            if (w < wave) before += sw;
+            all += sw;
+        }
+        v[k] = before + x[k] - v[k];
+        total[k] = all;
+    }
+    __syncthreads();
+}
+
+// Minimum over the work-group (kPlanWG threads).
+__device__ inline double plan_min(double v, PlanLds& S) {
+    v = wave_ops::tree<32, 1>(v, [](double p, double q) { return fmin(p, q); });
+    if ((threadIdx.x & 63) == 0) S.wd[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = S.wd[0];
+    for (int w = 1; w < kPlanWaves; ++w) v = fmin(v, S.wd[w]);
+    __syncthreads();
+    return v;
+}
+
+// Take the step at t with n active particles if t is at most the stop time,
+// else stop the loop (and every later kernel with it).
+__device__ inline bool loop_gate(DevLoop* L, const DevOut* o, double t, int64_t n) {
+    DevLoop z = *L;
+    const bool go = !(z.stop_after || o->below_floor || !(t <= z.t_stop) || z.steps >= z.max_steps || n < 1);
+    if (!go) {
+        L->halt = 1;
+        L->n_corr = 0;
+        return false;
+    }
+    L->t_cur = t;
+    L->n_corr = n;
+    L->steps = z.steps + 1;
+    L->psteps = z.psteps + n;
+    if (t == z.t_stop) L->stop_after = 1;
+    return true;
 }
 
 // The host planner's work items (plan()), built on the device by one
 // work-group: active groups, least-cost tiles, cost-based splits with the same
 // quantum (the costs are whole numbers when the gather cost is, so their sum
 // does not depend on the order of addition), in group order.  The order of the
-// items does not change any result.
-__device__ __forceinline__ void plan_body(const PlanArgs& A) {
-    __shared__ int64_t s_w64[kPlanWG / 64];
-    __shared__ double s_wd[kPlanWG / 64];
-    __shared__ int8_t s_ft[260];   // the tile table, indexed per thread
-    // up to kPlanWG active particles (the common small step): the active groups and
-    // the tiles stay in LDS instead of going through memory between the phases
-    __shared__ int32_t s_qk[kPlanWG + 1], s_qg[kPlanWG];
-    __shared__ DTile s_tiles[kPlanWG];
-    __shared__ int32_t s_g[kPlanWG];
-    __shared__ int32_t s_glast;
+// items does not change any result.  due0, due1: whether scheduler blocks 2t
+// and 2t + 1 of thread t are due.  Returns the number of items.
+__device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_next, bool due0, bool due1, Entry* out,
+                                    LoopSum* sum) {
     const int t = threadIdx.x;
-    if (t < 257) s_ft[t] = A.first_tile[t];
-    if (t == 0) s_glast = -1;
-    DevLoop* L = A.loop;
-    if (t == 0) loop_gate(L, A.dout);   // take this step or stop the loop
-    __syncthreads();
-    if (L->halt) {
-        if (t == 0) {
-            A.tab->n_items = 0;
-            A.tab->n_rtiles = 0;
-        }
-        return;
+    if (t < 257) S.ft[t] = e.first_tile[t];
+    if (t == 0) S.g_last = -1;
+    int64_t n;
+    {   // active positions of the due blocks
+        const int32_t c0 = due0 ? agent_load(e.s.bcount + 2 * t) : 0, c1 = due1 ? agent_load(e.s.bcount + 2 * t + 1) : 0;
+        int64_t v[1] = {c0 + static_cast<int64_t>(c1)}, tot[1];
+        plan_scan(v, tot, S);
+        n = tot[0];
+        S.boff[2 * t] = static_cast<int32_t>(v[0]);
+        S.boff[2 * t + 1] = static_cast<int32_t>(v[0]) + c0;
+        if (due0) e.boff[2 * t] = static_cast<int32_t>(v[0]);
+        if (due1) e.boff[2 * t + 1] = static_cast<int32_t>(v[0]) + c0;
     }
-    const int64_t n = L->n_corr;
+    if (t == 0) S.go = loop_gate(e.loop, e.dout, t_next, n);   // take this step or stop the loop
+    __syncthreads();
+    *sum = LoopSum{0, 0, S.go};
+    if (!S.go) return 0;
+    sum->rows = n;
     const bool small = n <= kPlanWG;
-    int32_t* QK = small ? s_qk : A.qk;
-    int32_t* QG = small ? s_qg : A.qg;
-    DTile* TL = small ? s_tiles : A.tiles;
-    // 1-2. the group of every active particle, and the active groups (first active
-    // position and group, in order); a particle's predecessor's group comes through LDS
+    int32_t* QK = small ? S.qk : e.qk;
+    int32_t* QG = small ? S.qg : e.qg;
+    DTile* TL = small ? S.tiles : e.tiles;
+    // 1-2. the active particles in ascending order, and the active groups (first
+    // active position and group, in order); four positions a thread, and a
+    // position's predecessor's group comes through LDS
     int64_t nq = 0;
-    for (int64_t base = 0; base < n; base += kPlanWG) {
-        const int64_t k = base + t;
-        const int32_t g = k < n ? A.pgroup[A.active[k]] : -1;
-        s_g[t] = g;
-        __syncthreads();
-        const int32_t gp = t > 0 ? s_g[t - 1] : s_glast;
-        const int64_t f = (k < n && (k == 0 || g != gp)) ? 1 : 0;
-        int64_t ex;
-        const int64_t tot = plan_scan<int64_t>(f, &ex, s_w64);
-        if (f) {
-            QK[nq + ex] = static_cast<int32_t>(k);
-            QG[nq + ex] = g;
+    constexpr int kPos = 4;
+    for (int64_t base = 0; base < n; base += kPos * kPlanWG) {
+        const int64_t q0 = base + kPos * t;
+        int32_t g[kPos];
+        int blk = 0;
+        if (q0 < n)   // the last block that begins at or before q0
+            for (int step = kPlanWG; step > 0; step >>= 1)
+                if (blk + step < e.nb && S.boff[blk + step] <= q0) blk += step;
+        uint64_t w[kPos];
+#pragma unroll
+        for (int u = 0; u < kPos; ++u) {
+            w[u] = 0;
+            if (q0 + u >= n) continue;
+            while (blk + 1 < e.nb && S.boff[blk + 1] <= q0 + u) ++blk;
+            w[u] = agent_load(e.due + static_cast<int64_t>(blk) * e.chunk + (q0 + u - S.boff[blk]));
         }
-        if (t == kPlanWG - 1) s_glast = g;
-        nq += tot;
+#pragma unroll
+        for (int u = 0; u < kPos; ++u) {
+            g[u] = q0 + u < n ? static_cast<int32_t>(w[u] >> 32) : -1;
+            if (q0 + u < n) e.s.active[q0 + u] = static_cast<int32_t>(w[u]);
+        }
+        S.g[t] = g[kPos - 1];
+        __syncthreads();
+        int32_t prev = t > 0 ? S.g[t - 1] : S.g_last;
+        int64_t v[1] = {0}, tot[1];
+        bool head[kPos];
+#pragma unroll
+        for (int u = 0; u < kPos; ++u) {
+            head[u] = q0 + u < n && (q0 + u == 0 || g[u] != prev);
+            v[0] += head[u];
+            prev = g[u];
+        }
+        plan_scan(v, tot, S);
+        int64_t at = nq + v[0];
+#pragma unroll
+        for (int u = 0; u < kPos; ++u)
+            if (head[u]) {
+                QK[at] = static_cast<int32_t>(q0 + u);
+                QG[at++] = g[u];
+            }
+        if (t == kPlanWG - 1) S.g_last = g[kPos - 1];
+        nq += tot[0];
     }
     if (t == 0) QK[nq] = static_cast<int32_t>(n);
     __syncthreads();
@@ -1338,259 +1477,307 @@ __device__ __forceinline__ void plan_body(const PlanArgs& A) {
     int64_t pairs = 0;
     for (int64_t base = 0; base < nq; base += kPlanWG) {
         const int64_t q = base + t;
-        int64_t cnt = 0;
-        if (q < nq)
-            for (int64_t r = QK[q + 1] - QK[q]; r > 0;) {
-                const int tl = r >= 256 ? 8 : s_ft[r];
-                r -= r < (int64_t(1) << tl) ? r : (int64_t(1) << tl);
-                ++cnt;
-            }
-        int64_t ex;
-        const int64_t tot = plan_scan<int64_t>(cnt, &ex, s_w64);
+        int64_t v[1] = {0}, tot[1];
+        int64_t jb = 0, je = 0;
+        int32_t r0 = 0, tb = 0;
         if (q < nq) {
             const int32_t g = QG[q];
-            const int64_t jb = A.loff[g], je = A.loff[g + 1];
-            const int64_t rounds = (je - jb + kRound - 1) / kRound;
-            int64_t at = ntile + ex;
-            int64_t tb = QK[q];
-            for (int64_t r = QK[q + 1] - QK[q]; r > 0; ++at) {
-                const int tl = r >= 256 ? 8 : s_ft[r];
-                const int64_t ni = r < (int64_t(1) << tl) ? r : (int64_t(1) << tl);
-                const double cost = static_cast<double>(rounds) * (A.gather_cost + static_cast<double>(1 << tl));
-                TL[at] = DTile{jb, je, static_cast<int32_t>(tb), static_cast<int32_t>(ni), tl, 0, cost};
+            jb = e.loff[g];
+            je = e.loff[g + 1];
+            tb = QK[q];
+            r0 = QK[q + 1] - tb;
+            for (int32_t r = r0; r > 0; ++v[0]) r -= min(r, 1 << (r >= 256 ? 8 : S.ft[r]));
+        }
+        plan_scan(v, tot, S);
+        if (q < nq) {
+            const uint32_t rounds = static_cast<uint32_t>((je - jb + kRound - 1) / kRound);
+            int64_t at = ntile + v[0];
+            for (int32_t r = r0; r > 0; ++at) {
+                const int tl = r >= 256 ? 8 : S.ft[r];
+                const int32_t ni = min(r, 1 << tl);
+                const double cost = static_cast<double>(rounds) * (e.gather_cost + static_cast<double>(1 << tl));
+                TL[at] = DTile{jb, je, tb, ni, tl, 0, cost};
                 total += cost;
                 pairs += ni * (je - jb);
                 tb += ni;
                 r -= ni;
             }
         }
-        ntile += tot;
+        ntile += tot[0];
     }
     {   // whole-number costs: the sum is exact in any order
-        double ex;
-        total = plan_scan<double>(total, &ex, s_wd);
-        int64_t ep;
-        pairs = plan_scan<int64_t>(pairs, &ep, s_w64);
-    }
-    __syncthreads();
-    // 4. splits: the quantum doubles until the plan fits, as on the host
-    double quantum = total / A.target_items;
-    int attempt = 0;
-    int64_t n_items = 0, n_parts = 0;
-    for (;; ++attempt) {
-        int64_t ci = 0, cp = 0;
-        for (int64_t q = t; q < ntile; q += kPlanWG) {
-            const DTile T = TL[q];
-            const int64_t rsz = int64_t(kRound) * round_mult(1 << T.tl);
-            const int64_t rounds = (T.je - T.jb + rsz - 1) / rsz;
-            int64_t ns = (attempt > 60 || !(quantum > 0.0)) ? 1 : static_cast<int64_t>(ceil(T.cost / quantum));
-            ns = ns < rounds ? ns : rounds;
-            ns = ns > 1 ? ns : 1;
-            if (ns == 1) {
-                ci += 1;
-            } else {
-                const int64_t per = (rounds + ns - 1) / ns * rsz;
-                const int64_t nsu = (T.je - T.jb + per - 1) / per;
-                ci += nsu;
-                cp += nsu * T.ni;
-            }
+        const int lane = t & 63, wave = t >> 6;
+        total = wave_ops::tree<32, 1>(total, [](double p, double q) { return p + q; });
+        pairs = wave_ops::tree<32, 1>(pairs, [](int64_t p, int64_t q) { return p + q; });
+        if (lane == 0) {
+            S.wd[wave] = total;
+            S.w64[0][wave] = pairs;
         }
-        int64_t ex;
-        n_items = plan_scan<int64_t>(ci, &ex, s_w64);
-        n_parts = plan_scan<int64_t>(cp, &ex, s_w64);
-        if (n_items <= A.items_max && n_parts <= A.partial_max) break;
+        __syncthreads();
+        total = 0.0;
+        pairs = 0;
+        for (int w = 0; w < kPlanWaves; ++w) {
+            total += S.wd[w];
+            pairs += S.w64[0][w];
+        }
+        __syncthreads();
+    }
+    // 4. splits: the quantum doubles until the plan fits, as on the host
+    double quantum = total / e.target_items;
+    int attempt = 0;
+    // how tile T is split: per entries a split (0: one item), into ns items
+    auto split = [&](const DTile& T, int64_t* per) {
+        const uint32_t rsz = static_cast<uint32_t>(kRound * round_mult(1 << T.tl));
+        const uint32_t rounds = static_cast<uint32_t>((T.je - T.jb + rsz - 1) / rsz);
+        *per = 0;
+        if (attempt > 60 || !(quantum > 0.0)) return 1u;
+        const double want = ceil(T.cost / quantum);
+        const uint32_t ns = want < static_cast<double>(rounds) ? static_cast<uint32_t>(want) : rounds;
+        if (ns <= 1) return 1u;
+        const uint32_t rper = (rounds + ns - 1) / ns;   // whole rounds
+        *per = static_cast<int64_t>(rper) * rsz;
+        return (rounds + rper - 1) / rper;
+    };
+    int64_t v[2], tot[2];
+    for (;; ++attempt) {
+        v[0] = v[1] = 0;
+        for (int64_t q = t; q < ntile; q += kPlanWG) {
+            int64_t per;
+            const uint32_t ns = split(TL[q], &per);
+            v[0] += ns;
+            if (per) v[1] += static_cast<int64_t>(ns) * TL[q].ni;
+        }
+        plan_scan(v, tot, S);
+        if (tot[0] <= e.items_max && tot[1] <= e.partial_max) break;
         if (attempt > 60) {   // does not fit: stop the loop before this step's force
             if (t == 0) {
+                DevLoop* L = e.loop;
                 L->err = 1;
                 L->halt = 1;
                 L->steps -= 1;
                 L->psteps -= n;
                 L->n_corr = 0;
-                A.tab->n_items = 0;
-                A.tab->n_rtiles = 0;
             }
-            return;
+            *sum = LoopSum{0, 0, 0};
+            return 0;
         }
         quantum *= 2.0;
     }
-    // 5. items and split tiles, in tile order
-    int64_t io = 0, po = 0, ro = 0;
+    // 5. items, in tile order
+    const int64_t n_items = tot[0];
+    int64_t io = 0, po = 0;
     for (int64_t base = 0; base < ntile; base += kPlanWG) {
         const int64_t q = base + t;
-        int64_t ci = 0, cp = 0, cr = 0, ns = 1, per = 0, nsu = 1;
+        int64_t per = 0;
+        uint32_t ns = 0;
         DTile T{};
         if (q < ntile) {
             T = TL[q];
-            const int64_t rsz = int64_t(kRound) * round_mult(1 << T.tl);
-            const int64_t rounds = (T.je - T.jb + rsz - 1) / rsz;
-            ns = (attempt > 60 || !(quantum > 0.0)) ? 1 : static_cast<int64_t>(ceil(T.cost / quantum));
-            ns = ns < rounds ? ns : rounds;
-            ns = ns > 1 ? ns : 1;
-            if (ns == 1) {
-                ci = 1;
-            } else {
-                per = (rounds + ns - 1) / ns * rsz;
-                nsu = (T.je - T.jb + per - 1) / per;
-                ci = nsu;
-                cp = nsu * T.ni;
-                cr = 1;
-            }
+            ns = split(T, &per);
         }
-        int64_t ei, ep, er;
-        const int64_t ti = plan_scan<int64_t>(ci, &ei, s_w64);
-        const int64_t tp = plan_scan<int64_t>(cp, &ep, s_w64);
-        const int64_t tr = plan_scan<int64_t>(cr, &er, s_w64);
+        if (ntile > kPlanWG) {   // else the sums of the splits above are these
+            v[0] = ns;
+            v[1] = per ? static_cast<int64_t>(ns) * T.ni : 0;
+            plan_scan(v, tot, S);
+        }
         if (q < ntile) {
             const int16_t ni = static_cast<int16_t>(T.ni), tl = static_cast<int16_t>(T.tl);
-            if (ns == 1) {
-                A.items[io + ei] = Item{T.jb, T.je, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
-                for (int32_t u = 0; u < T.ni; ++u) A.qmap[T.tb + u] = -1;
+            Item* it = e.items + io + v[0];
+            if (per == 0) {
+                *it = Item{T.jb, T.je, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
+                for (int32_t u = 0; u < T.ni; ++u) e.qsum[T.tb + u] = QSum{-1, 0, 0};
             } else {
-                for (int32_t u = 0; u < T.ni; ++u) A.qmap[T.tb + u] = static_cast<int32_t>(ro + er);
-                const int64_t pb = po + ep;
-                int64_t s = 0;
-                for (int64_t b = T.jb; b < T.je; b += per, ++s)
-                    A.items[io + ei + s] = Item{b, b + per < T.je ? b + per : T.je, pb + s * T.ni, T.tb, ni,
-                                                static_cast<int16_t>(s == 0 ? tl | kSelfTerm : tl)};
-                A.rtiles[ro + er] = RTile{pb, T.tb, T.ni, static_cast<int32_t>(nsu), 0};
+                const int64_t pb = po + v[1];
+                for (int32_t u = 0; u < T.ni; ++u) e.qsum[T.tb + u] = QSum{pb + u, T.ni, static_cast<int32_t>(ns)};
+                int64_t b = T.jb;
+                for (uint32_t s = 0; s < ns; ++s, b += per)
+                    it[s] = Item{b, b + per < T.je ? b + per : T.je, pb + static_cast<int64_t>(s) * T.ni, T.tb, ni,
+                                 static_cast<int16_t>(s == 0 ? tl | kSelfTerm : tl)};
             }
         }
-        io += ti;
-        po += tp;
-        ro += tr;
+        io += tot[0];
+        po += tot[1];
     }
     if (t == 0) {
-        Entry& e = *A.tab;
-        e.d = A.d;
-        e.d.t = L->t_cur;
-        e.items = A.items;
-        e.rtiles = A.rtiles;
-        e.first_item = 0;
-        e.first_rtile = 0;
-        e.n_items = io;
-        e.n_rtiles = ro;
-        L->pairs += pairs;
+        Entry& o = *out;
+        o.d = e.d;
+        o.d.t = t_next;
+        o.items = e.items;
+        o.rtiles = nullptr;   // the corrector sums the splits
+        o.first_rtile = 0;
+        o.n_items = n_items;
+        o.n_rtiles = 0;
+        e.loop->pairs += pairs;
     }
+    sum->items = n_items;
+    return n_items;
 }
 
-__global__ __launch_bounds__(kPlanWG) void dev_plan_kernel(PlanArgs A) { plan_body(A); }
-
-// ------------------------------------------------------------------------------------------------
-// Batched device loop (ht_batch_dev_run): the device loop of every context of
-// a batch in one chain of launches per engine step.  Each context keeps its
-// own loop state, scheduler, planner scratch, plan and partials; per engine
-// step the three scheduler passes run over all contexts' blocks, one planner
-// work-group per context plans that context's step, a one-work-group kernel
-// places the contexts' items and corrector rows one after another, and one
-// force launch and one corrector launch serve them all.  A context's plan is
-// the one it makes alone, so its bits are the same alone and in any batch.
-
-// One planner work-group per context.
-__global__ __launch_bounds__(kPlanWG) void dev_plan_batch_kernel(const PlanArgs* __restrict__ tab) {
-    plan_body(tab[blockIdx.x]);
-}
-
-// A context's loop state and scheduler results.
-struct LoopCtx {
-    DevLoop* loop;
-    DevOut* dout;
-};
-
-// Device words of a batched loop call.
-struct LoopCounts {
-    int64_t items, rtiles, rows;   // this engine step: work items, split tiles and corrector rows of all contexts
-    int64_t step;                  // engine steps in which some context stepped
-};
-
-// Per-call parameters of one context (pinned host memory, read by the init kernel).
-struct LoopParams {
-    double t_stop, eta, dt_tree;
-    int64_t max_steps;
-};
-static_assert(sizeof(LoopParams) == 4 * 8, "LoopParams is 4 words");
-
-// What a call reports per context (pinned host memory, written by the results kernel).
-struct LoopResult {
-    int64_t steps, psteps, pairs;
-    double t_cur;
-    int32_t err, below_floor;
-};
-
-constexpr int kLoopTabWG = 1024;   // threads of the table kernel (one per context: kMaxBatch)
-static_assert(kLoopTabWG >= kMaxBatch, "one table thread per context");
-
-// Start of a call: every context's loop state from its parameters, counts cleared.
-__global__ __launch_bounds__(kWG) void batch_loop_init_kernel(const LoopCtx* __restrict__ lc,
-                                                              const LoopParams* prm, int n, LoopCounts* cnt) {
-    const int k = blockIdx.x * kWG + threadIdx.x;
-    if (k == 0) *cnt = LoopCounts{};
-    if (k >= n) return;
-    const uint64_t* w = reinterpret_cast<const uint64_t*>(prm + k);
-    DevLoop z{};
-    z.t_stop = __builtin_bit_cast(double, host_word(w));
-    z.eta = __builtin_bit_cast(double, host_word(w + 1));
-    z.dt_tree = __builtin_bit_cast(double, host_word(w + 2));
-    z.max_steps = static_cast<int64_t>(host_word(w + 3));
-    z.halt = z.max_steps < 1;   // a context that sits out this call: no kernel touches its state
-    *lc[k].loop = z;
-    *lc[k].dout = DevOut{};
-}
-
-// Exclusive prefix sum over the kLoopTabWG threads of the work-group.
-__device__ inline int64_t tab_scan(int64_t v, int64_t* s_wave, int64_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t x = wave_ops::scan_inclusive(v);
-    __syncthreads();
-    if (lane == 63) s_wave[wave] = x;
-    __syncthreads();
-    int64_t before = 0, all = 0;
-    for (int w = 0; w < kLoopTabWG / 64; ++w) {
-        if (w < wave) before += s_wave[w];
-        all += s_wave[w];
-    }
-    *total = all;
-    return before + x - v;
-}
-
-// After the planners: each context's first item, first split tile and first
-// corrector row in the engine step's launches, and the step's totals; the
-// time of the step (wall clock) when some context takes one.
-__global__ __launch_bounds__(kLoopTabWG) void batch_loop_table_kernel(Entry* tab, CorrEntry* ctab,
-                                                                      const LoopCtx* __restrict__ lc, int n,
-                                                                      LoopCounts* cnt, int64_t* ts, int64_t ts_max) {
-    __shared__ int64_t s_wave[kLoopTabWG / 64];
-    const int k = threadIdx.x;
-    const bool on = k < n;
-    int64_t ti, tr, tc;
-    const int64_t ei = tab_scan(on ? tab[k].n_items : 0, s_wave, &ti);
-    const int64_t er = tab_scan(on ? tab[k].n_rtiles : 0, s_wave, &tr);
-    const int64_t ec = tab_scan(on ? lc[k].loop->n_corr : 0, s_wave, &tc);
-    if (on) {
-        tab[k].first_item = ei;
-        tab[k].first_rtile = er;
-        ctab[k].first_row = ec;
-    }
-    if (k == 0) {
-        cnt->items = ti;
-        cnt->rtiles = tr;
-        cnt->rows = tc;
-        if (tc > 0) {
-            const int64_t st = cnt->step;
-            if (st < ts_max) ts[st] = static_cast<int64_t>(wall_clock64());
-            cnt->step = st + 1;
+// Every context's first item in this step's launch, the totals, the contexts
+// that run the next step, and the time of the step (wall clock) when some
+// context takes one.
+__device__ inline void place_items(int n_tab, Entry* launch, const LoopSum* sums, LoopCounts* cnt, int64_t* ts,
+                                   int64_t ts_max, PlanLds& S) {
+    const int k0 = 2 * threadIdx.x;
+    int64_t items[2] = {0, 0}, v[3] = {0, 0, 0}, tot[3];
+    for (int u = 0; u < 2; ++u)
+        if (k0 + u < n_tab) {
+            items[u] = agent_load(&sums[k0 + u].items);
+            v[0] += items[u];
+            v[1] += agent_load(&sums[k0 + u].rows);
+            v[2] += agent_load(&sums[k0 + u].running);
         }
+    plan_scan(v, tot, S);
+    if (k0 < n_tab) launch[k0].first_item = v[0];
+    if (k0 + 1 < n_tab) launch[k0 + 1].first_item = v[0] + items[0];
+    if (threadIdx.x != 0) return;
+    LoopCounts z = *cnt;
+    z.items = tot[0];
+    z.rows = tot[1];
+    z.expect = tot[2];
+    z.ticket = 0;
+    if (tot[1] > 0) {
+        if (z.step < ts_max) ts[z.step] = static_cast<int64_t>(wall_clock64());
+        z.step += 1;
     }
+    *cnt = z;
+}
+
+// Step 2 and the work plan (see above).
+__global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* __restrict__ tab,
+                                                              const uint16_t* __restrict__ block_ctx, int n_tab,
+                                                              Entry* launch, LoopSum* sums, LoopCounts* cnt,
+                                                              int64_t* ts, int64_t ts_max) {
+    __shared__ PlanLds S;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int k = n_tab > 1 ? block_ctx[blockIdx.x] : 0;
+    const LoopEntry& e = tab[k];
+    const int b = blockIdx.x - e.first_block;
+    const int64_t lo = static_cast<int64_t>(b) * e.chunk, hi = lo + e.chunk < e.n ? lo + e.chunk : e.n;
+    // the earliest block time, the blocks that hold it, and whether this one does
+    if (e.loop->halt) return;
+    const double m0 = 2 * t < e.nb ? e.s.bmin[2 * t] : HUGE_VAL, m1 = 2 * t + 1 < e.nb ? e.s.bmin[2 * t + 1] : HUGE_VAL;
+    const double own = e.s.bmin[b];
+    const double t_next = plan_min(fmin(m0, m1), S);
+    if (own != t_next) return;
+    const bool due0 = 2 * t < e.nb && m0 == t_next, due1 = 2 * t + 1 < e.nb && m1 == t_next;
+    int32_t n_due = 0;
+    {
+        const int32_t c = __popcll(__ballot(due0)) + __popcll(__ballot(due1));
+        if (lane == 0) S.g[wave] = c;
+    }
+    // its due particles, in order, into its slots; the earliest time of the others
+    int32_t cnt_b = 0;
+    double rest = HUGE_VAL;
+    for (int64_t base = lo; base < hi; base += kPlanWG) {
+        const int64_t i = base + t;
+        bool due = false;
+        int32_t g = 0;
+        if (i < hi) {
+            const double tn = e.s.t0[i] + e.s.dt[i];
+            g = e.pgroup[i];
+            due = tn == t_next;
+            if (!due) rest = fmin(rest, tn);
+        }
+        const uint64_t mask = __ballot(due);
+        if (lane == 0) S.qg[wave] = __popcll(mask);
+        __syncthreads();
+        int32_t at = cnt_b + __popcll(mask & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kPlanWaves; ++w) {
+            if (w < wave) at += S.qg[w];
+            cnt_b += S.qg[w];
+        }
+        if (due) agent_store(e.due + lo + at, static_cast<uint64_t>(static_cast<uint32_t>(g)) << 32 | static_cast<uint32_t>(i));
+        __syncthreads();
+    }
+    for (int w = 0; w < kPlanWaves; ++w) n_due += S.g[w];
+    rest = plan_min(rest, S);
+    if (t == 0) {
+        e.brest[b] = rest;
+        agent_store(e.s.bcount + b, cnt_b);
+    }
+    stores_done();
+    __syncthreads();
+    if (t == 0) {
+        const int32_t ticket = __hip_atomic_fetch_add(&e.loop->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        S.last = ticket == n_due - 1;
+        if (S.last) agent_store(&e.loop->ticket, 0);
+    }
+    __syncthreads();
+    if (!S.last) return;
+    // the context's last due block: plan its step
+    asm volatile("" ::: "memory");
+    LoopSum sum;
+    plan_step(e, S, t_next, due0, due1, launch + k, &sum);
+    if (n_tab == 1) {
+        if (t == 0) {
+            launch->first_item = 0;
+            cnt->items = sum.items;
+        }
+        return;
+    }
+    if (t == 0) {
+        agent_store(&sums[k].items, sum.items);
+        agent_store(&sums[k].rows, sum.rows);
+        agent_store(&sums[k].running, sum.running);
+        stores_done();
+        const int64_t expect = agent_load(&cnt->expect);
+        S.last = expect == 1 ||
+                 __hip_atomic_fetch_add(&cnt->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == expect - 1;
+    }
+    __syncthreads();
+    if (!S.last) return;
+    // the last context of the step: place the items
+    asm volatile("" ::: "memory");
+    place_items(n_tab, launch, sums, cnt, ts, ts_max, S);
+}
+
+// Step 6 by scheduler blocks (see above).
+template <class P>
+__global__ __launch_bounds__(kWG) void loop_correct_kernel(const LoopEntry* __restrict__ tab,
+                                                           const uint16_t* __restrict__ block_ctx, int n_tab) {
+    __shared__ double red[4];
+    const int k = n_tab > 1 ? block_ctx[blockIdx.x] : 0;
+    const LoopEntry& e = tab[k];
+    const int b = blockIdx.x - e.first_block;
+    const DevLoop& L = *e.loop;
+    const double t1 = L.t_cur, eta = L.eta, dt_tree = L.dt_tree, own = e.s.bmin[b];
+    if (L.n_corr == 0 || own != t1) return;
+    const int32_t cnt = e.s.bcount[b], q0 = e.boff[b];
+    const uint64_t* due = e.due + static_cast<int64_t>(b) * e.chunk;
+    double first = e.brest[b];
+    for (int32_t j = threadIdx.x; j < cnt; j += kWG) {
+        const int32_t q = q0 + j;
+        const QSum sp = e.qsum[q];
+        const int32_t i = static_cast<int32_t>(due[j]);
+        double F[kOut];
+        if (sp.first < 0) {
+            for (int u = 0; u < 3; ++u) {
+                F[u] = e.s.acc[3 * q + u];
+                F[3 + u] = e.s.jerk[3 * q + u];
+            }
+            F[6] = e.s.fpot[q];
+        } else {   // the split partials of q, summed in split order
+            sum_splits(e.d.partial + sp.first * kOut, static_cast<int64_t>(sp.stride) * kOut, sp.nsplit, F);
+        }
+        const double h = correct_particle<P>(e.s, e.rec, i, t1, eta, dt_tree, F);
+        if (h == 0.0) e.dout->below_floor = 1;
+        first = fmin(first, t1 + h);
+    }
+    first = block_min(first, red);
+    if (threadIdx.x == 0) e.s.bmin[b] = first;
 }
 
 // End of a call: every context's counts and state, and the step times, into pinned memory.
-__global__ __launch_bounds__(kWG) void batch_loop_results_kernel(const LoopCtx* __restrict__ lc, int n,
-                                                                 LoopResult* out, const LoopCounts* cnt,
-                                                                 const int64_t* ts, int64_t ts_max, int64_t* ts_out) {
+__global__ __launch_bounds__(kWG) void loop_results_kernel(const LoopEntry* __restrict__ tab, int n, LoopResult* out,
+                                                           const LoopCounts* cnt, const int64_t* ts, int64_t ts_max,
+                                                           int64_t* ts_out) {
     const int k = blockIdx.x * kWG + threadIdx.x;
     if (k < n) {
-        const DevLoop& L = *lc[k].loop;
-        out[k] = LoopResult{L.steps, L.psteps, L.pairs, L.t_cur, L.err, lc[k].dout->below_floor};
+        const DevLoop& L = *tab[k].loop;
+        out[k] = LoopResult{L.steps, L.psteps, L.pairs, L.t_cur, L.err, tab[k].dout->below_floor};
     }
+    if (!ts_out) return;
     const int64_t m = cnt->step < ts_max ? cnt->step : ts_max;
     for (int64_t q = k; q < m; q += static_cast<int64_t>(gridDim.x) * kWG) ts_out[1 + q] = ts[q];
     if (k == 0) {
@@ -1711,6 +1898,18 @@ struct Timing {
     int64_t pairs = 0;
 };
 
+// The device side of a device loop over some contexts: its table in device
+// memory with the host's copy (uploaded again when it changes) and the graph
+// of kLoopGraphSteps steps (captured again when the launches change).
+struct LoopRun {
+    std::vector<LoopEntry> tab;
+    std::vector<uint16_t> block_ctx;
+    int32_t blocks = 0, force_grid = 0, precision = -1;   // the launches that the graph holds
+    size_t n_tab = 0;
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+};
+
 // A ring of pinned host slots, each mirroring a device region byte for byte,
 // so the host can pack several calls ahead of the device.  A slot is reused
 // once the copy that read it has completed.
@@ -1783,18 +1982,21 @@ struct ht_ctx {
     DevState ds{};
     char* ds_mem = nullptr;
     bool own_ds = false;   // ds_mem allocated by the library (ht_state_enable), not the caller's
-    // device loop (ht_dev_run): its state, the scheduler's results in device
-    // memory, the group and list offsets and the planner's scratch
+    // device loops: this context's loop state and table entry, the group and
+    // list offsets, and the planner's scratch
     DevLoop* d_loop = nullptr;
     DevOut* d_dout = nullptr;
     int64_t* d_gfirst = nullptr;
     int64_t* d_loff = nullptr;
-    int32_t *d_gk = nullptr, *d_qk = nullptr, *d_qg = nullptr, *d_pgroup = nullptr;
+    int32_t *d_qk = nullptr, *d_qg = nullptr, *d_pgroup = nullptr, *d_boff = nullptr;
+    QSum* d_qsum = nullptr;
+    uint64_t* d_due = nullptr;
+    double* d_brest = nullptr;
     DTile* d_tiles = nullptr;
-    hipGraph_t loop_graph = nullptr;      // kLoopGraphSteps device-loop steps, captured once
-    hipGraphExec_t loop_exec = nullptr;
-    double loop_tuning[2] = {-1.0, -1.0}; // the tuning the graph's planner launches carry
-    int32_t loop_self_once = -1;          // and the descriptor's self_once
+    // ht_dev_run: its table (one entry), counts and graph
+    LoopRun loop;
+    LoopParams* h_lparams = nullptr;   // pinned
+    LoopResult* h_lres = nullptr;      // pinned
     // every list holds each particle of its group exactly once (checked when
     // host lists are set; true for the device builder's lists by construction)
     bool self_once_lists = false;
@@ -1899,16 +2101,10 @@ struct ht_batch {
     std::vector<UpdEntry> utab;
     int32_t* h_err = nullptr;   // set by the row scatter when it dropped a row for its index
     // batched device loop (ht_batch_dev_run): its tables sit in the workspace
-    // after the plan region; the graph of kLoopGraphSteps engine steps is
-    // captured for one set of contexts (and their sizes and tunings) and kept
-    // until the set changes
+    // after the plan region
     char* loop_ws = nullptr;
-    std::vector<ht_ctx*> loop_ctxs;
-    std::vector<double> loop_key;
-    int32_t loop_blocks = 0;
+    LoopRun loop;
     hipStream_t cap_stream = nullptr;
-    hipGraph_t loop_graph = nullptr;
-    hipGraphExec_t loop_exec = nullptr;
     LoopParams* h_lparams = nullptr;   // pinned: per-call parameters
     LoopResult* h_lres = nullptr;      // pinned: per-call results
     int64_t* h_ts = nullptr;           // pinned: engine-step times of the last call
@@ -2297,6 +2493,13 @@ int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab,
     return HT_OK;
 }
 
+void loop_free(LoopRun& r) {
+    if (r.exec) (void)hipGraphExecDestroy(r.exec);
+    if (r.graph) (void)hipGraphDestroy(r.graph);
+    r.exec = nullptr;
+    r.graph = nullptr;
+}
+
 // A kernel dropped an update row whose particle index (read from device or
 // pinned memory) was outside [0, N): report it once, at the first
 // synchronisation that follows.
@@ -2575,8 +2778,9 @@ int ht_destroy(ht_ctx* c) {
         if (c->graph[k]) (void)hipGraphDestroy(c->graph[k]);
         if (c->hdr_free[k]) (void)hipEventDestroy(c->hdr_free[k]);
     }
-    if (c->loop_exec) (void)hipGraphExecDestroy(c->loop_exec);
-    if (c->loop_graph) (void)hipGraphDestroy(c->loop_graph);
+    loop_free(c->loop);
+    if (c->h_lparams) (void)hipHostFree(c->h_lparams);
+    if (c->h_lres) (void)hipHostFree(c->h_lres);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->h_hdr) (void)hipHostFree(c->h_hdr);
     if (c->ds_mem && c->own_ds) (void)hipFree(c->ds_mem);
@@ -2941,22 +3145,21 @@ SchedEntry sched_entry_of(const ht_ctx* c, int32_t first_block) {
     const int64_t n = c->n;
     const int nb = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(kSchedBlocks, (n + 2047) / 2048)));
     return SchedEntry{c->ds.t0, c->ds.dt, c->ds.active, c->ds.bmin, c->ds.bcount, n, (n + nb - 1) / nb, nb,
-                      first_block, c->h_dout, c->h_active, nullptr};
+                      first_block, c->h_dout, c->h_active};
 }
 
 // The corrector's table entry of a context's last active set, rows from first_row.
 CorrEntry corr_entry_of(const ht_ctx* c, int64_t first_row, double eta, double dt_tree) {
-    return CorrEntry{c->ds, c->ws + c->L.off_rec, c->h_dout, c->dev_n_active, first_row, c->dev_t_next, eta, dt_tree,
-                     nullptr, nullptr, nullptr, nullptr};
+    return CorrEntry{c->ds, c->ws + c->L.off_rec, c->h_dout, c->dev_n_active, first_row, c->dev_t_next, eta, dt_tree};
 }
 
 int launch_correct(int precision, hipStream_t stream, const CorrEntry& e0, const CorrEntry* tab, int n_tab,
                    int64_t total) {
     const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>((total + kWG - 1) / kWG, 65536)));
     if (precision == HT_PREC_FP64)
-        dev_correct_kernel<PrecFp64><<<grid, kWG, 0, stream>>>(e0, tab, n_tab, total, nullptr);
+        dev_correct_kernel<PrecFp64><<<grid, kWG, 0, stream>>>(e0, tab, n_tab, total);
     else
-        dev_correct_kernel<PrecMixed><<<grid, kWG, 0, stream>>>(e0, tab, n_tab, total, nullptr);
+        dev_correct_kernel<PrecMixed><<<grid, kWG, 0, stream>>>(e0, tab, n_tab, total);
     HT_HIP(hipGetLastError());
     return HT_OK;
 }
@@ -3101,7 +3304,7 @@ namespace {
 // Where the resident state's arrays sit in its one device allocation.
 struct StateLayout {
     size_t x, v, a, j, t0, dt, m, pot, acc, jerk, fpot, act, bmin, bcnt;
-    size_t loop, dout, gf, lo, gk, qk, qg, tiles, pgroup;
+    size_t loop, dout, gf, lo, qsum, qk, qg, tiles, pgroup, boff, brest, due, ltab, lsum, lcnt;
     size_t total;
 };
 
@@ -3133,11 +3336,17 @@ StateLayout state_layout(const ht_config& cfg) {
     S.dout = take(sizeof(DevOut));
     S.gf = take(g1 * 8);
     S.lo = take(g1 * 8);
-    S.gk = take(n * 4);
+    S.qsum = take(n * sizeof(QSum));
     S.qk = take((n + 1) * 4);
     S.qg = take(n * 4);
     S.tiles = take(n * sizeof(DTile));
     S.pgroup = take(n * 4);
+    S.boff = take(kSchedBlocks * 4);
+    S.brest = take(kSchedBlocks * 8);
+    S.due = take(n * 8);
+    S.ltab = take(sizeof(LoopEntry));
+    S.lsum = take(sizeof(LoopSum));
+    S.lcnt = take(sizeof(LoopCounts));
     S.total = o;
     return S;
 }
@@ -3160,18 +3369,23 @@ int state_attach(ht_ctx* c, char* mem, bool own) {
     c->d_dout = reinterpret_cast<DevOut*>(b + S.dout);
     c->d_gfirst = reinterpret_cast<int64_t*>(b + S.gf);
     c->d_loff = reinterpret_cast<int64_t*>(b + S.lo);
-    c->d_gk = reinterpret_cast<int32_t*>(b + S.gk);
+    c->d_qsum = reinterpret_cast<QSum*>(b + S.qsum);
     c->d_qk = reinterpret_cast<int32_t*>(b + S.qk);
     c->d_qg = reinterpret_cast<int32_t*>(b + S.qg);
     c->d_tiles = reinterpret_cast<DTile*>(b + S.tiles);
     c->d_pgroup = reinterpret_cast<int32_t*>(b + S.pgroup);
+    c->d_boff = reinterpret_cast<int32_t*>(b + S.boff);
+    c->d_brest = reinterpret_cast<double*>(b + S.brest);
+    c->d_due = reinterpret_cast<uint64_t*>(b + S.due);
     if (c->have_lists) {   // lists set before the state: their offsets for the device planner
         int rc = upload_group_offsets(c);
         if (rc) return rc;
     }
     const size_t n = static_cast<size_t>(c->cfg.n_max);
     if (hipHostMalloc(reinterpret_cast<void**>(&c->h_dout), sizeof(DevOut), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&c->h_active), n * 4, hipHostMallocDefault) != hipSuccess)
+        hipHostMalloc(reinterpret_cast<void**>(&c->h_active), n * 4, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&c->h_lparams), sizeof(LoopParams), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&c->h_lres), sizeof(LoopResult), hipHostMallocDefault) != hipSuccess)
         return fail(HT_ENOMEM, "hipHostMalloc for the scheduler results failed");
     std::memset(c->h_dout, 0, sizeof(DevOut));
     return HT_OK;
@@ -3369,6 +3583,8 @@ int ht_dev_step(ht_ctx* c, double eta, double dt_tree) { return dev_step(c, eta,
 
 int ht_dev_step_direct(ht_ctx* c, double eta, double dt_tree) { return dev_step(c, eta, dt_tree, true); }
 
+}  // extern "C"
+
 constexpr int kLoopGraphSteps = 32;  // device-loop steps per captured graph
 // Fixed force grid of the device loops (their launch arguments are captured
 // in graphs, so the grid cannot follow the item count): eight work-groups per
@@ -3378,110 +3594,124 @@ constexpr int kLoopGraphSteps = 32;  // device-loop steps per captured graph
 // exit at once.  (A grid of one work-group per slot assigns items statically and
 // was measured about 20% slower on all-particle steps.)
 constexpr int kLoopForceGrid = 8192;
-constexpr int kLoopCorrGrid = 256;    // fixed corrector grid of the device loop (grid-stride)
+constexpr int kLoopBlock = 512;       // least particles of a device loop's scheduler block
 
 namespace {
-// The device planner's arguments for a context: its loop state, scheduler
-// results, planner scratch and plan region; the launch-table entry it writes
-// is `tab` (its own plan region's, or a slot of a batched loop's table).
-PlanArgs plan_args_of(const ht_ctx* c, Entry* tab) {
-    PlanArgs pa{};
-    pa.loop = c->d_loop;
-    pa.dout = c->d_dout;
-    pa.qmap = c->d_gk;
-    pa.active = c->ds.active;
-    pa.pgroup = c->d_pgroup;
-    pa.loff = c->d_loff;
-    pa.qk = c->d_qk;
-    pa.qg = c->d_qg;
-    pa.tiles = c->d_tiles;
-    char* plan = c->ws + c->L.off_plan;
-    pa.tab = tab;
-    pa.items = reinterpret_cast<Item*>(plan + align_up(kMaxBatch * sizeof(Entry)));
-    pa.rtiles = reinterpret_cast<RTile*>(plan + align_up(kMaxBatch * sizeof(Entry)) +
-                                         align_up(static_cast<size_t>(c->L.items_max) * sizeof(Item)));
-    pa.items_max = c->L.items_max;
-    pa.partial_max = c->L.partial_max;
-    pa.gather_cost = c->gather_cost;
-    pa.target_items = c->target_items;
-    pa.d = c->desc();
-    pa.d.active = c->ds.active;
-    pa.d.acc = c->ds.acc;
-    pa.d.jerk = c->ds.jerk;
-    pa.d.pot = c->ds.fpot;
-    std::memcpy(pa.first_tile, c->first_tile, sizeof(pa.first_tile));
-    return pa;
+// A context's entry in a device loop's table, its scheduler blocks from first_block on.
+LoopEntry loop_entry_of(const ht_ctx* c, int32_t first_block) {
+    LoopEntry e;
+    std::memset(static_cast<void*>(&e), 0, sizeof e);   // entries are compared byte by byte
+    e.s = c->ds;
+    e.rec = c->ws + c->L.off_rec;
+    e.loop = c->d_loop;
+    e.dout = c->d_dout;
+    e.brest = c->d_brest;
+    e.boff = c->d_boff;
+    e.due = c->d_due;
+    e.n = c->n;
+    e.nb = static_cast<int32_t>(std::max<int64_t>(1, std::min<int64_t>(kSchedBlocks, (e.n + kLoopBlock - 1) / kLoopBlock)));
+    e.chunk = static_cast<int32_t>((e.n + e.nb - 1) / e.nb);
+    e.nb = std::max<int32_t>(1, static_cast<int32_t>((e.n + e.chunk - 1) / std::max(e.chunk, 1)));   // none of them empty
+    e.first_block = first_block;
+    e.pgroup = c->d_pgroup;
+    e.loff = c->d_loff;
+    e.qsum = c->d_qsum;
+    e.qk = c->d_qk;
+    e.qg = c->d_qg;
+    e.tiles = c->d_tiles;
+    e.items = reinterpret_cast<Item*>(c->ws + c->L.off_plan + align_up(kMaxBatch * sizeof(Entry)));
+    e.items_max = c->L.items_max;
+    e.partial_max = c->L.partial_max;
+    e.gather_cost = c->gather_cost;
+    e.target_items = c->target_items;
+    const Desc d = c->desc();
+    std::memcpy(&e.d, &d, sizeof d);
+    e.d.t = 0.0;   // set by the planner
+    e.d.active = c->ds.active;
+    e.d.acc = c->ds.acc;
+    e.d.jerk = c->ds.jerk;
+    e.d.pot = c->ds.fpot;
+    std::memcpy(e.first_tile, c->first_tile, sizeof(e.first_tile));
+    return e;
 }
 
-// The device loop's scheduler and corrector entries of a context.
-SchedEntry loop_sched_entry(const ht_ctx* c, int32_t first_block) {
-    SchedEntry se = sched_entry_of(c, first_block);
-    se.out = c->d_dout;
-    se.active_host = nullptr;
-    se.halt = &c->d_loop->halt;
-    return se;
+// Device arrays of a loop call.
+struct LoopMem {
+    LoopEntry* tab;
+    uint16_t* block_ctx;
+    Entry* launch;
+    LoopSum* sums;
+    LoopCounts* cnt;
+    int64_t* ts;
+    int64_t ts_max;
+};
+
+template <class P>
+void queue_loop_step(const LoopRun& r, const LoopMem& m, hipStream_t s) {
+    const int n_tab = static_cast<int>(r.n_tab);
+    loop_select_kernel<<<r.blocks, kPlanWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.launch, m.sums, m.cnt, m.ts, m.ts_max);
+    force_kernel<P, false, false><<<r.force_grid, kWG, 0, s>>>(m.launch, n_tab, -1, &m.cnt->items);
+    loop_correct_kernel<P><<<r.blocks, kWG, 0, s>>>(m.tab, m.block_ctx, n_tab);
 }
 
-CorrEntry loop_corr_entry(const ht_ctx* c, const PlanArgs& pa) {
-    CorrEntry ce = corr_entry_of(c, 0, 1.0, 1.0);   // eta and dt_tree come from the loop state
-    ce.out = c->d_dout;
-    ce.loop = c->d_loop;
-    ce.qmap = pa.qmap;
-    ce.rtiles = pa.rtiles;
-    ce.partial = pa.d.partial;
-    return ce;
-}
-
-// Capture kLoopGraphSteps device-loop steps into one graph.  Every launch
-// argument is fixed for the context's life (the call's parameters sit in the
-// loop state in device memory), except the work-plan tuning, on whose change
-// the graph is captured again.
-int build_loop_graph(ht_ctx* c) {
-    if (c->loop_exec) {
-        (void)hipGraphExecDestroy(c->loop_exec);
-        c->loop_exec = nullptr;
+// The loop's table and graph for these contexts, unless those of the last call serve.
+int prepare_loop(LoopRun& r, const LoopMem& m, int32_t n_ctx, ht_ctx* const* ctxs, hipStream_t stream,
+                 hipStream_t& cap) {
+    std::vector<LoopEntry> tab(n_ctx);
+    int64_t blocks = 0, items = 0;
+    for (int32_t k = 0; k < n_ctx; ++k) {
+        const LoopEntry e = loop_entry_of(ctxs[k], static_cast<int32_t>(blocks));
+        std::memcpy(static_cast<void*>(&tab[k]), &e, sizeof e);
+        blocks += e.nb;
+        // items of a large step: the split target, a tile per group and full tiles (by the
+        // context's capacity, so that rebuilds keep the graph)
+        items += static_cast<int64_t>(e.target_items) + ctxs[k]->cfg.group_max + e.n / 256;
     }
-    if (c->loop_graph) {
-        (void)hipGraphDestroy(c->loop_graph);
-        c->loop_graph = nullptr;
+    if (r.tab.size() != tab.size() || std::memcmp(r.tab.data(), tab.data(), tab.size() * sizeof(LoopEntry)) != 0) {
+        std::vector<uint16_t> map(static_cast<size_t>(blocks));
+        for (int32_t k = 0; k < n_ctx; ++k)
+            std::fill_n(map.begin() + tab[k].first_block, tab[k].nb, static_cast<uint16_t>(k));
+        r.tab.clear();   // not in force until the upload is done
+        HT_HIP(hipMemcpyAsync(m.tab, tab.data(), tab.size() * sizeof(LoopEntry), hipMemcpyHostToDevice, stream));
+        if (n_ctx > 1) HT_HIP(hipMemcpyAsync(m.block_ctx, map.data(), map.size() * 2, hipMemcpyHostToDevice, stream));
+        HT_HIP(hipStreamSynchronize(stream));   // pageable sources
+        r.tab = std::move(tab);
+        r.block_ctx = std::move(map);
     }
-    if (!c->cap_stream) HT_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-    const SchedEntry se = loop_sched_entry(c, 0);
-    const PlanArgs pa = plan_args_of(c, reinterpret_cast<Entry*>(c->ws + c->L.off_plan));
-    const CorrEntry ce = loop_corr_entry(c, pa);
-    const Entry* d_tab = pa.tab;
-    hipStream_t s = c->cap_stream;
-    HT_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+    const int32_t grid = static_cast<int32_t>(std::min<int64_t>(kLoopForceGrid, std::max<int64_t>(1024, (items + 255) / 256 * 256)));
+    const int32_t precision = ctxs[0]->cfg.precision;
+    if (r.exec && r.blocks == blocks && r.force_grid == grid && r.precision == precision && r.n_tab == r.tab.size()) return HT_OK;
+    loop_free(r);
+    r.blocks = static_cast<int32_t>(blocks);
+    r.force_grid = grid;
+    r.precision = precision;
+    r.n_tab = r.tab.size();
+    if (!cap) HT_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+    HT_HIP(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < kLoopGraphSteps; ++k) {
-        sched_min_kernel<<<se.nb, kWG, 0, s>>>(se, nullptr, 0);
-        sched_count_kernel<<<se.nb, kWG, 0, s>>>(se, nullptr, 0);
-        sched_write_kernel<<<se.nb, kWG, 0, s>>>(se, nullptr, 0);
-        dev_plan_kernel<<<1, kPlanWG, 0, s>>>(pa);   // takes the step (or stops the loop) and plans it
-        if (c->cfg.precision == HT_PREC_FP64) {
-            force_kernel<PrecFp64, false, false><<<kLoopForceGrid, kWG, 0, s>>>(d_tab, 1, -1, &d_tab->n_items);
-            dev_correct_kernel<PrecFp64><<<kLoopCorrGrid, kWG, 0, s>>>(ce, nullptr, 0, -1, nullptr);   // sums the splits too
-        } else {
-            force_kernel<PrecMixed, false, false><<<kLoopForceGrid, kWG, 0, s>>>(d_tab, 1, -1, &d_tab->n_items);
-            dev_correct_kernel<PrecMixed><<<kLoopCorrGrid, kWG, 0, s>>>(ce, nullptr, 0, -1, nullptr);
-        }
+        if (precision == HT_PREC_FP64) queue_loop_step<PrecFp64>(r, m, cap);
+        else queue_loop_step<PrecMixed>(r, m, cap);
     }
     const hipError_t launch = hipGetLastError();
-    hipGraph_t g = nullptr;
-    const hipError_t end = hipStreamEndCapture(s, &g);
+    const hipError_t end = hipStreamEndCapture(cap, &r.graph);
     if (launch != hipSuccess || end != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
+        loop_free(r);
         return fail(HT_EHIP, "capturing the device-loop graph failed: %s",
                     hipGetErrorString(launch != hipSuccess ? launch : end));
     }
-    c->loop_graph = g;
-    HT_HIP(hipGraphInstantiate(&c->loop_exec, g, nullptr, nullptr, 0));
-    c->loop_tuning[0] = c->gather_cost;
-    c->loop_tuning[1] = c->target_items;
-    c->loop_self_once = c->desc().self_once;
+    HT_HIP(hipGraphInstantiate(&r.exec, r.graph, nullptr, nullptr, 0));
     return HT_OK;
+}
+
+LoopMem loop_mem(const ht_ctx* c) {
+    const StateLayout S = state_layout(c->cfg);
+    return LoopMem{reinterpret_cast<LoopEntry*>(c->ds_mem + S.ltab), nullptr,
+                   reinterpret_cast<Entry*>(c->ws + c->L.off_plan), reinterpret_cast<LoopSum*>(c->ds_mem + S.lsum),
+                   reinterpret_cast<LoopCounts*>(c->ds_mem + S.lcnt), nullptr, 0};
 }
 }  // namespace
 
+extern "C" {
 
 int ht_dev_run(ht_ctx* c, double eta, double dt_tree, double t_stop, int32_t max_steps, int32_t* steps,
                double* t_last, int64_t* particle_steps) {
@@ -3498,20 +3728,18 @@ int ht_dev_run(ht_ctx* c, double eta, double dt_tree, double t_stop, int32_t max
     *t_last = c->dev_t_next;
     *particle_steps = 0;
     c->dev_n_active = -1;
-    if (!c->loop_exec || c->loop_tuning[0] != c->gather_cost || c->loop_tuning[1] != c->target_items ||
-        c->loop_self_once != c->desc().self_once) {
-        int rc = build_loop_graph(c);
-        if (rc) return rc;
-    }
+    const LoopMem m = loop_mem(c);
+    if (int rc = prepare_loop(c->loop, m, 1, &c, c->stream, c->cap_stream)) return rc;
     c->slots_all_free();
-    loop_init_kernel<<<1, 64, 0, c->stream>>>(c->d_loop, c->d_dout, t_stop, max_steps, eta, dt_tree);
+    *c->h_lparams = LoopParams{t_stop, eta, dt_tree, max_steps};
+    loop_init_kernel<<<1, kWG, 0, c->stream>>>(m.tab, 1, c->h_lparams, m.sums, m.cnt);
+    loop_min_kernel<<<c->loop.blocks, kWG, 0, c->stream>>>(m.tab, m.block_ctx, 1);
     HT_HIP(hipGetLastError());
-    for (int32_t k = 0; k < max_steps; k += kLoopGraphSteps) HT_HIP(hipGraphLaunch(c->loop_exec, c->stream));
-    DevLoop L{};
-    DevOut o{};
-    HT_HIP(hipMemcpyAsync(&L, c->d_loop, sizeof L, hipMemcpyDeviceToHost, c->stream));
-    HT_HIP(hipMemcpyAsync(&o, c->d_dout, sizeof o, hipMemcpyDeviceToHost, c->stream));
+    for (int32_t k = 0; k < max_steps; k += kLoopGraphSteps) HT_HIP(hipGraphLaunch(c->loop.exec, c->stream));
+    loop_results_kernel<<<1, kWG, 0, c->stream>>>(m.tab, 1, c->h_lres, m.cnt, nullptr, 0, nullptr);
+    HT_HIP(hipGetLastError());
     HT_HIP(hipStreamSynchronize(c->stream));
+    const LoopResult& L = *c->h_lres;
     *steps = static_cast<int32_t>(L.steps);
     *particle_steps = L.psteps;
     if (L.steps > 0) {
@@ -3520,7 +3748,7 @@ int ht_dev_run(ht_ctx* c, double eta, double dt_tree, double t_stop, int32_t max
     }
     c->last_pairs = L.pairs;
     c->predicted = false;
-    if (o.below_floor) return fail(HT_ERANGE, "a corrected block step fell below 2^-40");
+    if (L.below_floor) return fail(HT_ERANGE, "a corrected block step fell below 2^-40");
     if (L.err) return fail(HT_ERANGE, "a device work plan exceeded the context's capacity");
     return HT_OK;
 }
@@ -3650,7 +3878,7 @@ constexpr int kMaxLoopCallSteps = 4096;   // engine steps per ht_batch_dev_run c
 
 // The batched device loop's tables, one entry per context of the batch.
 struct LoopRegion {
-    size_t sched, plan, corr, tab, lctx, counts, ts, total;
+    size_t tab, blocks, launch, sums, counts, ts, total;
 };
 
 LoopRegion loop_region(int32_t max_clusters) {
@@ -3662,15 +3890,23 @@ LoopRegion loop_region(int32_t max_clusters) {
         return at;
     };
     const size_t m = static_cast<size_t>(max_clusters);
-    r.sched = take(m * sizeof(SchedEntry));
-    r.plan = take(m * sizeof(PlanArgs));
-    r.corr = take(m * sizeof(CorrEntry));
-    r.tab = take(m * sizeof(Entry));
-    r.lctx = take(m * sizeof(LoopCtx));
+    r.tab = take(m * sizeof(LoopEntry));
+    r.blocks = take(m * kSchedBlocks * sizeof(uint16_t));
+    r.launch = take(m * sizeof(Entry));
+    r.sums = take(m * sizeof(LoopSum));
     r.counts = take(sizeof(LoopCounts));
     r.ts = take(static_cast<size_t>(kMaxLoopCallSteps) * 8);
     r.total = o;
     return r;
+}
+
+LoopMem loop_mem(const ht_batch* b) {
+    const LoopRegion R = loop_region(b->max_clusters);
+    char* w = b->loop_ws;
+    return LoopMem{reinterpret_cast<LoopEntry*>(w + R.tab), reinterpret_cast<uint16_t*>(w + R.blocks),
+                   reinterpret_cast<Entry*>(w + R.launch), reinterpret_cast<LoopSum*>(w + R.sums),
+                   reinterpret_cast<LoopCounts*>(w + R.counts), reinterpret_cast<int64_t*>(w + R.ts),
+                   kMaxLoopCallSteps};
 }
 
 bool batch_args_ok(int32_t max_clusters, int64_t max_items, int64_t max_active, int64_t max_rows) {
@@ -3791,8 +4027,7 @@ int ht_batch_destroy(ht_batch* b) {
     ring_free(b->plan_ring);
     ring_free(b->rows_ring);
     if (b->h_err) (void)hipHostFree(b->h_err);
-    if (b->loop_exec) (void)hipGraphExecDestroy(b->loop_exec);
-    if (b->loop_graph) (void)hipGraphDestroy(b->loop_graph);
+    loop_free(b->loop);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     if (b->h_lparams) (void)hipHostFree(b->h_lparams);
     if (b->h_lres) (void)hipHostFree(b->h_lres);
@@ -4086,108 +4321,6 @@ int ht_batch_dev_step(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const dou
 
 }  // extern "C"
 
-namespace {
-
-// Capture kLoopGraphSteps engine steps of the batched device loop over the
-// n_ctx contexts whose tables sit in the batch's loop region.
-template <class P>
-int build_batch_loop_graph(ht_batch* b, int32_t n_ctx) {
-    if (b->loop_exec) {
-        (void)hipGraphExecDestroy(b->loop_exec);
-        b->loop_exec = nullptr;
-    }
-    if (b->loop_graph) {
-        (void)hipGraphDestroy(b->loop_graph);
-        b->loop_graph = nullptr;
-    }
-    if (!b->cap_stream) HT_HIP(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
-    const LoopRegion R = loop_region(b->max_clusters);
-    char* w = b->loop_ws;
-    const SchedEntry* d_sched = reinterpret_cast<const SchedEntry*>(w + R.sched);
-    const PlanArgs* d_plan = reinterpret_cast<const PlanArgs*>(w + R.plan);
-    CorrEntry* d_corr = reinterpret_cast<CorrEntry*>(w + R.corr);
-    Entry* d_tab = reinterpret_cast<Entry*>(w + R.tab);
-    const LoopCtx* d_lctx = reinterpret_cast<const LoopCtx*>(w + R.lctx);
-    LoopCounts* d_cnt = reinterpret_cast<LoopCounts*>(w + R.counts);
-    int64_t* d_ts = reinterpret_cast<int64_t*>(w + R.ts);
-    const SchedEntry none{};
-    const CorrEntry cnone{};
-    hipStream_t s = b->cap_stream;
-    HT_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < kLoopGraphSteps; ++k) {
-        sched_min_kernel<<<b->loop_blocks, kWG, 0, s>>>(none, d_sched, n_ctx);
-        sched_count_kernel<<<b->loop_blocks, kWG, 0, s>>>(none, d_sched, n_ctx);
-        sched_write_kernel<<<b->loop_blocks, kWG, 0, s>>>(none, d_sched, n_ctx);
-        dev_plan_batch_kernel<<<n_ctx, kPlanWG, 0, s>>>(d_plan);   // each context takes its step (or stops) and plans it
-        batch_loop_table_kernel<<<1, kLoopTabWG, 0, s>>>(d_tab, d_corr, d_lctx, n_ctx, d_cnt, d_ts, kMaxLoopCallSteps);
-        force_kernel<P, false, false><<<kLoopForceGrid, kWG, 0, s>>>(d_tab, n_ctx, -1, &d_cnt->items);
-        dev_correct_kernel<P><<<kLoopCorrGrid, kWG, 0, s>>>(cnone, d_corr, n_ctx, -1, &d_cnt->rows);
-    }
-    const hipError_t launch = hipGetLastError();
-    hipGraph_t g = nullptr;
-    const hipError_t end = hipStreamEndCapture(s, &g);
-    if (launch != hipSuccess || end != hipSuccess) {
-        if (g) (void)hipGraphDestroy(g);
-        return fail(HT_EHIP, "capturing the batched device-loop graph failed: %s",
-                    hipGetErrorString(launch != hipSuccess ? launch : end));
-    }
-    b->loop_graph = g;
-    HT_HIP(hipGraphInstantiate(&b->loop_exec, g, nullptr, nullptr, 0));
-    return HT_OK;
-}
-
-// The tables of the batched device loop for these contexts, and its graph,
-// unless the last call used the same contexts with the same sizes and tunings.
-int prepare_batch_loop(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs) {
-    std::vector<double> key;
-    key.reserve(static_cast<size_t>(n_ctx) * 3);
-    for (int32_t k = 0; k < n_ctx; ++k) {
-        key.push_back(static_cast<double>(ctxs[k]->n));
-        key.push_back(ctxs[k]->gather_cost);
-        key.push_back(ctxs[k]->target_items);
-        key.push_back(static_cast<double>(ctxs[k]->desc().self_once));
-    }
-    if (b->loop_exec && b->loop_ctxs.size() == static_cast<size_t>(n_ctx) &&
-        std::equal(b->loop_ctxs.begin(), b->loop_ctxs.end(), ctxs) && b->loop_key == key)
-        return HT_OK;
-    const LoopRegion R = loop_region(b->max_clusters);
-    char* w = b->loop_ws;
-    std::vector<SchedEntry> sched(n_ctx);
-    std::vector<PlanArgs> plan(n_ctx);
-    std::vector<CorrEntry> corr(n_ctx);
-    std::vector<LoopCtx> lctx(n_ctx);
-    std::vector<Entry> tab(n_ctx);
-    int32_t blocks = 0;
-    for (int32_t k = 0; k < n_ctx; ++k) {
-        const ht_ctx* c = ctxs[k];
-        sched[k] = loop_sched_entry(c, blocks);
-        blocks += sched[k].nb;
-        plan[k] = plan_args_of(c, reinterpret_cast<Entry*>(w + R.tab) + k);
-        corr[k] = loop_corr_entry(c, plan[k]);
-        lctx[k] = LoopCtx{c->d_loop, c->d_dout};
-        tab[k] = Entry{};
-    }
-    const size_t nk = static_cast<size_t>(n_ctx);
-    HT_HIP(hipMemcpyAsync(w + R.sched, sched.data(), nk * sizeof(SchedEntry), hipMemcpyHostToDevice, b->stream));
-    HT_HIP(hipMemcpyAsync(w + R.plan, plan.data(), nk * sizeof(PlanArgs), hipMemcpyHostToDevice, b->stream));
-    HT_HIP(hipMemcpyAsync(w + R.corr, corr.data(), nk * sizeof(CorrEntry), hipMemcpyHostToDevice, b->stream));
-    HT_HIP(hipMemcpyAsync(w + R.lctx, lctx.data(), nk * sizeof(LoopCtx), hipMemcpyHostToDevice, b->stream));
-    HT_HIP(hipMemcpyAsync(w + R.tab, tab.data(), nk * sizeof(Entry), hipMemcpyHostToDevice, b->stream));
-    HT_HIP(hipStreamSynchronize(b->stream));   // pageable sources
-    b->loop_blocks = blocks;
-    const int rc = ctxs[0]->cfg.precision == HT_PREC_FP64 ? build_batch_loop_graph<PrecFp64>(b, n_ctx)
-                                                           : build_batch_loop_graph<PrecMixed>(b, n_ctx);
-    if (rc) {
-        b->loop_ctxs.clear();
-        return rc;
-    }
-    b->loop_ctxs.assign(ctxs, ctxs + n_ctx);
-    b->loop_key = key;
-    return HT_OK;
-}
-
-}  // namespace
-
 extern "C" {
 
 int ht_batch_dev_run(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const double* eta, const double* dt_tree,
@@ -4215,13 +4348,14 @@ int ht_batch_dev_run(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const doub
         if (!(eta[k] > 0.0) || !(dt_tree[k] > 0.0) || !std::isfinite(t_stop[k]))
             return fail(HT_EINVAL, "ctx %d: bad eta, dt_tree or t_stop", k);
     }
-    int rc = prepare_batch_loop(b, n_ctx, ctxs);
+    const LoopMem m = loop_mem(b);
+    int rc = prepare_loop(b->loop, m, n_ctx, ctxs, b->stream, b->cap_stream);
     if (rc) return rc;
     if (!b->h_lparams) {
-        const size_t m = static_cast<size_t>(b->max_clusters);
-        if (hipHostMalloc(reinterpret_cast<void**>(&b->h_lparams), m * sizeof(LoopParams), hipHostMallocDefault) !=
+        const size_t most = static_cast<size_t>(b->max_clusters);
+        if (hipHostMalloc(reinterpret_cast<void**>(&b->h_lparams), most * sizeof(LoopParams), hipHostMallocDefault) !=
                 hipSuccess ||
-            hipHostMalloc(reinterpret_cast<void**>(&b->h_lres), m * sizeof(LoopResult), hipHostMallocDefault) !=
+            hipHostMalloc(reinterpret_cast<void**>(&b->h_lres), most * sizeof(LoopResult), hipHostMallocDefault) !=
                 hipSuccess ||
             hipHostMalloc(reinterpret_cast<void**>(&b->h_ts), (kMaxLoopCallSteps + 2) * sizeof(int64_t),
                           hipHostMallocDefault) != hipSuccess)
@@ -4233,17 +4367,12 @@ int ht_batch_dev_run(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const doub
         ctxs[k]->dev_n_active = -1;
         ctxs[k]->slots_all_free();
     }
-    const LoopRegion R = loop_region(b->max_clusters);
-    char* w = b->loop_ws;
-    const LoopCtx* d_lctx = reinterpret_cast<const LoopCtx*>(w + R.lctx);
-    LoopCounts* d_cnt = reinterpret_cast<LoopCounts*>(w + R.counts);
-    const int64_t* d_ts = reinterpret_cast<const int64_t*>(w + R.ts);
-    const int grid = (n_ctx + kWG - 1) / kWG;
-    batch_loop_init_kernel<<<grid, kWG, 0, b->stream>>>(d_lctx, b->h_lparams, n_ctx, d_cnt);
+    loop_init_kernel<<<1, kWG, 0, b->stream>>>(m.tab, n_ctx, b->h_lparams, m.sums, m.cnt);
+    loop_min_kernel<<<b->loop.blocks, kWG, 0, b->stream>>>(m.tab, m.block_ctx, n_ctx);
     HT_HIP(hipGetLastError());
-    for (int32_t q = 0; q < engine_steps; q += kLoopGraphSteps) HT_HIP(hipGraphLaunch(b->loop_exec, b->stream));
-    batch_loop_results_kernel<<<grid, kWG, 0, b->stream>>>(d_lctx, n_ctx, b->h_lres, d_cnt, d_ts, kMaxLoopCallSteps,
-                                                          b->h_ts);
+    for (int32_t q = 0; q < engine_steps; q += kLoopGraphSteps) HT_HIP(hipGraphLaunch(b->loop.exec, b->stream));
+    loop_results_kernel<<<(n_ctx + kWG - 1) / kWG, kWG, 0, b->stream>>>(m.tab, n_ctx, b->h_lres, m.cnt, m.ts, m.ts_max,
+                                                                       b->h_ts);
     HT_HIP(hipGetLastError());
     HT_HIP(hipStreamSynchronize(b->stream));
     ring_all_free(b->plan_ring);
@@ -4268,10 +4397,10 @@ int ht_batch_dev_run(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const doub
     }
     int rate_khz = 0;
     HT_HIP(hipDeviceGetAttribute(&rate_khz, hipDeviceAttributeWallClockRate, b->device));
-    const int64_t m = std::min<int64_t>(b->h_ts[0], engine_steps);
-    for (int64_t q = 0; q < m; ++q)
+    const int64_t stepped = std::min<int64_t>(b->h_ts[0], engine_steps);
+    for (int64_t q = 0; q < stepped; ++q)
         step_ms[q] = static_cast<double>(b->h_ts[2 + q] - b->h_ts[1 + q]) / std::max(rate_khz, 1);
-    *n_step_ms = static_cast<int32_t>(m);
+    *n_step_ms = static_cast<int32_t>(stepped);
     if (bad >= 0) return fail(HT_ERANGE, "ctx %d: a corrected block step fell below 2^-40", bad);
     if (bad_plan >= 0) return fail(HT_ERANGE, "ctx %d: a device work plan exceeded the context's capacity", bad_plan);
     return take_row_error(b->h_err);
