@@ -3427,8 +3427,14 @@ int ht_state_set(ht_ctx* c, int32_t n, const double* t0, const double* dt, const
     if (!c->ds_mem) return fail(HT_ESTATE, "device state not enabled");
     const double* vec[] = {t0, dt, m, x, v, a, jerk};
     if (n < 1 || !check_vectors(vec, 7)) return fail(HT_EINVAL, "bad state arrays");
-    int rc = ht_set_j_particles(c, n, nullptr, t0, m, x, v, a, jerk);   // the j-records
+    if (n > c->cfg.n_max) return fail(HT_ERANGE, "n = %d over capacity %d", n, c->cfg.n_max);
+    int rc = ctx_sync(c);   // an earlier call's error is reported before anything changes
     if (rc) return rc;
+    if (n != c->n) {
+        c->have_nodes = false;
+        c->have_lists = false;
+        c->n_nodes = 0;
+    }
     const size_t n1 = static_cast<size_t>(n) * 8, n3 = 3 * n1;
     HT_HIP(hipMemcpyAsync(c->ds.t0, t0, n1, hipMemcpyHostToDevice, c->stream));
     HT_HIP(hipMemcpyAsync(c->ds.dt, dt, n1, hipMemcpyHostToDevice, c->stream));
@@ -3439,6 +3445,20 @@ int ht_state_set(ht_ctx* c, int32_t n, const double* t0, const double* dt, const
     HT_HIP(hipMemcpyAsync(c->ds.j, jerk, n3, hipMemcpyHostToDevice, c->stream));
     if (pot) HT_HIP(hipMemcpyAsync(c->ds.pot, pot, n1, hipMemcpyHostToDevice, c->stream));
     else HT_HIP(hipMemsetAsync(c->ds.pot, 0, n1, c->stream));
+    // the j-records from the state on the device (sent once: a second upload of the rows through the
+    // staging area took as long again)
+    const Desc d = c->desc();
+    const int grid = (n + kWG - 1) / kWG;
+    if (c->cfg.precision == HT_PREC_FP64)
+        scatter_kernel<PrecFp64><<<grid, kWG, 0, c->stream>>>(d, n, nullptr, 0, c->ds.t0, 0.0, c->ds.m, c->ds.x, c->ds.v,
+                                                            c->ds.a, c->ds.j, n, c->h_err);
+    else
+        scatter_kernel<PrecMixed><<<grid, kWG, 0, c->stream>>>(d, n, nullptr, 0, c->ds.t0, 0.0, c->ds.m, c->ds.x,
+                                                             c->ds.v, c->ds.a, c->ds.j, n, c->h_err);
+    HT_HIP(hipGetLastError());
+    c->n = n;
+    c->have_particles = true;
+    c->predicted = false;
     c->dev_n_active = -1;
     rc = ctx_sync(c);   // pageable sources
     if (rc) return rc;
