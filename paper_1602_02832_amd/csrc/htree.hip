@@ -1183,6 +1183,8 @@ struct DevLoop {
     int32_t stop_after;  // the step in progress is at the stop time
     int32_t err;         // the device plan did not fit the context
     int32_t ticket;      // due blocks done in this step
+    int32_t below_floor; // a corrected step fell below 2^-40
+    int32_t pad;
     // the call's parameters, so that the captured launches never change
     double t_stop, eta, dt_tree;
     int64_t max_steps;
@@ -1207,8 +1209,6 @@ struct QSum {
 struct LoopEntry {
     DevState s;
     void* rec;
-    DevLoop* loop;
-    DevOut* dout;
     double* brest;        // per scheduler block: earliest next time of the particles not due
     int32_t* boff;        // per due block: its first active position
     uint64_t* due;        // per particle slot of a block: its due particles, (group << 32) | index
@@ -1269,11 +1269,13 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 
 constexpr int kPlanWG = 512;
 constexpr int kPlanWaves = kPlanWG / 64;
+constexpr int kWaveItems = 4;   // items a tile from which on a wave writes them
+constexpr int kEarly = 4;   // due particles of a block that the planner loads before it knows their number
 static_assert(kSchedBlocks <= 2 * kPlanWG && kMaxBatch <= 2 * kPlanWG, "two blocks or contexts a thread");
 
 // Start of a call: every context's loop state from its parameters, counts cleared.
-__global__ __launch_bounds__(kWG) void loop_init_kernel(const LoopEntry* __restrict__ tab, int n_tab,
-                                                        const LoopParams* prm, LoopSum* sums, LoopCounts* cnt) {
+__global__ __launch_bounds__(kWG) void loop_init_kernel(int n_tab, DevLoop* loops, const LoopParams* prm, LoopSum* sums,
+                                                        LoopCounts* cnt) {
     __shared__ int s_run;
     if (threadIdx.x == 0) s_run = 0;
     __syncthreads();
@@ -1285,8 +1287,7 @@ __global__ __launch_bounds__(kWG) void loop_init_kernel(const LoopEntry* __restr
         z.dt_tree = __builtin_bit_cast(double, host_word(w + 2));
         z.max_steps = static_cast<int64_t>(host_word(w + 3));
         z.halt = z.max_steps < 1;   // a context that sits out this call: no kernel touches its state
-        *tab[k].loop = z;
-        *tab[k].dout = DevOut{};
+        loops[k] = z;
         sums[k] = LoopSum{};
         if (!z.halt) atomicAdd(&s_run, 1);
     }
@@ -1300,10 +1301,12 @@ __global__ __launch_bounds__(kWG) void loop_init_kernel(const LoopEntry* __restr
 
 // Then the earliest next time of every scheduler block.
 __global__ __launch_bounds__(kWG) void loop_min_kernel(const LoopEntry* __restrict__ tab,
-                                                       const uint16_t* __restrict__ block_ctx, int n_tab) {
+                                                       const uint16_t* __restrict__ block_ctx, int n_tab,
+                                                       const DevLoop* loops) {
     __shared__ double red[4];
-    const LoopEntry& e = tab[n_tab > 1 ? block_ctx[blockIdx.x] : 0];
-    if (e.loop->halt) return;
+    const int k = n_tab > 1 ? block_ctx[blockIdx.x] : 0;
+    const LoopEntry& e = tab[k];
+    if (loops[k].halt) return;
     const int b = blockIdx.x - e.first_block;
     const int64_t lo = static_cast<int64_t>(b) * e.chunk, hi = lo + e.chunk < e.n ? lo + e.chunk : e.n;
     double v = HUGE_VAL;
@@ -1328,31 +1331,34 @@ __global__ __launch_bounds__(kWG) void group_of_kernel(int64_t n, const int64_t*
 struct PlanLds {
     double wd[kPlanWaves];
     int64_t w64[3][kPlanWaves];
+    struct { int32_t io, po, ns; } split[kPlanWG];   // a tile's first item, first partial slot and splits
+    int64_t per[kPlanWG];        // and entries a split
     int32_t boff[2 * kPlanWG];   // first active position of every scheduler block
     // up to kPlanWG active particles (the common small step): the active groups and
     // the tiles stay in LDS instead of going through memory between the phases
     int32_t qk[kPlanWG + 1], qg[kPlanWG];
     DTile tiles[kPlanWG];
     int32_t g[kPlanWG];
+    uint64_t words[kPlanWG];     // due particles of a small step
     int32_t g_last, go, last;
     int8_t ft[260];              // the tile table, indexed per thread
 };
 
 // Exclusive prefix sums over the work-group (kPlanWG threads) of K values at
 // once; v becomes the sums before the thread's own, total the totals.
-template <int K>
-__device__ inline void plan_scan(int64_t (&v)[K], int64_t (&total)[K], PlanLds& S) {
+template <class V, int K>
+__device__ inline void plan_scan(V (&v)[K], V (&total)[K], PlanLds& S) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int64_t x[K];
+    V x[K];
     for (int k = 0; k < K; ++k) {
         x[k] = wave_ops::scan_inclusive(v[k]);
         if (lane == 63) S.w64[k][wave] = x[k];
     }
     __syncthreads();
     for (int k = 0; k < K; ++k) {
-        int64_t before = 0, all = 0;
+        V before = 0, all = 0;
         for (int w = 0; w < kPlanWaves; ++w) {
-            const int64_t sw = S.w64[k][w];
+            const V sw = static_cast<V>(S.w64[k][w]);
             if (w < wave) before += sw;
             all += sw;
         }
@@ -1374,10 +1380,9 @@ __device__ inline double plan_min(double v, PlanLds& S) {
 }
 
 // Take the step at t with n active particles if t is at most the stop time,
-// else stop the loop (and every later kernel with it).
-__device__ inline bool loop_gate(DevLoop* L, const DevOut* o, double t, int64_t n) {
-    DevLoop z = *L;
-    const bool go = !(z.stop_after || o->below_floor || !(t <= z.t_stop) || z.steps >= z.max_steps || n < 1);
+// else stop the loop (and every later kernel with it); z: the loop's state.
+__device__ inline bool loop_gate(DevLoop* L, const DevLoop& z, double t, int64_t n) {
+    const bool go = !(z.stop_after || z.below_floor || !(t <= z.t_stop) || z.steps >= z.max_steps || n < 1);
     if (!go) {
         L->halt = 1;
         L->n_corr = 0;
@@ -1395,28 +1400,49 @@ __device__ inline bool loop_gate(DevLoop* L, const DevOut* o, double t, int64_t 
 // work-group: active groups, least-cost tiles, cost-based splits with the same
 // quantum (the costs are whole numbers when the gather cost is, so their sum
 // does not depend on the order of addition), in group order.  The order of the
-// items does not change any result.  due0, due1: whether scheduler blocks 2t
-// and 2t + 1 of thread t are due.  Returns the number of items.
-__device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_next, bool due0, bool due1, Entry* out,
-                                    LoopSum* sum) {
+// items does not change any result.  L, z: the loop's state, and as it was
+// loaded at the start; n_due: due scheduler blocks; due0, due1: whether blocks
+// 2t and 2t + 1 of thread t are among them; lds_n: where this work-group's block
+// is the only due one and its particles are in S.words, their number, else -1.
+__device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& z, PlanLds& S, double t_next,
+                                 int32_t n_due, bool due0, bool due1, int32_t lds_n, Entry* out, LoopSum* sum) {
     const int t = threadIdx.x;
-    if (t < 257) S.ft[t] = e.first_tile[t];
     if (t == 0) S.g_last = -1;
-    int64_t n;
-    {   // active positions of the due blocks
+    int64_t n = lds_n;
+    bool in_lds = lds_n >= 0;   // the due particles are in S.words, in order
+    if (in_lds) {
+        if (due0) e.boff[2 * t] = 0;
+        if (due1) e.boff[2 * t + 1] = 0;
+    } else {   // active positions of the due blocks
         const int32_t c0 = due0 ? agent_load(e.s.bcount + 2 * t) : 0, c1 = due1 ? agent_load(e.s.bcount + 2 * t + 1) : 0;
-        int64_t v[1] = {c0 + static_cast<int64_t>(c1)}, tot[1];
+        // the first particles of the due blocks come with the counts, not after them
+        uint64_t w0[kEarly], w1[kEarly];
+#pragma unroll
+        for (int u = 0; u < kEarly; ++u) {
+            w0[u] = due0 && u < e.chunk ? agent_load(e.due + int64_t(2 * t) * e.chunk + u) : 0;
+            w1[u] = due1 && u < e.chunk ? agent_load(e.due + int64_t(2 * t + 1) * e.chunk + u) : 0;
+        }
+        int32_t v[2] = {c0 + c1, c0 > kEarly || c1 > kEarly}, tot[2];
         plan_scan(v, tot, S);
         n = tot[0];
-        S.boff[2 * t] = static_cast<int32_t>(v[0]);
-        S.boff[2 * t + 1] = static_cast<int32_t>(v[0]) + c0;
-        if (due0) e.boff[2 * t] = static_cast<int32_t>(v[0]);
-        if (due1) e.boff[2 * t + 1] = static_cast<int32_t>(v[0]) + c0;
+        in_lds = tot[1] == 0 && n <= kPlanWG;
+        const int32_t p0 = v[0], p1 = p0 + c0;
+        S.boff[2 * t] = p0;
+        S.boff[2 * t + 1] = p1;
+        if (due0) e.boff[2 * t] = p0;
+        if (due1) e.boff[2 * t + 1] = p1;
+        if (in_lds) {
+#pragma unroll
+            for (int u = 0; u < kEarly; ++u) {
+                if (u < c0) S.words[p0 + u] = w0[u];
+                if (u < c1) S.words[p1 + u] = w1[u];
+            }
+        }
     }
-    if (t == 0) S.go = loop_gate(e.loop, e.dout, t_next, n);   // take this step or stop the loop
+    if (t == 0) S.go = loop_gate(L, z, t_next, n);   // take this step or stop the loop
     __syncthreads();
     *sum = LoopSum{0, 0, S.go};
-    if (!S.go) return 0;
+    if (!S.go) return;
     sum->rows = n;
     const bool small = n <= kPlanWG;
     int32_t* QK = small ? S.qk : e.qk;
@@ -1426,8 +1452,20 @@ __device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_nex
     // active position and group, in order); four positions a thread, and a
     // position's predecessor's group comes through LDS
     int64_t nq = 0;
+    if (in_lds) {   // a position a thread
+        const int32_t g = t < n ? static_cast<int32_t>(S.words[t] >> 32) : -1;
+        if (t < n) e.s.active[t] = static_cast<int32_t>(S.words[t]);
+        int32_t v[1] = {t < n && (t == 0 || g != static_cast<int32_t>(S.words[t - 1] >> 32))}, tot[1];
+        const bool head = v[0] != 0;
+        plan_scan(v, tot, S);
+        if (head) {
+            QK[v[0]] = t;
+            QG[v[0]] = g;
+        }
+        nq = tot[0];
+    }
     constexpr int kPos = 4;
-    for (int64_t base = 0; base < n; base += kPos * kPlanWG) {
+    for (int64_t base = 0; !in_lds && base < n; base += kPos * kPlanWG) {
         const int64_t q0 = base + kPos * t;
         int32_t g[kPos];
         int blk = 0;
@@ -1450,7 +1488,7 @@ __device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_nex
         S.g[t] = g[kPos - 1];
         __syncthreads();
         int32_t prev = t > 0 ? S.g[t - 1] : S.g_last;
-        int64_t v[1] = {0}, tot[1];
+        int32_t v[1] = {0}, tot[1];
         bool head[kPos];
 #pragma unroll
         for (int u = 0; u < kPos; ++u) {
@@ -1477,7 +1515,7 @@ __device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_nex
     int64_t pairs = 0;
     for (int64_t base = 0; base < nq; base += kPlanWG) {
         const int64_t q = base + t;
-        int64_t v[1] = {0}, tot[1];
+        int32_t v[1] = {0}, tot[1];
         int64_t jb = 0, je = 0;
         int32_t r0 = 0, tb = 0;
         if (q < nq) {
@@ -1539,64 +1577,77 @@ __device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_nex
         return (rounds + rper - 1) / rper;
     };
     int64_t v[2], tot[2];
+    uint32_t ns = 0;   // of tile t
+    int64_t per = 0;
     for (;; ++attempt) {
         v[0] = v[1] = 0;
         for (int64_t q = t; q < ntile; q += kPlanWG) {
-            int64_t per;
-            const uint32_t ns = split(TL[q], &per);
-            v[0] += ns;
-            if (per) v[1] += static_cast<int64_t>(ns) * TL[q].ni;
+            int64_t pq;
+            const uint32_t nsq = split(TL[q], &pq);
+            v[0] += nsq;
+            if (pq) v[1] += static_cast<int64_t>(nsq) * TL[q].ni;
+            if (q == t) {
+                ns = nsq;
+                per = pq;
+            }
         }
         plan_scan(v, tot, S);
         if (tot[0] <= e.items_max && tot[1] <= e.partial_max) break;
         if (attempt > 60) {   // does not fit: stop the loop before this step's force
             if (t == 0) {
-                DevLoop* L = e.loop;
                 L->err = 1;
                 L->halt = 1;
-                L->steps -= 1;
-                L->psteps -= n;
+                L->steps = z.steps;
+                L->psteps = z.psteps;
                 L->n_corr = 0;
             }
             *sum = LoopSum{0, 0, 0};
-            return 0;
+            return;
         }
         quantum *= 2.0;
     }
-    // 5. items, in tile order
+    // 5. items, in tile order: a thread writes its tile's, or a wave where a tile
+    // has several (the small steps: one after the other they took 2 us of 12)
     const int64_t n_items = tot[0];
-    int64_t io = 0, po = 0;
-    for (int64_t base = 0; base < ntile; base += kPlanWG) {
-        const int64_t q = base + t;
-        int64_t per = 0;
-        uint32_t ns = 0;
-        DTile T{};
-        if (q < ntile) {
-            T = TL[q];
-            ns = split(T, &per);
+    auto write_tile = [&](const DTile& T, uint32_t nsq, int64_t pq, int64_t first, int64_t slot, int begin, int step) {
+        const int16_t ni = static_cast<int16_t>(T.ni), tl = static_cast<int16_t>(T.tl);
+        Item* it = e.items + first;
+        const QSum qs{pq ? slot : -1, pq ? T.ni : 0, pq ? static_cast<int32_t>(nsq) : 0};
+        for (int32_t u = begin; u < T.ni; u += step) e.qsum[T.tb + u] = QSum{pq ? qs.first + u : -1, qs.stride, qs.nsplit};
+        if (pq == 0) {
+            if (begin == 0) it[0] = Item{T.jb, T.je, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
+            return;
         }
-        if (ntile > kPlanWG) {   // else the sums of the splits above are these
-            v[0] = ns;
-            v[1] = per ? static_cast<int64_t>(ns) * T.ni : 0;
-            plan_scan(v, tot, S);
+        for (int32_t k = begin; k < static_cast<int32_t>(nsq); k += step) {
+            const int64_t b = T.jb + k * pq;
+            it[k] = Item{b, b + pq < T.je ? b + pq : T.je, slot + static_cast<int64_t>(k) * T.ni, T.tb, ni,
+                         static_cast<int16_t>(k == 0 ? tl | kSelfTerm : tl)};
         }
-        if (q < ntile) {
-            const int16_t ni = static_cast<int16_t>(T.ni), tl = static_cast<int16_t>(T.tl);
-            Item* it = e.items + io + v[0];
-            if (per == 0) {
-                *it = Item{T.jb, T.je, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
-                for (int32_t u = 0; u < T.ni; ++u) e.qsum[T.tb + u] = QSum{-1, 0, 0};
-            } else {
-                const int64_t pb = po + v[1];
-                for (int32_t u = 0; u < T.ni; ++u) e.qsum[T.tb + u] = QSum{pb + u, T.ni, static_cast<int32_t>(ns)};
-                int64_t b = T.jb;
-                for (uint32_t s = 0; s < ns; ++s, b += per)
-                    it[s] = Item{b, b + per < T.je ? b + per : T.je, pb + static_cast<int64_t>(s) * T.ni, T.tb, ni,
-                                 static_cast<int16_t>(s == 0 ? tl | kSelfTerm : tl)};
+    };
+    if (small && n_items >= kWaveItems * ntile) {
+        S.split[t].io = static_cast<int32_t>(v[0]);
+        S.split[t].po = static_cast<int32_t>(v[1]);
+        S.split[t].ns = static_cast<int32_t>(ns);
+        S.per[t] = per;
+        __syncthreads();
+        for (int k = t >> 6; k < ntile; k += kPlanWaves)
+            write_tile(S.tiles[k], S.split[k].ns, S.per[k], S.split[k].io, S.split[k].po, t & 63, 64);
+    } else {
+        int64_t io = 0, po = 0;
+        for (int64_t base = 0; base < ntile; base += kPlanWG) {
+            const int64_t q = base + t;
+            DTile T{};
+            if (q < ntile) T = TL[q];
+            if (ntile > kPlanWG) {   // else the sums of the splits above are these
+                ns = q < ntile ? split(T, &per) : 0;
+                v[0] = ns;
+                v[1] = ns > 1 ? static_cast<int64_t>(ns) * T.ni : 0;
+                plan_scan(v, tot, S);
             }
+            if (q < ntile) write_tile(T, ns, per, io + v[0], po + v[1], 0, 1);
+            io += tot[0];
+            po += tot[1];
         }
-        io += tot[0];
-        po += tot[1];
     }
     if (t == 0) {
         Entry& o = *out;
@@ -1607,10 +1658,9 @@ __device__ inline int64_t plan_step(const LoopEntry& e, PlanLds& S, double t_nex
         o.first_rtile = 0;
         o.n_items = n_items;
         o.n_rtiles = 0;
-        e.loop->pairs += pairs;
+        L->pairs = z.pairs + pairs;
     }
     sum->items = n_items;
-    return n_items;
 }
 
 // Every context's first item in this step's launch, the totals, the contexts
@@ -1646,7 +1696,7 @@ __device__ inline void place_items(int n_tab, Entry* launch, const LoopSum* sums
 // Step 2 and the work plan (see above).
 __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* __restrict__ tab,
                                                               const uint16_t* __restrict__ block_ctx, int n_tab,
-                                                              Entry* launch, LoopSum* sums, LoopCounts* cnt,
+                                                              DevLoop* loops, Entry* launch, LoopSum* sums, LoopCounts* cnt,
                                                               int64_t* ts, int64_t ts_max) {
     __shared__ PlanLds S;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -1654,12 +1704,15 @@ __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* _
     const LoopEntry& e = tab[k];
     const int b = blockIdx.x - e.first_block;
     const int64_t lo = static_cast<int64_t>(b) * e.chunk, hi = lo + e.chunk < e.n ? lo + e.chunk : e.n;
+    DevLoop* L = loops + k;
+    const DevLoop z = *L;   // only the planner, at the end of this launch, changes it (and the ticket)
     // the earliest block time, the blocks that hold it, and whether this one does
-    if (e.loop->halt) return;
+    if (z.halt) return;
     const double m0 = 2 * t < e.nb ? e.s.bmin[2 * t] : HUGE_VAL, m1 = 2 * t + 1 < e.nb ? e.s.bmin[2 * t + 1] : HUGE_VAL;
     const double own = e.s.bmin[b];
     const double t_next = plan_min(fmin(m0, m1), S);
     if (own != t_next) return;
+    const int8_t ft = t < 257 ? e.first_tile[t] : 0;   // for the plan
     const bool due0 = 2 * t < e.nb && m0 == t_next, due1 = 2 * t + 1 < e.nb && m1 == t_next;
     int32_t n_due = 0;
     {
@@ -1687,28 +1740,33 @@ __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* _
             if (w < wave) at += S.qg[w];
             cnt_b += S.qg[w];
         }
-        if (due) agent_store(e.due + lo + at, static_cast<uint64_t>(static_cast<uint32_t>(g)) << 32 | static_cast<uint32_t>(i));
+        if (due) {
+            const uint64_t w = static_cast<uint64_t>(static_cast<uint32_t>(g)) << 32 | static_cast<uint32_t>(i);
+            agent_store(e.due + lo + at, w);
+            if (at < kPlanWG) S.words[at] = w;
+        }
         __syncthreads();
     }
     for (int w = 0; w < kPlanWaves; ++w) n_due += S.g[w];
+    if (t < 257) S.ft[t] = ft;
     rest = plan_min(rest, S);
     if (t == 0) {
         e.brest[b] = rest;
         agent_store(e.s.bcount + b, cnt_b);
     }
-    stores_done();
-    __syncthreads();
-    if (t == 0) {
-        const int32_t ticket = __hip_atomic_fetch_add(&e.loop->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        S.last = ticket == n_due - 1;
-        if (S.last) agent_store(&e.loop->ticket, 0);
+    if (n_due > 1) {   // on to the plan in the last of the due blocks
+        stores_done();
+        __syncthreads();
+        if (t == 0) {
+            S.last = __hip_atomic_fetch_add(&L->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_due - 1;
+            if (S.last) agent_store(&L->ticket, 0);
+        }
+        __syncthreads();
+        if (!S.last) return;
+        asm volatile("" ::: "memory");
     }
-    __syncthreads();
-    if (!S.last) return;
-    // the context's last due block: plan its step
-    asm volatile("" ::: "memory");
     LoopSum sum;
-    plan_step(e, S, t_next, due0, due1, launch + k, &sum);
+    plan_step(e, L, z, S, t_next, n_due, due0, due1, n_due == 1 && cnt_b <= kPlanWG ? cnt_b : -1, launch + k, &sum);
     if (n_tab == 1) {
         if (t == 0) {
             launch->first_item = 0;
@@ -1735,12 +1793,13 @@ __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* _
 // Step 6 by scheduler blocks (see above).
 template <class P>
 __global__ __launch_bounds__(kWG) void loop_correct_kernel(const LoopEntry* __restrict__ tab,
-                                                           const uint16_t* __restrict__ block_ctx, int n_tab) {
+                                                           const uint16_t* __restrict__ block_ctx, int n_tab,
+                                                           DevLoop* loops) {
     __shared__ double red[4];
     const int k = n_tab > 1 ? block_ctx[blockIdx.x] : 0;
     const LoopEntry& e = tab[k];
     const int b = blockIdx.x - e.first_block;
-    const DevLoop& L = *e.loop;
+    const DevLoop& L = loops[k];
     const double t1 = L.t_cur, eta = L.eta, dt_tree = L.dt_tree, own = e.s.bmin[b];
     if (L.n_corr == 0 || own != t1) return;
     const int32_t cnt = e.s.bcount[b], q0 = e.boff[b];
@@ -1761,7 +1820,7 @@ __global__ __launch_bounds__(kWG) void loop_correct_kernel(const LoopEntry* __re
             sum_splits(e.d.partial + sp.first * kOut, static_cast<int64_t>(sp.stride) * kOut, sp.nsplit, F);
         }
         const double h = correct_particle<P>(e.s, e.rec, i, t1, eta, dt_tree, F);
-        if (h == 0.0) e.dout->below_floor = 1;
+        if (h == 0.0) loops[k].below_floor = 1;
         first = fmin(first, t1 + h);
     }
     first = block_min(first, red);
@@ -1769,13 +1828,13 @@ __global__ __launch_bounds__(kWG) void loop_correct_kernel(const LoopEntry* __re
 }
 
 // End of a call: every context's counts and state, and the step times, into pinned memory.
-__global__ __launch_bounds__(kWG) void loop_results_kernel(const LoopEntry* __restrict__ tab, int n, LoopResult* out,
+__global__ __launch_bounds__(kWG) void loop_results_kernel(const DevLoop* loops, int n, LoopResult* out,
                                                            const LoopCounts* cnt, const int64_t* ts, int64_t ts_max,
                                                            int64_t* ts_out) {
     const int k = blockIdx.x * kWG + threadIdx.x;
     if (k < n) {
-        const DevLoop& L = *tab[k].loop;
-        out[k] = LoopResult{L.steps, L.psteps, L.pairs, L.t_cur, L.err, tab[k].dout->below_floor};
+        const DevLoop& L = loops[k];
+        out[k] = LoopResult{L.steps, L.psteps, L.pairs, L.t_cur, L.err, L.below_floor};
     }
     if (!ts_out) return;
     const int64_t m = cnt->step < ts_max ? cnt->step : ts_max;
@@ -1982,10 +2041,7 @@ struct ht_ctx {
     DevState ds{};
     char* ds_mem = nullptr;
     bool own_ds = false;   // ds_mem allocated by the library (ht_state_enable), not the caller's
-    // device loops: this context's loop state and table entry, the group and
-    // list offsets, and the planner's scratch
-    DevLoop* d_loop = nullptr;
-    DevOut* d_dout = nullptr;
+    // device loops: the group and list offsets, and the planner's scratch
     int64_t* d_gfirst = nullptr;
     int64_t* d_loff = nullptr;
     int32_t *d_qk = nullptr, *d_qg = nullptr, *d_pgroup = nullptr, *d_boff = nullptr;
@@ -3304,7 +3360,7 @@ namespace {
 // Where the resident state's arrays sit in its one device allocation.
 struct StateLayout {
     size_t x, v, a, j, t0, dt, m, pot, acc, jerk, fpot, act, bmin, bcnt;
-    size_t loop, dout, gf, lo, qsum, qk, qg, tiles, pgroup, boff, brest, due, ltab, lsum, lcnt;
+    size_t loop, gf, lo, qsum, qk, qg, tiles, pgroup, boff, brest, due, ltab, lsum, lcnt;
     size_t total;
 };
 
@@ -3333,7 +3389,6 @@ StateLayout state_layout(const ht_config& cfg) {
     S.bcnt = take(kSchedBlocks * 4);
     const size_t g1 = static_cast<size_t>(cfg.group_max) + 1;
     S.loop = take(sizeof(DevLoop));
-    S.dout = take(sizeof(DevOut));
     S.gf = take(g1 * 8);
     S.lo = take(g1 * 8);
     S.qsum = take(n * sizeof(QSum));
@@ -3365,8 +3420,6 @@ int state_attach(ht_ctx* c, char* mem, bool own) {
                      reinterpret_cast<double*>(b + S.acc), reinterpret_cast<double*>(b + S.jerk),
                      reinterpret_cast<double*>(b + S.fpot), reinterpret_cast<int32_t*>(b + S.act),
                      reinterpret_cast<double*>(b + S.bmin), reinterpret_cast<int32_t*>(b + S.bcnt)};
-    c->d_loop = reinterpret_cast<DevLoop*>(b + S.loop);
-    c->d_dout = reinterpret_cast<DevOut*>(b + S.dout);
     c->d_gfirst = reinterpret_cast<int64_t*>(b + S.gf);
     c->d_loff = reinterpret_cast<int64_t*>(b + S.lo);
     c->d_qsum = reinterpret_cast<QSum*>(b + S.qsum);
@@ -3623,8 +3676,6 @@ LoopEntry loop_entry_of(const ht_ctx* c, int32_t first_block) {
     std::memset(static_cast<void*>(&e), 0, sizeof e);   // entries are compared byte by byte
     e.s = c->ds;
     e.rec = c->ws + c->L.off_rec;
-    e.loop = c->d_loop;
-    e.dout = c->d_dout;
     e.brest = c->d_brest;
     e.boff = c->d_boff;
     e.due = c->d_due;
@@ -3659,6 +3710,7 @@ LoopEntry loop_entry_of(const ht_ctx* c, int32_t first_block) {
 struct LoopMem {
     LoopEntry* tab;
     uint16_t* block_ctx;
+    DevLoop* loops;
     Entry* launch;
     LoopSum* sums;
     LoopCounts* cnt;
@@ -3669,9 +3721,10 @@ struct LoopMem {
 template <class P>
 void queue_loop_step(const LoopRun& r, const LoopMem& m, hipStream_t s) {
     const int n_tab = static_cast<int>(r.n_tab);
-    loop_select_kernel<<<r.blocks, kPlanWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.launch, m.sums, m.cnt, m.ts, m.ts_max);
+    loop_select_kernel<<<r.blocks, kPlanWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.loops, m.launch, m.sums, m.cnt, m.ts,
+                                                    m.ts_max);
     force_kernel<P, false, false><<<r.force_grid, kWG, 0, s>>>(m.launch, n_tab, -1, &m.cnt->items);
-    loop_correct_kernel<P><<<r.blocks, kWG, 0, s>>>(m.tab, m.block_ctx, n_tab);
+    loop_correct_kernel<P><<<r.blocks, kWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.loops);
 }
 
 // The loop's table and graph for these contexts, unless those of the last call serve.
@@ -3726,7 +3779,7 @@ int prepare_loop(LoopRun& r, const LoopMem& m, int32_t n_ctx, ht_ctx* const* ctx
 LoopMem loop_mem(const ht_ctx* c) {
     const StateLayout S = state_layout(c->cfg);
     return LoopMem{reinterpret_cast<LoopEntry*>(c->ds_mem + S.ltab), nullptr,
-                   reinterpret_cast<Entry*>(c->ws + c->L.off_plan), reinterpret_cast<LoopSum*>(c->ds_mem + S.lsum),
+                   reinterpret_cast<DevLoop*>(c->ds_mem + S.loop), reinterpret_cast<Entry*>(c->ws + c->L.off_plan), reinterpret_cast<LoopSum*>(c->ds_mem + S.lsum),
                    reinterpret_cast<LoopCounts*>(c->ds_mem + S.lcnt), nullptr, 0};
 }
 }  // namespace
@@ -3752,11 +3805,11 @@ int ht_dev_run(ht_ctx* c, double eta, double dt_tree, double t_stop, int32_t max
     if (int rc = prepare_loop(c->loop, m, 1, &c, c->stream, c->cap_stream)) return rc;
     c->slots_all_free();
     *c->h_lparams = LoopParams{t_stop, eta, dt_tree, max_steps};
-    loop_init_kernel<<<1, kWG, 0, c->stream>>>(m.tab, 1, c->h_lparams, m.sums, m.cnt);
-    loop_min_kernel<<<c->loop.blocks, kWG, 0, c->stream>>>(m.tab, m.block_ctx, 1);
+    loop_init_kernel<<<1, kWG, 0, c->stream>>>(1, m.loops, c->h_lparams, m.sums, m.cnt);
+    loop_min_kernel<<<c->loop.blocks, kWG, 0, c->stream>>>(m.tab, m.block_ctx, 1, m.loops);
     HT_HIP(hipGetLastError());
     for (int32_t k = 0; k < max_steps; k += kLoopGraphSteps) HT_HIP(hipGraphLaunch(c->loop.exec, c->stream));
-    loop_results_kernel<<<1, kWG, 0, c->stream>>>(m.tab, 1, c->h_lres, m.cnt, nullptr, 0, nullptr);
+    loop_results_kernel<<<1, kWG, 0, c->stream>>>(m.loops, 1, c->h_lres, m.cnt, nullptr, 0, nullptr);
     HT_HIP(hipGetLastError());
     HT_HIP(hipStreamSynchronize(c->stream));
     const LoopResult& L = *c->h_lres;
@@ -3898,7 +3951,7 @@ constexpr int kMaxLoopCallSteps = 4096;   // engine steps per ht_batch_dev_run c
 
 // The batched device loop's tables, one entry per context of the batch.
 struct LoopRegion {
-    size_t tab, blocks, launch, sums, counts, ts, total;
+    size_t tab, blocks, loops, launch, sums, counts, ts, total;
 };
 
 LoopRegion loop_region(int32_t max_clusters) {
@@ -3912,6 +3965,7 @@ LoopRegion loop_region(int32_t max_clusters) {
     const size_t m = static_cast<size_t>(max_clusters);
     r.tab = take(m * sizeof(LoopEntry));
     r.blocks = take(m * kSchedBlocks * sizeof(uint16_t));
+    r.loops = take(m * sizeof(DevLoop));
     r.launch = take(m * sizeof(Entry));
     r.sums = take(m * sizeof(LoopSum));
     r.counts = take(sizeof(LoopCounts));
@@ -3924,7 +3978,7 @@ LoopMem loop_mem(const ht_batch* b) {
     const LoopRegion R = loop_region(b->max_clusters);
     char* w = b->loop_ws;
     return LoopMem{reinterpret_cast<LoopEntry*>(w + R.tab), reinterpret_cast<uint16_t*>(w + R.blocks),
-                   reinterpret_cast<Entry*>(w + R.launch), reinterpret_cast<LoopSum*>(w + R.sums),
+                   reinterpret_cast<DevLoop*>(w + R.loops), reinterpret_cast<Entry*>(w + R.launch), reinterpret_cast<LoopSum*>(w + R.sums),
                    reinterpret_cast<LoopCounts*>(w + R.counts), reinterpret_cast<int64_t*>(w + R.ts),
                    kMaxLoopCallSteps};
 }
@@ -4387,11 +4441,11 @@ int ht_batch_dev_run(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const doub
         ctxs[k]->dev_n_active = -1;
         ctxs[k]->slots_all_free();
     }
-    loop_init_kernel<<<1, kWG, 0, b->stream>>>(m.tab, n_ctx, b->h_lparams, m.sums, m.cnt);
-    loop_min_kernel<<<b->loop.blocks, kWG, 0, b->stream>>>(m.tab, m.block_ctx, n_ctx);
+    loop_init_kernel<<<1, kWG, 0, b->stream>>>(n_ctx, m.loops, b->h_lparams, m.sums, m.cnt);
+    loop_min_kernel<<<b->loop.blocks, kWG, 0, b->stream>>>(m.tab, m.block_ctx, n_ctx, m.loops);
     HT_HIP(hipGetLastError());
     for (int32_t q = 0; q < engine_steps; q += kLoopGraphSteps) HT_HIP(hipGraphLaunch(b->loop.exec, b->stream));
-    loop_results_kernel<<<(n_ctx + kWG - 1) / kWG, kWG, 0, b->stream>>>(m.tab, n_ctx, b->h_lres, m.cnt, m.ts, m.ts_max,
+    loop_results_kernel<<<(n_ctx + kWG - 1) / kWG, kWG, 0, b->stream>>>(m.loops, n_ctx, b->h_lres, m.cnt, m.ts, m.ts_max,
                                                                        b->h_ts);
     HT_HIP(hipGetLastError());
     HT_HIP(hipStreamSynchronize(b->stream));
