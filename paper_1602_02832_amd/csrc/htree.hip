@@ -145,6 +145,7 @@ struct Item {
     int64_t j_begin;    // first list entry (or first particle, direct sum)
     int64_t j_end;
     int64_t out;        // -1: final results; otherwise partial slot of i-slot 0
+    int32_t rtile;      // the split tile whose partials the last of its items sums, or -1
     int32_t act_begin;  // active-array position of i-slot 0
     int16_t n_i;        // valid i-slots (1..T)
     int16_t tile_log2;  // T = 1 << (tile_log2 & kTileMask); kSelfTerm: the item holding the start of its
@@ -162,7 +163,7 @@ struct RTile {
     int32_t act_begin;
     int32_t n_i;
     int32_t nsplit;
-    int32_t pad;
+    int32_t ticket;   // items done in this launch (0 as the plan is delivered)
 };
 
 // One cluster in a launch: its descriptor and where its items sit in the
@@ -173,8 +174,8 @@ struct Entry {
     const RTile* rtiles;
     int64_t first_item;
     int64_t first_rtile;
-    int64_t n_items;    // entry 0: items and split tiles of the whole launch (graph replays
-    int64_t n_rtiles;   // read them here, their launch arguments being fixed)
+    int64_t n_items;    // entry 0: items of the whole launch (graph replays read them here, their launch
+                        // arguments being fixed)
 };
 
 struct PrecFp64 {
@@ -219,6 +220,21 @@ struct RunLds {
     int32_t off[kRoundMax];
 };
 struct NoRunLds {};
+
+// ------------------------------------------------------------------------------------------------
+// Data that work-groups of one launch hand to each other: agent-scope stores
+// and loads, which every XCD sees (they pass the L2s, which are not coherent
+// with each other), and a ticket taken once the stores are done.
+template <class V>
+__device__ __forceinline__ V agent_load(const V* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class V>
+__device__ __forceinline__ void agent_store(V* p, V v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// All of the wave's stores so far have reached the scope they were made for.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ------------------------------------------------------------------------------------------------
 // predictor (4th-order Hermite, Section 1/2): Taylor series to the jerk, FP64.
@@ -359,7 +375,11 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
     constexpr int R = kRound * G;       // entries per round
     constexpr int S = kWG / T;          // j-streams
     constexpr int PER = R / S;          // pairs per thread in a full round (= G T)
-    const int tid = threadIdx.x;
+    // The kernel holds nine of these, one for each T, in its loop over items:
+    // without this the compiler works out every one's addresses before the loop
+    // and keeps them, which takes about 40 VGPRs.
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     const int islot = tid & (T - 1);
     const int stream = tid / T;
     const bool has_i = islot < it.n_i;
@@ -561,10 +581,79 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
             write_out(c, it.act_begin + islot, A.v);
         } else {
             double* p = c.partial + (it.out + islot) * kOut;
+            if (it.rtile >= 0) {
 #pragma unroll
-            for (int q = 0; q < kOut; ++q) p[q] = A.v[q];
+                for (int q = 0; q < kOut; ++q) agent_store(p + q, A.v[q]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < kOut; ++q) p[q] = A.v[q];
+            }
         }
     }
+}
+
+// The sums over nsplit splits, in split order, of `vals` values that lie next
+// to each other in every split (slot by slot from active position o0 on; splits
+// are `stride` values apart), into the outputs.  They come through LDS, as many
+// splits at a time as buf holds, so that the dependent adds wait on no memory.
+// The work-group's threads take at most kOut values each.
+template <int HOLD, class Load>
+__device__ __forceinline__ void sum_slots(const Desc& c, int64_t o0, int vals, int nsplit, int64_t stride, double* buf,
+                                          int tid, Load load) {
+    const int per = HOLD / vals;
+    double sum[kOut];
+    for (int s0 = 0; s0 < nsplit; s0 += per) {
+        const int m = nsplit - s0 < per ? nsplit - s0 : per;
+        __syncthreads();
+#pragma unroll 4
+        for (int k = tid; k < m * vals; k += kWG) {
+            const int s = k / vals;
+            buf[k] = load((s0 + s) * stride + (k - s * vals));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kOut; ++u) {
+            const int v = tid + u * kWG;
+            if (v >= vals) break;
+            double a = s0 == 0 ? buf[v] : sum[u];
+            for (int k = s0 == 0 ? 1 : 0; k < m; ++k) a += buf[k * vals + v];
+            sum[u] = a;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kOut; ++u) {
+        const int v = tid + u * kWG;
+        if (v >= vals) break;
+        const int64_t o = o0 + v / kOut;
+        const int q = v % kOut;
+        if (q < 3) c.acc[3 * o + q] = sum[u];
+        else if (q < 6) c.jerk[3 * o + q - 3] = sum[u];
+        else c.pot[o] = sum[u];
+    }
+}
+
+// An item of a split tile is done: the last one sums the tile's partials.  (A
+// launch of its own for these sums costs 4 to 11 us of a small step and 3.5 us
+// of the host's time.  Fences instead of agent-scope stores cost 7 us: they
+// write back and invalidate the whole L2.)
+template <class P>
+__device__ __forceinline__ void fold_splits(const Desc& c, const Item& it, RTile* rtiles, LdsAll<P>& lds) {
+    __shared__ int s_last;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // addresses are worked out here, not kept in registers from the kernel's start on
+    RTile* rt = rtiles + it.rtile;
+    const int nsplit = rt->nsplit;
+    const double* src = c.partial + rt->pbase * kOut;
+    stores_done();
+    __syncthreads();
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(&rt->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
+    __syncthreads();
+    if (!s_last) return;
+    asm volatile("" ::: "memory");
+    const int vals = it.n_i * kOut;
+    sum_slots<sizeof(LdsAll<P>) / sizeof(double)>(c, it.act_begin, vals, nsplit, vals, reinterpret_cast<double*>(&lds),
+                                                  tid, [&](int64_t k) { return agent_load(src + k); });
 }
 
 __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g, bool rtile) {
@@ -577,11 +666,8 @@ __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g
     return lo;
 }
 
-// Register budget: the mixed form fits 128 VGPRs (4 waves per SIMD) without
-// spilling; the FP64 form, the run-length lists' expansion and the union
-// tiles' masked pairs need a little more and run 3 waves per SIMD.
-template <class P, bool RUNS = false, bool UNI = false>
-struct WavesPerSimd { static constexpr int value = P::kMixed && !RUNS && !UNI ? 4 : 3; };
+// Register budget: every form fits 128 VGPRs (4 waves per SIMD) without spilling.
+constexpr int kWavesPerSimd = 4;
 
 // Work-group g takes items g, g + grid, ...  The grid is normally the item
 // count; graph replays and device loops launch a fixed grid and pass
@@ -597,7 +683,7 @@ struct WavesPerSimd { static constexpr int value = P::kMixed && !RUNS && !UNI ? 
 // UNI: the plan holds union-tile items (a separate instantiation, so that the
 // plain kernel keeps its register budget).
 template <class P, bool EAGER, bool DIRECT, bool RUNS = false, bool UNI = false>
-__global__ __launch_bounds__(kWG, (WavesPerSimd<P, RUNS, UNI>::value)) void force_kernel(const Entry* __restrict__ tab,
+__global__ __launch_bounds__(kWG, kWavesPerSimd) void force_kernel(const Entry* __restrict__ tab,
                                                                                    int n_tab, int64_t n_items,
                                                                                    const int64_t* counts,
                                                                                    const int64_t* bins = nullptr,
@@ -629,44 +715,33 @@ __global__ __launch_bounds__(kWG, (WavesPerSimd<P, RUNS, UNI>::value)) void forc
             case 1: run_item<P, EAGER, DIRECT, RUNS, 2, decltype(rl), UNI>(c, it, r0, lds, rl); break;
             default: run_item<P, EAGER, DIRECT, RUNS, 1, decltype(rl), UNI>(c, it, r0, lds, rl); break;
         }
+        {   // the item is read again, so that nothing of it stays in registers over the pair loops
+            int64_t h = g;
+            asm volatile("" : "+s"(h));
+            const Entry& te = tab[find_entry(tab, n_tab, h, false)];
+            const Item done = te.items[h - te.first_item];
+            if (done.rtile >= 0) fold_splits<P>(te.d, done, const_cast<RTile*>(te.rtiles), lds);
+        }
         __syncthreads();
     }
 }
 
-// Sum the split partials of each i-slot in split order (a separate launch:
-// the kernel boundary makes every partial visible, with no device-wide
-// fences in the force kernel).  A tile's partials are first loaded into LDS
-// by all threads at once, so the dependent adds read LDS, not memory.
-constexpr int kRedLds = 6144;   // doubles of LDS for one tile's partials
+// Sum the split partials in a launch of its own (plans with many of them): a
+// work-group takes n_slots slots of a tile.  Direct sums (at 2^20 particles and
+// 559 active 380 splits of 256 slots) took 257 us as one work-group a tile.
+constexpr int kRedLds = 6144;   // doubles of LDS
 
-// n_rtiles < 0 (graph replays): the count is read from the table.
-__global__ __launch_bounds__(kWG) void reduce_kernel(const Entry* __restrict__ tab, int n_tab, int64_t n_rtiles) {
+__global__ __launch_bounds__(kWG) void reduce_kernel(const Entry* __restrict__ tab, int n_tab, int n_slots) {
     __shared__ double buf[kRedLds];
-    if (n_rtiles < 0) n_rtiles = tab[0].n_rtiles;
-    for (int64_t g = blockIdx.x; g < n_rtiles; g += gridDim.x) {
-        const int cl = find_entry(tab, n_tab, g, true);
-        const Desc& c = tab[cl].d;
-        const RTile rt = tab[cl].rtiles[g - tab[cl].first_rtile];
-        const int64_t nval = static_cast<int64_t>(rt.nsplit) * rt.n_i * kOut;
-        const double* src = c.partial + rt.pbase * kOut;
-        if (nval <= kRedLds) {
-            __syncthreads();
-            for (int k = threadIdx.x; k < nval; k += kWG) buf[k] = src[k];
-            __syncthreads();
-        }
-        for (int s = threadIdx.x; s < rt.n_i; s += kWG) {
-            const double* p = nval <= kRedLds ? buf : src;
-            double A[kOut];
-#pragma unroll
-            for (int q = 0; q < kOut; ++q) A[q] = p[static_cast<int64_t>(s) * kOut + q];
-            for (int b = 1; b < rt.nsplit; ++b) {
-                const double* pb = p + (static_cast<int64_t>(b) * rt.n_i + s) * kOut;
-#pragma unroll
-                for (int q = 0; q < kOut; ++q) A[q] += pb[q];
-            }
-            write_out(c, rt.act_begin + s, A);
-        }
-    }
+    const int64_t g = blockIdx.x;
+    const int cl = find_entry(tab, n_tab, g, true);
+    const RTile rt = tab[cl].rtiles[g - tab[cl].first_rtile];
+    const int s0 = blockIdx.y * n_slots;
+    if (s0 >= rt.n_i) return;
+    const int slots = rt.n_i - s0 < n_slots ? rt.n_i - s0 : n_slots;
+    const double* src = tab[cl].d.partial + (rt.pbase + s0) * kOut;
+    sum_slots<kRedLds>(tab[cl].d, rt.act_begin + s0, slots * kOut, rt.nsplit, static_cast<int64_t>(rt.n_i) * kOut, buf,
+                       threadIdx.x, [&](int64_t k) { return src[k]; });
 }
 
 // Predict the whole combined memory into the EAGER records.
@@ -1256,17 +1331,6 @@ struct LoopResult {
     int32_t err, below_floor;
 };
 
-template <class V>
-__device__ __forceinline__ V agent_load(const V* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class V>
-__device__ __forceinline__ void agent_store(V* p, V v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// All of the wave's stores so far have reached the scope they were made for.
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 constexpr int kPlanWG = 512;
 constexpr int kPlanWaves = kPlanWG / 64;
 constexpr int kWaveItems = 4;   // items a tile from which on a wave writes them
@@ -1615,12 +1679,12 @@ __device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& 
         const QSum qs{pq ? slot : -1, pq ? T.ni : 0, pq ? static_cast<int32_t>(nsq) : 0};
         for (int32_t u = begin; u < T.ni; u += step) e.qsum[T.tb + u] = QSum{pq ? qs.first + u : -1, qs.stride, qs.nsplit};
         if (pq == 0) {
-            if (begin == 0) it[0] = Item{T.jb, T.je, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
+            if (begin == 0) it[0] = Item{T.jb, T.je, -1, -1, T.tb, ni, static_cast<int16_t>(tl | kSelfTerm)};
             return;
         }
         for (int32_t k = begin; k < static_cast<int32_t>(nsq); k += step) {
             const int64_t b = T.jb + k * pq;
-            it[k] = Item{b, b + pq < T.je ? b + pq : T.je, slot + static_cast<int64_t>(k) * T.ni, T.tb, ni,
+            it[k] = Item{b, b + pq < T.je ? b + pq : T.je, slot + static_cast<int64_t>(k) * T.ni, -1, T.tb, ni,
                          static_cast<int16_t>(k == 0 ? tl | kSelfTerm : tl)};
         }
     };
@@ -1657,7 +1721,6 @@ __device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& 
         o.rtiles = nullptr;   // the corrector sums the splits
         o.first_rtile = 0;
         o.n_items = n_items;
-        o.n_rtiles = 0;
         L->pairs = z.pairs + pairs;
     }
     sum->items = n_items;
@@ -1957,6 +2020,18 @@ struct Timing {
     int64_t pairs = 0;
 };
 
+// Split tiles that the reduce launch sums (none: the items do), and the most
+// slots and splits of one.
+struct Reduce {
+    int64_t n = 0;
+    int32_t most_slots = 0, most_splits = 0;
+    void add(const Reduce& r) {
+        n += r.n;
+        most_slots = std::max(most_slots, r.most_slots);
+        most_splits = std::max(most_splits, r.most_splits);
+    }
+};
+
 // The device side of a device loop over some contexts: its table in device
 // memory with the host's copy (uploaded again when it changes) and the graph
 // of kLoopGraphSteps steps (captured again when the launches change).
@@ -2011,6 +2086,7 @@ struct ht_ctx {
     // last call statistics
     int64_t last_pairs = 0;
     int32_t last_items = 0;
+    Reduce reduce;   // the last plan's sums of split tiles
     Timing tm;
     // per-call scratch: marks for repeated update indices (generation-stamped)
     std::vector<uint32_t> mark;
@@ -2195,6 +2271,12 @@ bool check_vectors(const double* const* ptrs, int count) {
 // context's lists, active set and tuning, so a context gives the same bits
 // alone and in a batched launch.
 
+// Partial slots of a plan up to which the items sum them.  Taking the ticket
+// holds an item's place on the chip for about 2 us and the sum for some more,
+// which a launch of 2300 items of an all-particle step (130 thousand slots)
+// feels more (20 us of 300) than the launch of its own (8 us).
+constexpr int64_t kFoldSlots = 16384;
+
 struct Tile {
     int64_t jb, je;
     int32_t tb, ni;
@@ -2228,7 +2310,7 @@ void tile_table(double gather_cost, int8_t* first_tile) {
     }
 }
 
-int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool place = false) {
+int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool place = false, bool fold = false) {
     auto& items = c->items;
     auto& rtiles = c->rtiles;
     static thread_local std::vector<Tile> tiles;
@@ -2324,14 +2406,15 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
             int64_t ns = attempt > 60 ? 1 : static_cast<int64_t>(std::ceil(t.cost / quantum));
             ns = std::max<int64_t>(1, std::min<int64_t>(ns, rounds));
             if (ns == 1) {
-                items.push_back(Item{t.jb, t.je, -1, t.tb, static_cast<int16_t>(t.ni),
+                items.push_back(Item{t.jb, t.je, -1, -1, t.tb, static_cast<int16_t>(t.ni),
                                      static_cast<int16_t>(t.tl | kSelfTerm | (t.uni ? kUnion : 0))});
                 continue;
             }
             const int64_t per = (rounds + ns - 1) / ns * rsz;   // entries per split, whole rounds
             int32_t nsu = 0;
             for (int64_t b = t.jb; b < t.je; b += per, ++nsu)
-                items.push_back(Item{b, std::min(t.je, b + per), pslots + static_cast<int64_t>(nsu) * t.ni, t.tb,
+                items.push_back(Item{b, std::min(t.je, b + per), pslots + static_cast<int64_t>(nsu) * t.ni,
+                                     static_cast<int32_t>(rtiles.size()), t.tb,
                                      static_cast<int16_t>(t.ni),
                                      static_cast<int16_t>((nsu == 0 ? t.tl | kSelfTerm : t.tl) |
                                                           (t.uni ? kUnion : 0))});
@@ -2341,6 +2424,20 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
         if (static_cast<int64_t>(items.size()) <= c->L.items_max && pslots <= c->L.partial_max) break;
         if (attempt > 60) return fail(HT_ERANGE, "work plan exceeds the context's item capacity");
         quantum *= 2.0;
+    }
+    // The last item of a split tile sums the tile's partials, unless there are
+    // so many that a launch of their own is better (fold: the caller has none).
+    c->reduce = Reduce{};
+    int64_t slots = 0;
+    for (const RTile& r : rtiles) slots += static_cast<int64_t>(r.nsplit) * r.n_i;
+    if (!fold && slots > kFoldSlots) {
+        Reduce& rd = c->reduce;
+        rd.n = static_cast<int64_t>(rtiles.size());
+        for (const RTile& r : rtiles) {
+            rd.most_slots = std::max(rd.most_slots, r.n_i);
+            rd.most_splits = std::max(rd.most_splits, r.nsplit);
+        }
+        for (Item& it : items) it.rtile = -1;
     }
     // Placement (more than one run requested, list items): the items, still in
     // group order, i.e. in space-filling order of their groups, are cut into
@@ -2514,7 +2611,7 @@ int copy_plan(ht_ctx* c, size_t end) {
 
 template <class P>
 int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab, int n_tab, int64_t n_items,
-                 int64_t n_rtiles, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
+                 const Reduce& reduce, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
                  int n_bins = 1, int64_t bin_max = 0, bool uni = false) {
     const int grid = d_bins ? static_cast<int>(n_bins * bin_max) : grid_for(n_items);
     using Kern = void (*)(const Entry*, int, int64_t, const int64_t*, const int64_t*, int);
@@ -2542,8 +2639,12 @@ int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab,
         kern<<<grid, kWG, 0, stream>>>(d_tab, n_tab, n_items, counts, d_bins, n_bins);
         HT_HIP(hipGetLastError());
     }
-    if (n_rtiles > 0) {
-        reduce_kernel<<<grid_for(n_rtiles), kWG, 0, stream>>>(d_tab, n_tab, n_rtiles);
+    if (reduce.n > 0) {
+        // as many slots a work-group as LDS holds the splits of at once, at least four
+        const int fit = kRedLds / (kOut * std::max(reduce.most_splits, 1));
+        const int n_slots = std::min(std::max(fit, 4), kWG);
+        reduce_kernel<<<dim3(static_cast<unsigned>(reduce.n), (reduce.most_slots + n_slots - 1) / n_slots), kWG, 0,
+                        stream>>>(d_tab, n_tab, n_slots);
         HT_HIP(hipGetLastError());
     }
     return HT_OK;
@@ -2639,8 +2740,7 @@ int enqueue_step(ht_ctx* c, const DevRows& u, bool predict_eager, int32_t n_acti
         e.first_item = 0;
         e.first_rtile = 0;
         e.n_items = static_cast<int64_t>(c->items.size());
-        e.n_rtiles = static_cast<int64_t>(c->rtiles.size());
-        std::memcpy(c->plan_host(), &e, sizeof(Entry));
+            std::memcpy(c->plan_host(), &e, sizeof(Entry));
     } else {
         c->last_pairs = 0;
         c->last_items = 0;
@@ -2654,13 +2754,13 @@ int enqueue_step(ht_ctx* c, const DevRows& u, bool predict_eager, int32_t n_acti
     }
     if (n_active == 0) return HT_OK;
     const Entry* d_tab = reinterpret_cast<const Entry*>(c->ws + c->L.off_plan);
-    const int64_t ni = static_cast<int64_t>(c->items.size()), nr = static_cast<int64_t>(c->rtiles.size());
+    const int64_t ni = static_cast<int64_t>(c->items.size());
     const bool eager = c->cfg.predict_mode == HT_PREDICT_EAGER;
     const bool runs = c->list_form == HT_LISTS_RUNS && !direct;
     rc = c->cfg.precision == HT_PREC_FP64
-             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, nr, direct, c->last_pairs, runs,
+             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, direct, c->last_pairs, runs,
                                       d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct)
-             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, nr, direct, c->last_pairs, runs,
+             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, direct, c->last_pairs, runs,
                                        d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct);
     if (rc) return rc;
     // The prep launch is the slot's only reader; marking the slot after the
@@ -3223,11 +3323,10 @@ int launch_correct(int precision, hipStream_t stream, const CorrEntry& e0, const
 constexpr int kGraphForceGrid = 2048;   // fixed force grid of a replay (2 per resident work-group slot)
 constexpr int kGraphCopyBlocks = 256;
 constexpr int kGraphScatterBlocks = 256;
-constexpr int kGraphReduceGrid = 256;
 
 // Capture the step graph of header slot k: prep (plan pulled from the
-// header's slot, update rows written), force and reduce (fixed grids, counts
-// read from the plan).
+// header's slot, update rows written) and force (fixed grid, count read from
+// the plan; the items sum the split tiles).
 template <class P>
 int build_step_graph(ht_ctx* c, int k) {
     if (!c->cap_stream) HT_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
@@ -3246,7 +3345,6 @@ int build_step_graph(ht_ctx* c, int k) {
                                                                              c->ws + c->L.off_rec,
                                                                              kGraphCopyBlocks);
     force_kernel<P, false, false><<<kGraphForceGrid, kWG, 0, s>>>(d_tab, 1, -1, &d_tab->n_items);
-    reduce_kernel<<<kGraphReduceGrid, kWG, 0, s>>>(d_tab, 1, -1);
     const hipError_t launch = hipGetLastError();
     hipGraph_t g = nullptr;
     const hipError_t end = hipStreamEndCapture(s, &g);
@@ -3285,7 +3383,7 @@ int ht_step_graph(ht_ctx* c, int32_t n_upd, const int32_t* d_idx, const double* 
     }
     c->t_pred = t;
     c->predicted = true;
-    rc = plan(c, n_active, ids, false);
+    rc = plan(c, n_active, ids, false, false, true);
     if (rc) return rc;
     rc = c->slot_acquire();
     if (rc) return rc;
@@ -3294,7 +3392,6 @@ int ht_step_graph(ht_ctx* c, int32_t n_upd, const int32_t* d_idx, const double* 
     e.first_item = 0;
     e.first_rtile = 0;
     e.n_items = static_cast<int64_t>(c->items.size());
-    e.n_rtiles = static_cast<int64_t>(c->rtiles.size());
     std::memcpy(c->plan_host(), &e, sizeof(Entry));
     const int k = c->gslot;
     if (!c->gexec[k]) {
@@ -3882,7 +3979,8 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     }
     std::vector<Entry> tab;
     tab.reserve(n_ctx);
-    int64_t n_items = 0, n_rtiles = 0, pairs = 0;
+    int64_t n_items = 0, pairs = 0;
+    Reduce reduce;
     int rc = c0->slot_acquire();
     if (rc) return rc;
     const size_t tab_bytes = static_cast<size_t>(n_ctx) * sizeof(Entry);
@@ -3906,15 +4004,14 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
             if (rc) return rc;
         }
         e.first_item = n_items;
-        e.first_rtile = n_rtiles;
+        e.first_rtile = reduce.n;
         n_items += static_cast<int64_t>(c->items.size());
-        n_rtiles += static_cast<int64_t>(c->rtiles.size());
+        reduce.add(c->reduce);
         pairs += c->last_pairs;
         tab.push_back(e);
     }
     if (tab.empty()) return HT_OK;
     tab[0].n_items = n_items;
-    tab[0].n_rtiles = n_rtiles;
     std::memcpy(c0->plan_host(), tab.data(), tab.size() * sizeof(Entry));
     rc = launch_prep_any(c0->cfg.precision, c0->stream, c0->plan_host(), c0->ws + c0->L.off_plan, end0, nullptr,
                          DevRows{});
@@ -3925,8 +4022,8 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     const int nt = static_cast<int>(tab.size());
     const bool eager = c0->cfg.predict_mode == HT_PREDICT_EAGER;
     if (c0->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, n_rtiles, false, pairs);
-    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, n_rtiles, false, pairs);
+        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, false, pairs);
+    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, false, pairs);
 }
 
 }  // extern "C"
@@ -4244,7 +4341,8 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     char* hs = b->plan_ring.host();
     char* dv = b->ws;
     b->tab.clear();
-    int64_t n_items = 0, n_rtiles = 0, pairs = 0;
+    int64_t n_items = 0, pairs = 0;
+    Reduce reduce;
     size_t at = static_cast<size_t>(n_ctx) * sizeof(Entry);
     for (int32_t k = 0; k < n_ctx; ++k) {
         ht_ctx* c = ctxs[k];
@@ -4255,15 +4353,14 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
         }
         rc = plan(c, n_active[k], ids[k], false);
         if (rc) return rc;
-        if (n_items + static_cast<int64_t>(c->items.size()) > b->max_items ||
-            n_rtiles + static_cast<int64_t>(c->rtiles.size()) > b->max_items)
+        if (n_items + static_cast<int64_t>(c->items.size()) > b->max_items)   // split tiles are fewer
             return fail(HT_ERANGE, "work items over the batch capacity %lld", (long long)b->max_items);
         Entry e{};
         at = pack_plan_into(c, hs, dv, at, n_active[k], ids[k], d_acc[k], d_jerk[k], d_pot[k], e);
         e.first_item = n_items;
-        e.first_rtile = n_rtiles;
+        e.first_rtile = reduce.n;
         n_items += static_cast<int64_t>(c->items.size());
-        n_rtiles += static_cast<int64_t>(c->rtiles.size());
+        reduce.add(c->reduce);
         pairs += c->last_pairs;
         b->tab.push_back(e);
     }
@@ -4276,7 +4373,6 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     }
     if (at > b->plan_bytes) return fail(HT_ERANGE, "batch plan over its capacity");
     b->tab[0].n_items = n_items;
-    b->tab[0].n_rtiles = n_rtiles;
     std::memcpy(hs, b->tab.data(), b->tab.size() * sizeof(Entry));
     rc = launch_prep_any(ctxs[0]->cfg.precision, b->stream, hs, dv, at, nullptr, DevRows{});
     if (rc) return rc;
@@ -4288,8 +4384,8 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     const int nt = static_cast<int>(b->tab.size());
     const bool eager = ctxs[0]->cfg.predict_mode == HT_PREDICT_EAGER;
     if (ctxs[0]->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, n_rtiles, false, pairs);
-    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, n_rtiles, false, pairs);
+        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, false, pairs);
+    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, false, pairs);
 }
 
 }  // namespace
