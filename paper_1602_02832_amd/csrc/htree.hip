@@ -319,8 +319,11 @@ __device__ __forceinline__ void pair_fp64(double xi, double yi, double zi, doubl
 
 // Mixed form: the j-memory stores m, a and jerk in FP32 (the predictor reads
 // them), and s^-1/2 starts from the FP32 reciprocal square root (v_rsq_f32,
-// about one ulp) refined by one Newton step in FP64 in residual form
-// (e = 1 - s y^2, y += y e / 2), which leaves a relative error near 1e-13.
+// about one ulp) refined by one Newton step in FP64, which leaves a relative
+// error near 1e-13.  The step is taken as Y = y (3 - s y^2) = 2 s^-1/2, one
+// multiplication less than in residual form; the sums carry the factors that
+// follow (8 in acc and jerk, 2 in the potential, powers of two and so without
+// rounding) until unscale() takes them out.
 // Everything else is FP64.  The jerk is a sum of terms that can cancel to a
 // few hundredths of their magnitudes; with s^-3/2 and the jerk terms in FP32
 // (a few ulp each) such particles missed the 1e-5 jerk target, so only the
@@ -330,16 +333,15 @@ __device__ __forceinline__ void pair_mixed(double xi, double yi, double zi, doub
                                            int i, const JRec<PrecMixed>& J, double eps2, Acc64& A, int mb) {
     const double dx = J.x - xi, dy = J.y - yi, dz = J.z - zi;
     const double s = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-    const double y0 = static_cast<double>(__builtin_amdgcn_rsqf(static_cast<float>(s)));
-    const double e = fma(-(s * y0), y0, 1.0);
-    double rinv = fma(0.5 * y0, e, y0);
-    if constexpr (SKIP) rinv = (J.idx == i) ? 0.0 : rinv;
-    if constexpr (MASK) rinv = ((J.mask >> mb) & 1) ? rinv : 0.0;
-    const double rinv2 = rinv * rinv;
-    const double mr = J.m * rinv;
-    const double mr3 = mr * rinv2;
+    const double y = static_cast<double>(__builtin_amdgcn_rsqf(static_cast<float>(s)));
+    double Y = y * fma(-(s * y), y, 3.0);
+    if constexpr (SKIP) Y = (J.idx == i) ? 0.0 : Y;
+    if constexpr (MASK) Y = ((J.mask >> mb) & 1) ? Y : 0.0;
+    const double Y2 = Y * Y;
+    const double mr = J.m * Y;
+    const double mr3 = mr * Y2;
     const double wx = J.vx - vxi, wy = J.vy - vyi, wz = J.vz - vzi;
-    const double alpha = 3.0 * fma(dz, wz, fma(dy, wy, dx * wx)) * rinv2;
+    const double alpha = 0.75 * fma(dz, wz, fma(dy, wy, dx * wx)) * Y2;
     A.v[0] = fma(mr3, dx, A.v[0]);
     A.v[1] = fma(mr3, dy, A.v[1]);
     A.v[2] = fma(mr3, dz, A.v[2]);
@@ -356,6 +358,16 @@ __device__ __forceinline__ void pair(double xi, double yi, double zi, double vxi
     else pair_fp64<SKIP, MASK>(xi, yi, zi, vxi, vyi, vzi, i, J, eps2, A, mb);
 }
 
+// The factors that the pairs leave in their sums.
+template <class P>
+__device__ __forceinline__ void unscale(Acc64& A) {
+    if constexpr (P::kMixed) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) A.v[q] *= 0.125;
+        A.v[6] *= 0.5;
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 __device__ __forceinline__ void write_out(const Desc& c, int64_t o, const double* v) {
     c.acc[3 * o + 0] = v[0];
@@ -369,20 +381,31 @@ __device__ __forceinline__ void write_out(const Desc& c, int64_t o, const double
 
 // ------------------------------------------------------------------------------------------------
 // one work item with tile size T
+//
+// A thread of a tile of kWideTile or more sums two i-slots at once, so that
+// every staged entry that it reads from LDS serves two pairs.  With one, a
+// wave's pair reads 56 bytes a lane for 34 VALU instructions, which keeps the
+// LDS busy for three quarters of the time that the four SIMDs take for the
+// arithmetic.  All-particle step of 2^20 particles 12.35 -> 11.85 ms, direct
+// sum of 559 670 -> 640 us, all-particle step of 65536 in FP64 288 -> 280 us.
+constexpr int kWideTile = 128;
+__host__ __device__ constexpr int per_thread(int T) { return T >= kWideTile ? 2 : 1; }
+
 template <class P, bool EAGER, bool DIRECT, bool RUNS, int T, class RL, bool UNI = false>
 __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t run0, LdsAll<P>& lds, RL& rl) {
     constexpr int G = round_mult(T);    // entries gathered per thread and round
     constexpr int R = kRound * G;       // entries per round
-    constexpr int S = kWG / T;          // j-streams
-    constexpr int PER = R / S;          // pairs per thread in a full round (= G T)
+    constexpr int IB = per_thread(T);   // i-slots per thread: islot, islot + TT
+    constexpr int TT = T / IB;          // threads across the tile
+    constexpr int S = kWG / TT;         // j-streams
+    constexpr int PER = R / S;          // entries per thread in a full round
     // The kernel holds nine of these, one for each T, in its loop over items:
     // without this the compiler works out every one's addresses before the loop
     // and keeps them, which takes about 40 VGPRs.
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    const int islot = tid & (T - 1);
-    const int stream = tid / T;
-    const bool has_i = islot < it.n_i;
+    const int islot = tid & (TT - 1);
+    const int stream = tid / TT;
     // List indices of the round about to be gathered, loaded one round ahead so
     // that a round's gather waits on one memory access (the record) instead of
     // two in a row (index, then record); the first round's are loaded beside
@@ -402,17 +425,23 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
     // round's first barrier (run: the run holding the round's first position).
     int64_t run = run0;
     if constexpr (!RUNS) load_idx(it.j_begin);
-    const int i = c.active[it.act_begin + (has_i ? islot : 0)];
-    const int mb = uni ? static_cast<int>(c.act_member[it.act_begin + (has_i ? islot : 0)]) : 0;
-
-    double xi, yi, zi;
-    typename P::Vel vxi, vyi, vzi;
-    typename P::Stored mi;
-    load_state<P, EAGER>(c, i, xi, yi, zi, vxi, vyi, vzi, mi);
-
-    Acc64 A;
+    int i[IB], mb[IB];
+    double xi[IB], yi[IB], zi[IB];
+    typename P::Vel vxi[IB], vyi[IB], vzi[IB];
+    Acc64 A[IB];
 #pragma unroll
-    for (int q = 0; q < kOut; ++q) A.v[q] = 0.0;
+    for (int b = 0; b < IB; ++b) {
+        const int pos = it.act_begin + (islot + b * TT < it.n_i ? islot + b * TT : 0);
+        i[b] = c.active[pos];
+        mb[b] = uni ? static_cast<int>(c.act_member[pos]) : 0;
+    }
+#pragma unroll
+    for (int b = 0; b < IB; ++b) {
+        typename P::Stored mi;
+        load_state<P, EAGER>(c, i[b], xi[b], yi[b], zi[b], vxi[b], vyi[b], vzi[b], mi);
+#pragma unroll
+        for (int q = 0; q < kOut; ++q) A[b].v[q] = 0.0;
+    }
 
     for (int64_t base = it.j_begin; base < it.j_end; base += R) {
         const int64_t rest = it.j_end - base;
@@ -485,14 +514,18 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
         // own list (union tiles)
         auto pairs_of_round = [&](auto sk, auto mkt) {
             constexpr bool SK = decltype(sk)::value, MK = decltype(mkt)::value;
+            constexpr int kUnroll = per_thread(T) == 1 ? 4 : 1;
+            auto entry = [&](const JRec<P>& J) {
+#pragma unroll
+                for (int b = 0; b < IB; ++b)
+                    pair<P, SK, MK>(xi[b], yi[b], zi[b], vxi[b], vyi[b], vzi[b], i[b], J, eps2, A[b], mb[b]);
+            };
             if (cnt == R) {
-#pragma unroll 4
-                for (int u = 0; u < PER; ++u)
-                    pair<P, SK, MK>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[stream + u * S], eps2, A, mb);
+#pragma unroll kUnroll
+                for (int u = 0; u < PER; ++u) entry(lds.j[stream + u * S]);
             } else {
 #pragma unroll 1
-                for (int k = stream; k < cnt; k += S)
-                    pair<P, SK, MK>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[k], eps2, A, mb);
+                for (int k = stream; k < cnt; k += S) entry(lds.j[k]);
             }
         };
         using Yes = std::true_type;
@@ -506,22 +539,9 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
                 else pairs_of_round(Yes{}, No{});
             }
         } else if (c.self_once) {
-            if (cnt == R) {
-#pragma unroll 4
-                for (int u = 0; u < PER; ++u)
-                    pair<P, false>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[stream + u * S], eps2, A);
-            } else {
-#pragma unroll 1
-                for (int k = stream; k < cnt; k += S) pair<P, false>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[k], eps2, A);
-            }
+            pairs_of_round(No{}, No{});
         } else {
-            if (cnt == R) {
-#pragma unroll 4
-                for (int u = 0; u < PER; ++u) pair<P>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[stream + u * S], eps2, A);
-            } else {
-#pragma unroll 1
-                for (int k = stream; k < cnt; k += S) pair<P>(xi, yi, zi, vxi, vyi, vzi, i, lds.j[k], eps2, A);
-            }
+            pairs_of_round(Yes{}, No{});
         }
     }
 
@@ -531,62 +551,77 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
     // 1, i.e. lane offsets 32 down to T), then the four waves in order through
     // LDS.  T >= 64 (at most four streams, whole waves each): a pairwise tree
     // in LDS.
-    if constexpr (T < 64) {
-        auto add = [](double p, double q) { return p + q; };
 #pragma unroll
-        for (int q = 0; q < kOut; ++q) A.v[q] = wave_ops::tree<32, T>(A.v[q], add);
-        const int lane = tid & 63, wave = tid >> 6;
-        __syncthreads();
-        if (lane < T) {
+    for (int b = 0; b < IB; ++b) {
+        if constexpr (TT < 64) {
+            auto add = [](double p, double q) { return p + q; };
 #pragma unroll
-            for (int q = 0; q < kOut; ++q) lds.red[q * kWG + wave * T + lane] = A.v[q];
-        }
-        __syncthreads();
-        if (tid < T) {
-#pragma unroll
-            for (int q = 0; q < kOut; ++q)
-                A.v[q] = ((lds.red[q * kWG + islot] + lds.red[q * kWG + T + islot]) + lds.red[q * kWG + 2 * T + islot]) +
-                         lds.red[q * kWG + 3 * T + islot];
-        }
-    } else if constexpr (S > 1) {
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kOut; ++q) lds.red[q * kWG + tid] = A.v[q];
-#pragma unroll
-        for (int h = S / 2; h >= 1; h /= 2) {
+            for (int q = 0; q < kOut; ++q) A[b].v[q] = wave_ops::tree<32, TT>(A[b].v[q], add);
+            const int lane = tid & 63, wave = tid >> 6;
             __syncthreads();
-            if (stream < h) {
+            if (lane < TT) {
 #pragma unroll
-                for (int q = 0; q < kOut; ++q) lds.red[q * kWG + tid] += lds.red[q * kWG + tid + h * T];
+                for (int q = 0; q < kOut; ++q) lds.red[q * kWG + wave * TT + lane] = A[b].v[q];
+            }
+            __syncthreads();
+            if (tid < TT) {
+#pragma unroll
+                for (int q = 0; q < kOut; ++q)
+                    A[b].v[q] = ((lds.red[q * kWG + islot] + lds.red[q * kWG + TT + islot]) +
+                                 lds.red[q * kWG + 2 * TT + islot]) +
+                                lds.red[q * kWG + 3 * TT + islot];
+            }
+        } else if constexpr (S > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kOut; ++q) lds.red[q * kWG + tid] = A[b].v[q];
+#pragma unroll
+            for (int h = S / 2; h >= 1; h /= 2) {
+                __syncthreads();
+                if (stream < h) {
+#pragma unroll
+                    for (int q = 0; q < kOut; ++q) lds.red[q * kWG + tid] += lds.red[q * kWG + tid + h * TT];
+                }
+            }
+            __syncthreads();
+            if (stream == 0) {
+#pragma unroll
+                for (int q = 0; q < kOut; ++q) A[b].v[q] = lds.red[q * kWG + islot];
             }
         }
-        __syncthreads();
-        if (stream == 0) {
-#pragma unroll
-            for (int q = 0; q < kOut; ++q) A.v[q] = lds.red[q * kWG + islot];
-        }
     }
-    if (stream == 0 && has_i) {
+    if (stream != 0) return;
+#pragma unroll
+    for (int b = 0; b < IB; ++b) {
+        const int slot = islot + b * TT;
+        if (slot >= it.n_i) continue;
         if (c.self_once && (it.tile_log2 & kSelfTerm)) {
             // the self pair's potential term, as the pair loop summed it (same
-            // inputs, same operations; its acc and jerk terms are exact zeros)
+            // inputs, same operations; its acc and jerk terms are exact zeros).
+            // The mass is read again: kept over the pair loops it would cost registers.
+            double x, y, z;
+            typename P::Vel vx, vy, vz;
+            typename P::Stored mi;
+            load_state<P, EAGER>(c, i[b], x, y, z, vx, vy, vz, mi);
             Acc64 Z;
 #pragma unroll
             for (int q = 0; q < kOut; ++q) Z.v[q] = 0.0;
-            pair<P, false>(xi, yi, zi, vxi, vyi, vzi, i,
-                           JRec<P>{xi, yi, zi, vxi, vyi, vzi, static_cast<double>(mi), i, 0}, c.eps2, Z);
-            A.v[6] -= Z.v[6];
+            pair<P, false>(xi[b], yi[b], zi[b], vxi[b], vyi[b], vzi[b], i[b],
+                           JRec<P>{xi[b], yi[b], zi[b], vxi[b], vyi[b], vzi[b], static_cast<double>(mi), i[b], 0},
+                           c.eps2, Z);
+            A[b].v[6] -= Z.v[6];
         }
+        unscale<P>(A[b]);
         if (it.out < 0) {
-            write_out(c, it.act_begin + islot, A.v);
+            write_out(c, it.act_begin + slot, A[b].v);
         } else {
-            double* p = c.partial + (it.out + islot) * kOut;
+            double* p = c.partial + (it.out + slot) * kOut;
             if (it.rtile >= 0) {
 #pragma unroll
-                for (int q = 0; q < kOut; ++q) agent_store(p + q, A.v[q]);
+                for (int q = 0; q < kOut; ++q) agent_store(p + q, A[b].v[q]);
             } else {
 #pragma unroll
-                for (int q = 0; q < kOut; ++q) p[q] = A.v[q];
+                for (int q = 0; q < kOut; ++q) p[q] = A[b].v[q];
             }
         }
     }
@@ -666,9 +701,13 @@ __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g
     return lo;
 }
 
-// Register budget: every form fits 128 VGPRs (4 waves per SIMD) without spilling.
-constexpr int kWavesPerSimd = 4;
-
+// Register budget.  Two i-slots a thread take 164 VGPRs or so: 3 waves per SIMD
+// (4 with spills are 1 to 3% slower).  Plans without a tile of kWideTile or
+// more, most small steps, run a kernel without those cases (WIDE false) in 106
+// VGPRs, 4 waves per SIMD, which hides their gathers better: a step of 559
+// active of 2^20 particles takes 28 us, and 30 us with the line at tiles of 64,
+// which lone crowded groups of such steps reach.  The arithmetic of a tile is
+// the same in both kernels.
 // Work-group g takes items g, g + grid, ...  The grid is normally the item
 // count; graph replays and device loops launch a fixed grid and pass
 // n_items < 0, and the count is read from counts[0] (the items of the whole
@@ -682,8 +721,8 @@ constexpr int kWavesPerSimd = 4;
 // turn, so each run stays on one XCD and its L2.
 // UNI: the plan holds union-tile items (a separate instantiation, so that the
 // plain kernel keeps its register budget).
-template <class P, bool EAGER, bool DIRECT, bool RUNS = false, bool UNI = false>
-__global__ __launch_bounds__(kWG, kWavesPerSimd) void force_kernel(const Entry* __restrict__ tab,
+template <class P, bool EAGER, bool DIRECT, bool WIDE = true, bool RUNS = false, bool UNI = false>
+__global__ __launch_bounds__(kWG, (WIDE ? 3 : 4)) void force_kernel(const Entry* __restrict__ tab,
                                                                                    int n_tab, int64_t n_items,
                                                                                    const int64_t* counts,
                                                                                    const int64_t* bins = nullptr,
@@ -704,16 +743,29 @@ __global__ __launch_bounds__(kWG, kWavesPerSimd) void force_kernel(const Entry* 
         const int64_t k = g - tab[cl].first_item;
         const Item it = tab[cl].items[k];
         const int64_t r0 = RUNS ? c.item_runs[k] : 0;
-        switch (it.tile_log2 & kTileMask) {
-            case 8: run_item<P, EAGER, DIRECT, RUNS, 256, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 7: run_item<P, EAGER, DIRECT, RUNS, 128, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 6: run_item<P, EAGER, DIRECT, RUNS, 64, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 5: run_item<P, EAGER, DIRECT, RUNS, 32, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 4: run_item<P, EAGER, DIRECT, RUNS, 16, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 3: run_item<P, EAGER, DIRECT, RUNS, 8, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 2: run_item<P, EAGER, DIRECT, RUNS, 4, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            case 1: run_item<P, EAGER, DIRECT, RUNS, 2, decltype(rl), UNI>(c, it, r0, lds, rl); break;
-            default: run_item<P, EAGER, DIRECT, RUNS, 1, decltype(rl), UNI>(c, it, r0, lds, rl); break;
+        auto item_of = [&](auto tile) {
+            run_item<P, EAGER, DIRECT, RUNS, decltype(tile)::value, decltype(rl), UNI>(c, it, r0, lds, rl);
+        };
+        const int tl = it.tile_log2 & kTileMask;
+        bool wide = false;
+        if constexpr (WIDE) {
+            wide = true;
+            switch (tl) {
+                case 8: item_of(std::integral_constant<int, 256>{}); break;
+                case 7: item_of(std::integral_constant<int, 128>{}); break;
+                default: wide = false; break;
+            }
+        }
+        if (!wide) {
+            switch (tl) {
+                case 6: item_of(std::integral_constant<int, 64>{}); break;
+                case 5: item_of(std::integral_constant<int, 32>{}); break;
+                case 4: item_of(std::integral_constant<int, 16>{}); break;
+                case 3: item_of(std::integral_constant<int, 8>{}); break;
+                case 2: item_of(std::integral_constant<int, 4>{}); break;
+                case 1: item_of(std::integral_constant<int, 2>{}); break;
+                default: item_of(std::integral_constant<int, 1>{}); break;
+            }
         }
         {   // the item is read again, so that nothing of it stays in registers over the pair loops
             int64_t h = g;
@@ -2086,7 +2138,8 @@ struct ht_ctx {
     // last call statistics
     int64_t last_pairs = 0;
     int32_t last_items = 0;
-    Reduce reduce;   // the last plan's sums of split tiles
+    Reduce reduce;       // the last plan's sums of split tiles
+    bool wide = false;   // it holds a tile of kWideTile or more
     Timing tm;
     // per-call scratch: marks for repeated update indices (generation-stamped)
     std::vector<uint32_t> mark;
@@ -2427,6 +2480,8 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
     }
     // The last item of a split tile sums the tile's partials, unless there are
     // so many that a launch of their own is better (fold: the caller has none).
+    c->wide = false;
+    for (const Tile& t : tiles) c->wide |= (1 << t.tl) >= kWideTile;
     c->reduce = Reduce{};
     int64_t slots = 0;
     for (const RTile& r : rtiles) slots += static_cast<int64_t>(r.nsplit) * r.n_i;
@@ -2611,15 +2666,17 @@ int copy_plan(ht_ctx* c, size_t end) {
 
 template <class P>
 int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab, int n_tab, int64_t n_items,
-                 const Reduce& reduce, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
+                 const Reduce& reduce, bool wide, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
                  int n_bins = 1, int64_t bin_max = 0, bool uni = false) {
     const int grid = d_bins ? static_cast<int>(n_bins * bin_max) : grid_for(n_items);
     using Kern = void (*)(const Entry*, int, int64_t, const int64_t*, const int64_t*, int);
     Kern kern;
-    if (direct) kern = eager ? force_kernel<P, true, true> : force_kernel<P, false, true>;
-    else if (runs) kern = force_kernel<P, false, false, true>;
-    else if (uni) kern = force_kernel<P, false, false, false, true>;
-    else kern = eager ? force_kernel<P, true, false> : force_kernel<P, false, false>;
+    if (runs) kern = force_kernel<P, false, false, true, true>;
+    else if (uni) kern = force_kernel<P, false, false, true, false, true>;
+    else if (wide) kern = direct ? (eager ? force_kernel<P, true, true> : force_kernel<P, false, true>)
+                                 : (eager ? force_kernel<P, true, false> : force_kernel<P, false, false>);
+    else kern = direct ? (eager ? force_kernel<P, true, true, false> : force_kernel<P, false, true, false>)
+                       : (eager ? force_kernel<P, true, false, false> : force_kernel<P, false, false, false>);
     const int64_t* counts = nullptr;
     if (tm.enabled) {
         // Timing: the extended launch stamps the two events with the kernel's
@@ -2758,9 +2815,9 @@ int enqueue_step(ht_ctx* c, const DevRows& u, bool predict_eager, int32_t n_acti
     const bool eager = c->cfg.predict_mode == HT_PREDICT_EAGER;
     const bool runs = c->list_form == HT_LISTS_RUNS && !direct;
     rc = c->cfg.precision == HT_PREC_FP64
-             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, direct, c->last_pairs, runs,
+             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, c->wide, direct, c->last_pairs, runs,
                                       d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct)
-             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, direct, c->last_pairs, runs,
+             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, c->wide, direct, c->last_pairs, runs,
                                        d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct);
     if (rc) return rc;
     // The prep launch is the slot's only reader; marking the slot after the
@@ -3981,6 +4038,7 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     tab.reserve(n_ctx);
     int64_t n_items = 0, pairs = 0;
     Reduce reduce;
+    bool wide = false;
     int rc = c0->slot_acquire();
     if (rc) return rc;
     const size_t tab_bytes = static_cast<size_t>(n_ctx) * sizeof(Entry);
@@ -4007,6 +4065,7 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
         e.first_rtile = reduce.n;
         n_items += static_cast<int64_t>(c->items.size());
         reduce.add(c->reduce);
+        wide |= c->wide;
         pairs += c->last_pairs;
         tab.push_back(e);
     }
@@ -4022,8 +4081,8 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     const int nt = static_cast<int>(tab.size());
     const bool eager = c0->cfg.predict_mode == HT_PREDICT_EAGER;
     if (c0->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, false, pairs);
-    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, false, pairs);
+        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
+    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
 }
 
 }  // extern "C"
@@ -4343,6 +4402,7 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     b->tab.clear();
     int64_t n_items = 0, pairs = 0;
     Reduce reduce;
+    bool wide = false;
     size_t at = static_cast<size_t>(n_ctx) * sizeof(Entry);
     for (int32_t k = 0; k < n_ctx; ++k) {
         ht_ctx* c = ctxs[k];
@@ -4361,6 +4421,7 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
         e.first_rtile = reduce.n;
         n_items += static_cast<int64_t>(c->items.size());
         reduce.add(c->reduce);
+        wide |= c->wide;
         pairs += c->last_pairs;
         b->tab.push_back(e);
     }
@@ -4384,8 +4445,8 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     const int nt = static_cast<int>(b->tab.size());
     const bool eager = ctxs[0]->cfg.predict_mode == HT_PREDICT_EAGER;
     if (ctxs[0]->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, false, pairs);
-    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, false, pairs);
+        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
+    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
 }
 
 }  // namespace
@@ -4849,6 +4910,7 @@ __global__ __launch_bounds__(kWG) void noalloc_direct_kernel(int32_t n, const do
         for (int k = 0; k < cnt; ++k) pair<P>(xi, yi, zi, vxi, vyi, vzi, i, tile[k], eps2, A);
     }
     if (!has_q) return;
+    unscale<P>(A);
     if (!ok) {
 #pragma unroll
         for (int k = 0; k < kOut; ++k) A.v[k] = __builtin_nan("");
