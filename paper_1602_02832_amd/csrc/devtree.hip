@@ -26,6 +26,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -33,7 +34,6 @@
 #include <string>
 
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_scan.hpp>
 
 namespace {
 
@@ -72,15 +72,82 @@ struct Cell {
 };
 static_assert(sizeof(Cell) == 32, "cell record");
 
-struct Totals {           // written by the device after the prefix sums
+struct Totals {
     int32_t cells, nodes, groups, pad;
 };
+
+struct Caps {             // what the arrays of cells and nodes hold
+    int64_t cells, nodes;
+};
+__device__ inline bool fits(const Totals* t, const Caps& c) { return t->cells <= c.cells && t->nodes <= c.nodes; }
 
 struct Counters {         // list phase
     unsigned long long staged;   // entries reserved in the staging array
     int32_t max_cut;             // most opened cells that did not fit a work-group's scratch
     int32_t pad;
 };
+
+struct Root {
+    double lo[3];
+    double side;
+    double scale;    // 2^21 / side
+};
+
+// A build's small state on the device: the tickets of the launches whose last
+// work-group finishes their sums, and when each phase began.
+constexpr int kStamps = 6;
+struct Progress {
+    Root root;
+    Totals tot;
+    Counters ctr;
+    uint64_t stamp[kStamps];
+    uint32_t bbox_done, counts_done, offsets_done, pad;
+};
+// What the host reads at the end of it (pinned memory).
+struct Outcome {
+    Root root;
+    Totals tot;
+    Counters ctr;
+    uint64_t stamp[kStamps];
+};
+
+// True, in every thread, in the last of n_wgs work-groups to get here; what
+// the others stored with agent-scope stores before can then be read with
+// agent-scope loads.  The ticket is 0 again after the last one.
+__device__ inline bool last_here(uint32_t* ticket, uint32_t n_wgs) {
+    __shared__ uint32_t s_ticket;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's stores are where every XCD sees them
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool last = s_ticket == n_wgs - 1;
+    if (last && threadIdx.x == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    return last;
+}
+template <class V>
+__device__ inline void put_agent(V* p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class V>
+__device__ inline V get_agent(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Exclusive prefix sum over a work-group of WG threads, and its total.
+template <int WG, class V>
+__device__ inline V scan_group(V x, V* total) {
+    __shared__ V s_wave[WG / 64];
+    const V in = wave_ops::scan_inclusive(x);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 63) s_wave[wave] = in;
+    __syncthreads();
+    V before = 0, sum = 0;
+    for (int w = 0; w < WG / 64; ++w) {
+        if (w == wave) before = sum;
+        sum += s_wave[w];
+    }
+    __syncthreads();   // s_wave may be written again
+    *total = sum;
+    return before + in - x;
+}
 
 // ---------------------------------------------------------------- keys
 __device__ inline uint64_t spread3(uint32_t v) {
@@ -130,72 +197,60 @@ __device__ inline uint64_t ph_key(uint32_t x, uint32_t y, uint32_t z) {
 __device__ inline double dmin(double a, double b) { return b < a ? b : a; }
 __device__ inline double dmax(double a, double b) { return a < b ? b : a; }
 
-// Per-block componentwise min and max of x (exact in any order).
-__global__ __launch_bounds__(kWG) void bbox_partial_kernel(int64_t n, const double* __restrict__ x,
-                                                           double* __restrict__ part) {
+// Componentwise min and max over a work-group (exact in any order), in thread 0.
+template <int WG>
+__device__ inline void box_of_group(double* lo, double* hi) {
+    __shared__ double s_box[6][WG / 64];
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = wave_ops::tree<32, 1>(lo[d], [](double p, double q) { return dmin(p, q); });
+        hi[d] = wave_ops::tree<32, 1>(hi[d], [](double p, double q) { return dmax(p, q); });
+    }
+    if ((threadIdx.x & 63) == 0)
+        for (int d = 0; d < 3; ++d) {
+            s_box[d][threadIdx.x >> 6] = lo[d];
+            s_box[3 + d][threadIdx.x >> 6] = hi[d];
+        }
+    __syncthreads();
+    for (int d = 0; d < 3; ++d) {
+        lo[d] = s_box[d][0];
+        hi[d] = s_box[3 + d][0];
+        for (int w = 1; w < WG / 64; ++w) {
+            lo[d] = dmin(lo[d], s_box[d][w]);
+            hi[d] = dmax(hi[d], s_box[3 + d][w]);
+        }
+    }
+    __syncthreads();
+}
+
+// The root cube: side is the smallest power of two above the largest extent (1
+// when all particles coincide).  Every work-group's box goes to part; the last
+// one to be done reduces them.
+constexpr int kBoxWGs = 512;   // at most: 12 ns a ticket
+__global__ __launch_bounds__(kWG) void bbox_kernel(int64_t n, const double* __restrict__ x, double* part,
+                                                   Progress* pr) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) pr->stamp[0] = wall_clock64();
     double lo[3], hi[3];
     for (int d = 0; d < 3; ++d) lo[d] = hi[d] = x[d];
+#pragma unroll 4
     for (int64_t i = blockIdx.x * int64_t(kWG) + threadIdx.x; i < n; i += int64_t(gridDim.x) * kWG)
         for (int d = 0; d < 3; ++d) {
             lo[d] = dmin(lo[d], x[3 * i + d]);
             hi[d] = dmax(hi[d], x[3 * i + d]);
         }
-    __shared__ double s[6][kWG];
-    for (int d = 0; d < 3; ++d) {
-        s[d][threadIdx.x] = lo[d];
-        s[3 + d][threadIdx.x] = hi[d];
-    }
-    __syncthreads();
-    for (int w = kWG / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-            for (int d = 0; d < 3; ++d) {
-                s[d][threadIdx.x] = dmin(s[d][threadIdx.x], s[d][threadIdx.x + w]);
-                s[3 + d][threadIdx.x] = dmax(s[3 + d][threadIdx.x], s[3 + d][threadIdx.x + w]);
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x < 6) part[6 * blockIdx.x + threadIdx.x] = s[threadIdx.x][0];
-}
-
-struct Root {
-    double lo[3];
-    double side;
-    double scale;    // 2^21 / side
-};
-
-// Final reduction and the root cube: side is the smallest power of two above
-// the largest extent (1 when all particles coincide).
-__global__ __launch_bounds__(kWG) void bbox_final_kernel(int nb, const double* __restrict__ part, Root* root) {
-    __shared__ double s[6][kWG];
-    const int t = threadIdx.x;
-    double lo[3], hi[3];
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = part[d];
-        hi[d] = part[3 + d];
-    }
-    for (int b = t; b < nb; b += kWG)
+    box_of_group<kWG>(lo, hi);
+    if (threadIdx.x == 0)
         for (int d = 0; d < 3; ++d) {
-            lo[d] = dmin(lo[d], part[6 * b + d]);
-            hi[d] = dmax(hi[d], part[6 * b + 3 + d]);
+            put_agent(part + 6 * blockIdx.x + d, lo[d]);
+            put_agent(part + 6 * blockIdx.x + 3 + d, hi[d]);
         }
-    for (int d = 0; d < 3; ++d) {
-        s[d][t] = lo[d];
-        s[3 + d][t] = hi[d];
-    }
-    __syncthreads();
-    for (int w = kWG / 2; w > 0; w >>= 1) {
-        if (t < w)
-            for (int d = 0; d < 3; ++d) {
-                s[d][t] = dmin(s[d][t], s[d][t + w]);
-                s[3 + d][t] = dmax(s[3 + d][t], s[3 + d][t + w]);
-            }
-        __syncthreads();
-    }
-    if (t != 0) return;
-    for (int d = 0; d < 3; ++d) {
-        lo[d] = s[d][0];
-        hi[d] = s[3 + d][0];
-    }
+    if (!last_here(&pr->bbox_done, gridDim.x)) return;
+    for (uint32_t b = threadIdx.x; b < gridDim.x; b += kWG)
+        for (int d = 0; d < 3; ++d) {
+            lo[d] = dmin(lo[d], get_agent(part + 6 * b + d));
+            hi[d] = dmax(hi[d], get_agent(part + 6 * b + 3 + d));
+        }
+    box_of_group<kWG>(lo, hi);
+    if (threadIdx.x != 0) return;
     const double ext = dmax(dmax(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]);
     double side = 1.0;
     if (ext > 0.0) {
@@ -203,15 +258,16 @@ __global__ __launch_bounds__(kWG) void bbox_final_kernel(int nb, const double* _
         frexp(ext, &e);
         side = ldexp(1.0, e);
     }
-    for (int d = 0; d < 3; ++d) root->lo[d] = lo[d];
-    root->side = side;
-    root->scale = ldexp(1.0, kAxisBits) / side;
+    for (int d = 0; d < 3; ++d) pr->root.lo[d] = lo[d];
+    pr->root.side = side;
+    pr->root.scale = ldexp(1.0, kAxisBits) / side;
 }
 
-__global__ __launch_bounds__(kWG) void keys_kernel(int64_t n, const double* __restrict__ x, const Root* root,
+__global__ __launch_bounds__(kWG) void keys_kernel(int64_t n, const double* __restrict__ x, Progress* pr,
                                                    uint64_t* __restrict__ key, int32_t* __restrict__ idx) {
     const int64_t i = blockIdx.x * int64_t(kWG) + threadIdx.x;
     if (i >= n) return;
+    const Root* root = &pr->root;
     const double qmax = ldexp(1.0, kAxisBits) - 1.0;
     uint32_t q[3];
     for (int d = 0; d < 3; ++d) {
@@ -221,35 +277,10 @@ __global__ __launch_bounds__(kWG) void keys_kernel(int64_t n, const double* __re
     }
     key[i] = ph_key(q[0], q[1], q[2]);
     idx[i] = static_cast<int32_t>(i);
-}
-
-// Particle state in key order, and L_k.
-__global__ __launch_bounds__(kWG) void gather_kernel(int64_t n, const int32_t* __restrict__ perm32,
-                                                     const uint64_t* __restrict__ key, const double* __restrict__ x,
-                                                     const double* __restrict__ v, const double* __restrict__ a,
-                                                     const double* __restrict__ j, const double* __restrict__ m,
-                                                     int64_t* __restrict__ perm, double* __restrict__ sx,
-                                                     double* __restrict__ sv, double* __restrict__ sa,
-                                                     double* __restrict__ sj, double* __restrict__ sm,
-                                                     int8_t* __restrict__ lev) {
-    const int64_t k = blockIdx.x * int64_t(kWG) + threadIdx.x;
-    if (k >= n) return;
-    const int64_t o = perm32[k];
-    perm[k] = o;
-    sm[k] = m[o];
-    for (int d = 0; d < 3; ++d) {
-        sx[3 * k + d] = x[3 * o + d];
-        sv[3 * k + d] = v[3 * o + d];
-        sa[3 * k + d] = a[3 * o + d];
-        sj[3 * k + d] = j[3 * o + d];
+    if (i == n - 1) {
+        pr->ctr = Counters{0, 0, 0};
+        pr->stamp[1] = wall_clock64();   // the sort follows
     }
-    int L = 0;
-    if (k > 0) {
-        const uint64_t diff = key[k] ^ key[k - 1];
-        // digit i (0-based from the top) holds bits 60-3i .. 62-3i; the keys part at level i+1
-        L = diff == 0 ? kNoCellLevel : kDeepest - (63 - __clzll(diff)) / 3;
-    }
-    lev[k] = static_cast<int8_t>(L);
 }
 
 __device__ inline uint64_t level_mask(int level) {
@@ -257,125 +288,187 @@ __device__ inline uint64_t level_mask(int level) {
     return sh >= 63 ? 0ull : (~0ull << sh);
 }
 
-// [b, e): the particles whose key shares key's first `level` digits.
-__device__ inline void prefix_range(const uint64_t* __restrict__ key, int64_t n, uint64_t k, int level, int64_t* b,
-                                    int64_t* e) {
-    const uint64_t mask = level_mask(level);
-    const uint64_t lo = k & mask, hi = lo | (~mask & 0x7fffffffffffffffull);
-    int64_t l = 0, r = n;   // first key >= lo
-    while (l < r) {
-        const int64_t mid = (l + r) >> 1;
-        if (key[mid] < lo) l = mid + 1; else r = mid;
-    }
-    *b = l;
-    r = n;                  // first key > hi
-    while (l < r) {
-        const int64_t mid = (l + r) >> 1;
-        if (key[mid] <= hi) l = mid + 1; else r = mid;
-    }
-    *e = l;
+// The first level at which two keys of the sorted order part, the least of the
+// levels at which neighbours part between them.
+__device__ inline int parting(uint64_t a, uint64_t b) {
+    const uint64_t diff = a ^ b;
+    // digit i (0-based from the top) holds bits 60-3i .. 62-3i; the keys part at level i+1
+    return diff == 0 ? kNoCellLevel : kDeepest - (63 - __clzll(diff)) / 3;
 }
 
-__device__ inline int64_t prefix_end(const uint64_t* __restrict__ key, int64_t n, int64_t from, uint64_t k,
-                                     int level) {
-    const uint64_t hi = (k & level_mask(level)) | (~level_mask(level) & 0x7fffffffffffffffull);
-    int64_t l = from, r = n;
+// How many of 0 ... top - 1 are `in`; those that are come first, and the first
+// `have` are known to be.  Steps outwards from the near end in growing strides
+// and narrows the bracket then, several accesses at a time, since each round
+// waits for the last: most cells are small, and what is looked at lies near
+// together.
+template <class In>
+__device__ inline int64_t extent(int64_t have, int64_t top, In in) {
+    int64_t l = have, r = top;   // l are in, at most r are
+    for (int64_t step = max(have, int64_t(1)); l < r; step *= 16) {
+        int64_t p[4];
+        bool ok[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            p[j] = min(l + step * ((2 << j) - 1), r);
+            ok[j] = in(p[j] - 1);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (ok[j]) l = p[j];
+            else r = min(r, p[j] - 1);
+        }
+        if (!ok[3]) break;
+    }
     while (l < r) {
-        const int64_t mid = (l + r) >> 1;
-        if (key[mid] <= hi) l = mid + 1; else r = mid;
+        const int64_t w = (r - l + 7) / 8, l0 = l, r0 = r;
+        bool ok[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) ok[j] = in(min(l0 + (j + 1) * w, r0) - 1);
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const int64_t p = min(l0 + (j + 1) * w, r0);
+            if (ok[j]) l = p;
+            else r = min(r, p - 1);
+        }
     }
     return l;
 }
 
-// Whether cells begin at k, and their deepest level.
-__device__ inline bool cells_at(const uint64_t* __restrict__ key, const int8_t* __restrict__ lev, int64_t n,
-                                int n_leaf, int64_t k, int* Lk, int* Ek) {
-    const int L = lev[k];
-    if (L > kDeepest) return false;
-    if (k > 0 && n_leaf > 1) {   // the parent cell must hold more than n_leaf particles
-        int64_t b, e;
-        prefix_range(key, n, key[k], L - 1, &b, &e);
-        if (e - b <= n_leaf) return false;
-    }
-    int mk = kNoCellLevel;   // min L over the next n_leaf particles; 0 when they run out
-    if (k + n_leaf >= n) {
-        mk = 0;
-    } else {
-        for (int i = 1; i <= n_leaf; ++i) mk = min(mk, static_cast<int>(lev[k + i]));
-    }
-    *Lk = L;
-    *Ek = max(L, min(kDeepest, mk));
-    return true;
-}
+// Counts over the kScanWG particles of a work-group, in one word: cells in the
+// low 16 bits, nodes in the next 16, groups in the 16 above.  A particle's word
+// holds the sums over the particles before it in the work-group, and above
+// them its level L_k (6 bits), its cells (6) and whether a group begins (1).
+constexpr int kScanWG = 512;
+static_assert(kScanWG * (kDeepest + 1) < 1 << 16, "the counts of a work-group fit their fields");
+__device__ inline int32_t cells_in(uint64_t w) { return static_cast<int32_t>(w & 0xffff); }
+__device__ inline int32_t nodes_in(uint64_t w) { return static_cast<int32_t>((w >> 16) & 0xffff); }
+__device__ inline int32_t groups_in(uint64_t w) { return static_cast<int32_t>((w >> 32) & 0xffff); }
 
-// Per particle: cells, nodes and the group that begin there.
-__global__ __launch_bounds__(kWG) void count_kernel(int64_t n, int n_leaf, int n_crit,
-                                                    const uint64_t* __restrict__ key, const int8_t* __restrict__ lev,
-                                                    int32_t* __restrict__ n_cells, int32_t* __restrict__ n_nodes,
-                                                    int32_t* __restrict__ gflag) {
-    const int64_t k = blockIdx.x * int64_t(kWG) + threadIdx.x;
-    if (k >= n) return;
-    int L, E;
-    int32_t nc = 0, nn = 0, g = 0;
-    if (cells_at(key, lev, n, n_leaf, k, &L, &E)) {
-        nc = E - L + 1;
-        if (k + 1 < n) nn = max(0, min(E, static_cast<int>(lev[k + 1]) - 1) - L + 1);
-        if (k == 0) {
-            g = 1;
-        } else {   // a group starts here unless the enclosing cell already qualifies
-            int64_t b, e;
-            prefix_range(key, n, key[k], L - 1, &b, &e);
-            g = (e - b > n_crit) ? 1 : 0;
+// Particle state in key order; the cells, nodes and the group that begin at
+// each particle, their sums over the particles before it in the work-group,
+// and (by the last work-group to be done) the sums before every work-group.
+// The gather of 104 bytes a particle from random places bounds it, and hides
+// the counting.  At 2^20 particles 135 us; a gather, a count that searched all
+// n keys for the cell above, three scans and a kernel for their totals took
+// 210 us.
+__global__ __launch_bounds__(kScanWG) void particles_kernel(
+    int64_t n, int n_leaf, int n_crit, const int32_t* __restrict__ perm32, const uint64_t* __restrict__ key,
+    const double* __restrict__ x, const double* __restrict__ v, const double* __restrict__ a,
+    const double* __restrict__ j, const double* __restrict__ m, int64_t* __restrict__ perm, double* __restrict__ sx,
+    double* __restrict__ sv, double* __restrict__ sa, double* __restrict__ sj, double* __restrict__ sm,
+    uint64_t* __restrict__ word, uint64_t* part, Totals* __restrict__ base, Progress* pr, Outcome* out) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) pr->stamp[2] = wall_clock64();
+    const int64_t k = blockIdx.x * int64_t(kScanWG) + threadIdx.x;
+    int L = 0;
+    uint64_t count = 0, rest = 0;
+    if (k < n) {
+        const int64_t o = perm32[k];
+        const uint64_t mine = key[k];
+        if (k > 0) L = parting(mine, key[k - 1]);
+        bool begins = L <= kDeepest, group = k == 0;
+        if (begins && k > 0) {
+            // the cell above: its particles from here on and before, as far as the answers need them
+            const uint64_t mask = level_mask(L - 1), lo = mine & mask, hi = lo | (~mask & 0x7fffffffffffffffull);
+            const int64_t far = max(int64_t(n_leaf), int64_t(n_crit)) + 1;
+            int64_t above = extent(1, min(n - k, far), [&](int64_t i) { return key[k + i] <= hi; });
+            if (above < far) above += extent(1, min(k, far), [&](int64_t i) { return key[k - 1 - i] >= lo; });
+            begins = above > n_leaf;   // no cells in a leaf of up to n_leaf particles
+            group = above > n_crit;    // no groups in a cell that is one, or in one
+        }
+        if (begins) {
+            // levels L ... E: down to the last with more than n_leaf particles, and their children
+            const int E = max(L, k + n_leaf >= n ? 0 : min(kDeepest, parting(mine, key[k + n_leaf])));
+            const int nodes = k + 1 < n ? max(0, min(E, parting(mine, key[k + 1]) - 1) - L + 1) : 0;
+            const uint64_t cells = E - L + 1;
+            count = cells | static_cast<uint64_t>(nodes) << 16 | static_cast<uint64_t>(group) << 32;
+            rest = static_cast<uint64_t>(L) << 48 | cells << 54 | static_cast<uint64_t>(group) << 60;
+        }
+        perm[k] = o;
+        sm[k] = m[o];
+        for (int d = 0; d < 3; ++d) {
+            sx[3 * k + d] = x[3 * o + d];
+            sv[3 * k + d] = v[3 * o + d];
+            sa[3 * k + d] = a[3 * o + d];
+            sj[3 * k + d] = j[3 * o + d];
         }
     }
-    n_cells[k] = nc;
-    n_nodes[k] = nn;
-    gflag[k] = g;
+    uint64_t sum;
+    const uint64_t before = scan_group<kScanWG>(count, &sum);
+    if (k < n) word[k] = before | rest;
+    if (threadIdx.x == 0) put_agent(part + blockIdx.x, sum);
+    if (!last_here(&pr->counts_done, gridDim.x)) return;
+    int32_t at[3] = {0, 0, 0};
+    for (uint32_t w = 0; w < gridDim.x; w += kScanWG) {
+        const uint32_t i = w + threadIdx.x;
+        const uint64_t c = i < gridDim.x ? get_agent(part + i) : 0;
+        const int32_t here[3] = {cells_in(c), nodes_in(c), groups_in(c)};
+        int32_t off[3];
+        for (int q = 0; q < 3; ++q) {
+            int32_t all;
+            off[q] = at[q] + scan_group<kScanWG>(here[q], &all);
+            at[q] += all;
+        }
+        if (i < gridDim.x) base[i] = Totals{off[0], off[1], off[2], 0};
+    }
+    if (threadIdx.x == 0) {
+        const Totals tot{at[0], at[1], at[2], 0};
+        pr->tot = tot;
+        out->tot = tot;
+        out->root = pr->root;
+    }
 }
 
-__global__ void totals_kernel(int64_t n, const int32_t* __restrict__ n_cells, const int32_t* __restrict__ cbase,
-                              const int32_t* __restrict__ n_nodes, const int32_t* __restrict__ nbase,
-                              const int32_t* __restrict__ gflag, const int32_t* __restrict__ gbase, Totals* t) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    t->cells = cbase[n - 1] + n_cells[n - 1];
-    t->nodes = nbase[n - 1] + n_nodes[n - 1];
-    t->groups = gbase[n - 1] + gflag[n - 1];
-    t->pad = 0;
-}
-
+// The cells and nodes that begin at each particle, from the deepest up: a
+// cell's end lies past the one below it, at most a few doublings of its size
+// away.  At 2^20 and 20011 particles 100 and 15 us with a search of all keys
+// for every cell.
+constexpr int kTile = 4 * kWG;
 __global__ __launch_bounds__(kWG) void cells_kernel(int64_t n, int n_leaf, const uint64_t* __restrict__ key,
-                                                    const int8_t* __restrict__ lev,
-                                                    const int32_t* __restrict__ cbase,
-                                                    const int32_t* __restrict__ nbase,
-                                                    const int32_t* __restrict__ gflag,
-                                                    const int32_t* __restrict__ gbase, const Totals* tot,
+                                                    const uint64_t* __restrict__ word,
+                                                    const Totals* __restrict__ base, Caps caps, const Progress* pr,
                                                     Cell* __restrict__ cell, int32_t* __restrict__ node_level,
                                                     int64_t* __restrict__ node_begin, int64_t* __restrict__ node_end,
                                                     int32_t* __restrict__ node_cell, int64_t* __restrict__ group_first) {
-    const int64_t k = blockIdx.x * int64_t(kWG) + threadIdx.x;
-    if (k == 0) group_first[tot->groups] = n;
-    if (k >= n) return;
-    int L, E;
-    if (!cells_at(key, lev, n, n_leaf, k, &L, &E)) return;
-    if (gflag[k]) group_first[gbase[k]] = k;
-    const int32_t total = tot->cells;
-    for (int l = L; l <= E; ++l) {
-        const int64_t e = prefix_end(key, n, k, key[k], l);
-        const int64_t cnt = e - k;
+    __shared__ uint64_t s_key[kTile], s_word[kTile];
+    const int64_t first = blockIdx.x * int64_t(kWG), k = first + threadIdx.x;
+    const int64_t ahead = min(int64_t(kTile), n - first);
+    for (int64_t i = threadIdx.x; i < ahead; i += kWG) {
+        s_key[i] = key[first + i];
+        s_word[i] = word[first + i];
+    }
+    __syncthreads();
+    if (k >= n || !fits(&pr->tot, caps)) return;
+    if (k == 0) group_first[pr->tot.groups] = n;
+    const uint64_t w = s_word[threadIdx.x];
+    const int cells = static_cast<int>((w >> 54) & 63), L = static_cast<int>((w >> 48) & 63);
+    if (cells == 0) return;
+    const Totals b = base[k / kScanWG];
+    if ((w >> 60) & 1) group_first[b.groups + groups_in(w)] = k;
+    const int32_t c0 = b.cells + cells_in(w), q0 = b.nodes + nodes_in(w);
+    const uint64_t mine = s_key[threadIdx.x];
+    const int64_t near = ahead - threadIdx.x;
+    int64_t cnt = 1;
+    for (int l = L + cells - 1; l >= L; --l) {
+        const uint64_t hi = mine | ~(level_mask(l) | ~0x7fffffffffffffffull);
+        if (l == 0) cnt = n - k;
+        else if (cnt < near) cnt = extent(cnt, near, [&](int64_t i) { return s_key[threadIdx.x + i] <= hi; });
+        if (cnt >= near && cnt < n - k) cnt = extent(cnt, n - k, [&](int64_t i) { return key[k + i] <= hi; });
+        const int64_t e = k + cnt;
         Cell c;
         c.begin = static_cast<int32_t>(k);
         c.end = static_cast<int32_t>(e);
-        c.skip = e < n ? cbase[e] : total;
-        c.node = cnt >= 2 ? nbase[k] + (l - L) : -1;
+        c.skip = e < n ? base[e / kScanWG].cells + cells_in(cnt < near ? s_word[threadIdx.x + cnt] : word[e])
+                       : pr->tot.cells;
+        c.node = cnt >= 2 ? q0 + (l - L) : -1;
         c.level = l;
         c.split = (cnt > n_leaf && l < kDeepest) ? 1 : 0;
         c.pad0 = c.pad1 = 0;
-        cell[cbase[k] + (l - L)] = c;
+        cell[c0 + (l - L)] = c;
         if (c.node >= 0) {
             node_level[c.node] = l;
             node_begin[c.node] = k;
             node_end[c.node] = e;
-            node_cell[c.node] = cbase[k] + (l - L);
+            node_cell[c.node] = c0 + (l - L);
         }
     }
 }
@@ -404,11 +497,12 @@ __device__ inline int32_t size_of(const NodeTest& r) { return static_cast<int32_
 __device__ inline bool is_node(int32_t kid) { return kid < 0 && kid != kNone; }
 
 // Every node's range, level and children (its centre of mass follows the moments).
-__global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const int32_t* __restrict__ node_cell,
-                                                        const Cell* __restrict__ cell, NodeRec* __restrict__ rec,
+__global__ __launch_bounds__(kWG) void node_recs_kernel(Caps caps, Progress* pr,
+                                                        const int32_t* __restrict__ node_cell, const Cell* __restrict__ cell, NodeRec* __restrict__ rec,
                                                         int32_t* __restrict__ parent, int32_t* __restrict__ arrived) {
     const int32_t q = blockIdx.x * kWG + threadIdx.x;
-    if (q >= m_nodes) return;
+    if (q == 0) pr->stamp[3] = wall_clock64();
+    if (q >= pr->tot.nodes || !fits(&pr->tot, caps)) return;
     const int32_t ci = node_cell[q];
     const Cell c = cell[ci];
     NodeRec r;
@@ -448,20 +542,21 @@ __global__ __launch_bounds__(kWG) void node_recs_kernel(int32_t m_nodes, const i
 // sizes by the rows it keeps waiting.  At 2^20 and 20011 particles one launch
 // per level from the deepest up took 336 and 124 us, with 28 and 4 us for the
 // means after them; this one takes 254 and 41 us.  (Rows that take a new node
-// when they are done: 350 and 46 us.  Whole subtrees in LDS first, tickets for
+// when they are done: 350 and 46 us.  Four lanes to a node: 270 and 51 us.  Whole subtrees in LDS first, tickets for
 // the nodes above them: 237 and 97 us.)
 #pragma clang fp contract(off)
 struct NodeOut {
     double *m, *x, *v, *a, *j;
 };
-__global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t m_nodes, const int32_t* __restrict__ parent,
+__global__ __launch_bounds__(kWG) void node_sums_kernel(Caps caps, const Progress* pr,
+                                                        const int32_t* __restrict__ parent,
                                                         int32_t* __restrict__ arrived, const double* __restrict__ sm,
                                                         const double* __restrict__ sx, const double* __restrict__ sv,
                                                         const double* __restrict__ sa, const double* __restrict__ sj,
                                                         double* __restrict__ raw, NodeRec* rec, NodeOut o) {
     const int r = threadIdx.x & 15;
     int32_t q = static_cast<int32_t>((blockIdx.x * int64_t(kWG) + threadIdx.x) >> 4);
-    if (q >= m_nodes) return;
+    if (q >= pr->tot.nodes || !fits(&pr->tot, caps)) return;
     int32_t kid[8];
     for (int c = 0; c < 8; ++c) kid[c] = rec[q].kid[c];
     for (int c = 0; c < 8; ++c)
@@ -482,7 +577,7 @@ __global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t m_nodes, const i
                 f[c] = mk[c] = 0.0;
                 if (is_node(kid[c])) {
                     if (r < 13)
-                        f[c] = __hip_atomic_load(raw + 13 * int64_t(~kid[c]) + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        f[c] = get_agent(raw + 13 * int64_t(~kid[c]) + r);
                 } else if (kid[c] != kNone) {
                     mk[c] = sm[kid[c]];
                     f[c] = src[r == 0 ? int64_t(kid[c]) : 3 * int64_t(kid[c])];
@@ -492,7 +587,7 @@ __global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t m_nodes, const i
             for (int c = 0; c < 8; ++c)
                 if (kid[c] != kNone) s = s + (is_node(kid[c]) ? f[c] : 0.0 + product(mk[c], f[c]));
         }
-        if (r < 13) __hip_atomic_store(raw + 13 * int64_t(q) + r, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (r < 13) put_agent(raw + 13 * int64_t(q) + r, s);
         const double M = wave_ops::first_of_row(s);
         if (r < 13) {
             const double mean = r == 0 ? M : s / M;
@@ -517,9 +612,9 @@ __global__ __launch_bounds__(kWG) void node_sums_kernel(int32_t m_nodes, const i
 // ---------------------------------------------------------------- lists
 struct ListArgs {
     int64_t n;
-    int32_t n_groups;
-    int32_t m_nodes;
     int32_t cut_cap;
+    Caps caps;
+    Progress* pr;
     const NodeRec* rec;
     const double* sx;
     const int64_t* group_first;
@@ -528,9 +623,7 @@ struct ListArgs {
     int64_t stage_cap;
     int32_t* glen;
     int64_t* gstage;
-    Counters* ctr;
     double theta2;
-    double s2[kDeepest + 1];
 };
 
 #pragma clang fp contract(off)
@@ -655,7 +748,7 @@ __device__ __forceinline__ bool walk_group(const ListArgs& A, int32_t g, int64_t
     const int32_t len = w.ocount[0];
     __syncthreads();
     if (t == 0) {
-        S.off = atomicAdd(&A.ctr->staged, static_cast<unsigned long long>(len));
+        S.off = atomicAdd(&A.pr->ctr.staged, static_cast<unsigned long long>(len));
         w.ocount[0] = 0;
     }
     __syncthreads();
@@ -714,17 +807,23 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
     __shared__ WalkShared S;
     __shared__ double s_box[6][kListWaves];
     const int t = threadIdx.x;
-    if (t <= kDeepest) S.s2[t] = A.s2[t];
-    if (A.m_nodes == 0) {   // a single particle
+    const Totals tot = A.pr->tot;
+    if (t == 0 && blockIdx.x == 0) A.pr->stamp[4] = wall_clock64();
+    if (!fits(&tot, A.caps)) return;
+    if (t <= kDeepest) {
+        const double side = ldexp(A.pr->root.side, -t);
+        S.s2[t] = side * side;
+    }
+    if (tot.nodes == 0) {   // a single particle
         if (t == 0 && blockIdx.x == 0) {
-            const unsigned long long off = atomicAdd(&A.ctr->staged, 1ull);
+            const unsigned long long off = atomicAdd(&A.pr->ctr.staged, 1ull);
             if (off < static_cast<unsigned long long>(A.stage_cap)) A.stage[off] = 0;
             A.glen[0] = 1;
             A.gstage[0] = static_cast<int64_t>(off);
         }
         return;
     }
-    for (int32_t g = blockIdx.x; g < A.n_groups; g += gridDim.x) {
+    for (int32_t g = blockIdx.x; g < tot.groups; g += gridDim.x) {
         const int64_t gb = A.group_first[g], ge = A.group_first[g + 1];
         // group box: componentwise min and max of the members' positions
         double lo[3], hi[3];
@@ -759,7 +858,7 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
             const Walk w{m, m + A.cut_cap, m + 2 * static_cast<int64_t>(A.cut_cap),
                          reinterpret_cast<uint16_t*>(m + 3 * static_cast<int64_t>(A.cut_cap)), A.cut_cap};
             if (!walk_group(A, g, gb, ge, lo, hi, w, S, &need) && t == 0) {
-                atomicMax(&A.ctr->max_cut, need);
+                atomicMax(&A.pr->ctr.max_cut, need);
                 A.glen[g] = 0;
                 A.gstage[g] = -1;
             }
@@ -768,20 +867,61 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
     }
 }
 
-// CSR copy: group g's staged list to entries[list_off[g] ...].
-__global__ __launch_bounds__(kWG) void csr_kernel(int32_t n_groups, const int64_t* __restrict__ list_off,
-                                                  const int64_t* __restrict__ gstage,
-                                                  const int32_t* __restrict__ stage, int32_t* __restrict__ entries) {
-    for (int32_t g = blockIdx.x; g < n_groups; g += gridDim.x) {
-        const int64_t b = list_off[g], len = list_off[g + 1] - b, s = gstage[g];
-        for (int64_t i = threadIdx.x; i < len; i += kWG) entries[b + i] = stage[s + i];
+// Whether every list was walked and staged.
+__device__ inline bool staged_all(const Progress* pr, const Caps& caps, int64_t stage_cap) {
+    return fits(&pr->tot, caps) && pr->ctr.max_cut == 0 &&
+           pr->ctr.staged <= static_cast<unsigned long long>(stage_cap);
+}
+
+// Where the lists begin: the sums of the lengths within each work-group's
+// kOffWG groups, and by the last work-group to be done those before each
+// work-group.  Also hands the build's outcome to the host.
+constexpr int kOffWG = 1024;
+__global__ __launch_bounds__(kOffWG) void offsets_kernel(Caps caps, int64_t stage_cap, Progress* pr,
+                                                         const int32_t* __restrict__ glen, int64_t* __restrict__ local,
+                                                         int64_t* part, int64_t* __restrict__ base, Outcome* out) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        out->ctr = pr->ctr;
+        for (int i = 0; i < kStamps - 1; ++i) out->stamp[i] = pr->stamp[i];
+        out->stamp[kStamps - 1] = wall_clock64();
+    }
+    const int32_t groups = pr->tot.groups, wgs = (groups + kOffWG - 1) / kOffWG;
+    if (!staged_all(pr, caps, stage_cap)) return;
+    // a work-group may have several turns: the grid is chosen before the groups are counted
+    for (int32_t w = blockIdx.x; w < wgs; w += gridDim.x) {
+        const int32_t g = w * kOffWG + threadIdx.x;
+        int64_t sum;
+        const int64_t off = scan_group<kOffWG>(g < groups ? int64_t(glen[g]) : 0, &sum);
+        if (g < groups) local[g] = off;
+        if (threadIdx.x == 0) put_agent(part + w, sum);
+    }
+    if (!last_here(&pr->offsets_done, gridDim.x)) return;
+    int64_t at = 0;
+    for (int32_t w = 0; w < wgs; w += kOffWG) {
+        const int32_t i = w + threadIdx.x;
+        int64_t all;
+        const int64_t off = scan_group<kOffWG>(i < wgs ? get_agent(part + i) : int64_t(0), &all);
+        if (i < wgs) base[i] = at + off;
+        at += all;
     }
 }
 
-__global__ void glen_to_off_kernel(int32_t n_groups, const int32_t* __restrict__ glen, int64_t* __restrict__ len64) {
-    const int32_t g = blockIdx.x * kWG + threadIdx.x;
-    if (g < n_groups) len64[g] = glen[g];
-    if (g == n_groups) len64[g] = 0;
+// CSR copy: group g's staged list to entries[list_off[g] ...].
+__global__ __launch_bounds__(kWG) void csr_kernel(Caps caps, int64_t stage_cap, int64_t entries_cap,
+                                                  const Progress* pr, const int32_t* __restrict__ glen,
+                                                  const int64_t* __restrict__ local, const int64_t* __restrict__ base,
+                                                  const int64_t* __restrict__ gstage,
+                                                  const int32_t* __restrict__ stage, int64_t* __restrict__ list_off,
+                                                  int32_t* __restrict__ entries) {
+    const int64_t total = static_cast<int64_t>(pr->ctr.staged);
+    if (!staged_all(pr, caps, stage_cap) || total > entries_cap) return;
+    const int32_t groups = pr->tot.groups;
+    if (blockIdx.x == 0 && threadIdx.x == 0) list_off[groups] = total;
+    for (int32_t g = blockIdx.x; g < groups; g += gridDim.x) {
+        const int64_t b = base[g / kOffWG] + local[g], len = glen[g], s = gstage[g];
+        if (threadIdx.x == 0) list_off[g] = b;
+        for (int64_t i = threadIdx.x; i < len; i += kWG) entries[b + i] = stage[s + i];
+    }
 }
 
 template <class T>
@@ -821,12 +961,12 @@ struct htd_tree {
     DevBuf<int32_t> idx_in, idx;
     DevBuf<int64_t> perm;
     DevBuf<double> sx, sv, sa, sj, sm;
-    DevBuf<int8_t> lev;
-    DevBuf<int32_t> ncell, cbase, nnode, nbase, gflag, gbase;
+    DevBuf<uint64_t> word, cpart;   // per particle and per work-group: counts
+    DevBuf<Totals> cbase;
     DevBuf<char> tmp;
     DevBuf<double> part;
-    DevBuf<Root> root;
-    DevBuf<Totals> tot;
+    DevBuf<Progress> pr;
+    Outcome* out = nullptr;         // pinned
     // cells and nodes
     DevBuf<Cell> cell;
     DevBuf<double> nm, nx, nv, na, nj;
@@ -836,200 +976,195 @@ struct htd_tree {
     DevBuf<int32_t> npar, narr;     // per node: parent, children whose sums are done
     DevBuf<int64_t> nbeg, nend;
     // groups and lists
-    DevBuf<int64_t> group_first, list_off, gstage, glen64;
+    DevBuf<int64_t> group_first, list_off, gstage, glocal, gpart, gbase;
     DevBuf<int32_t> glen, cut, stage, entries;
-    DevBuf<Counters> ctr;
     int32_t cut_cap = 1 << 15;
     int n_list_wg = 1024;
     // results of the last build
     int64_t n = 0, C = 0, M = 0, G = 0, L = 0;
     Root root_h{};
-    hipEvent_t ev[8] = {};
+    hipEvent_t ev[2] = {};
+    double tick_ms = 0;             // of the device's constant-rate counter
     float phase_ms[7] = {};
     bool built = false;
 };
 
 namespace {
 
-// Temporary storage of the library primitives, sized once per build before
-// anything is queued (freeing a buffer a queued primitive still uses would
-// be unsafe).  Node counts are bounded by 22 n (a chain of single-child
-// cells down to the deepest level per particle).
+// Temporary storage of the sort, sized before anything is queued (freeing a
+// buffer a queued primitive still uses would be unsafe).
 int reserve_tmp(htd_tree* t, int64_t n) {
-    size_t a = 0, b = 0, c = 0;
+    size_t a = 0;
     HTD_HIP(rocprim::radix_sort_pairs(nullptr, a, t->key_in.p, t->key.p, t->idx_in.p, t->idx.p,
                                       static_cast<size_t>(n), 0, 63, t->stream));
-    HTD_HIP(rocprim::exclusive_scan(nullptr, b, t->ncell.p, t->cbase.p, int32_t(0), static_cast<size_t>(22 * n),
-                                    rocprim::plus<int32_t>(), t->stream));
-    HTD_HIP(rocprim::exclusive_scan(nullptr, c, t->glen64.p, t->list_off.p, int64_t(0), static_cast<size_t>(n + 1),
-                                    rocprim::plus<int64_t>(), t->stream));
-    return t->tmp.grow(static_cast<int64_t>(std::max(a, std::max(b, c))));
-}
-
-int scan_i32(htd_tree* t, const int32_t* in, int32_t* out, int64_t n) {
-    size_t bytes = static_cast<size_t>(t->tmp.cap);
-    HTD_HIP(rocprim::exclusive_scan(t->tmp.p, bytes, in, out, int32_t(0), static_cast<size_t>(n),
-                                    rocprim::plus<int32_t>(), t->stream));
-    return 0;
-}
-
-int scan_i64(htd_tree* t, const int64_t* in, int64_t* out, int64_t n) {
-    size_t bytes = static_cast<size_t>(t->tmp.cap);
-    HTD_HIP(rocprim::exclusive_scan(t->tmp.p, bytes, in, out, int64_t(0), static_cast<size_t>(n),
-                                    rocprim::plus<int64_t>(), t->stream));
-    return 0;
+    return t->tmp.grow(static_cast<int64_t>(a));
 }
 
 int grow_particles(htd_tree* t, int64_t n) {
     int rc = 0;
+    const int64_t scans = (n + kScanWG - 1) / kScanWG, offs = (n + kOffWG - 1) / kOffWG;
     if ((rc = t->key_in.grow(n)) || (rc = t->key.grow(n)) || (rc = t->idx_in.grow(n)) || (rc = t->idx.grow(n)) ||
         (rc = t->perm.grow(n)) || (rc = t->sx.grow(3 * n)) || (rc = t->sv.grow(3 * n)) || (rc = t->sa.grow(3 * n)) ||
-        (rc = t->sj.grow(3 * n)) || (rc = t->sm.grow(n)) || (rc = t->lev.grow(n)) || (rc = t->ncell.grow(n)) ||
-        (rc = t->cbase.grow(n)) || (rc = t->nnode.grow(n)) || (rc = t->nbase.grow(n)) || (rc = t->gflag.grow(n)) ||
-        (rc = t->gbase.grow(n)) || (rc = t->part.grow(6 * 1024)) || (rc = t->root.grow(1)) || (rc = t->tot.grow(1)) ||
-        (rc = t->ctr.grow(1)) || (rc = t->group_first.grow(n + 1)) ||
-        (rc = t->list_off.grow(n + 1)) ||
-        (rc = t->gstage.grow(n + 1)) || (rc = t->glen64.grow(n + 1)) || (rc = t->glen.grow(n + 1)))
+        (rc = t->sj.grow(3 * n)) || (rc = t->sm.grow(n)) || (rc = t->word.grow(n)) || (rc = t->cpart.grow(scans)) ||
+        (rc = t->cbase.grow(scans)) || (rc = t->part.grow(6 * kBoxWGs)) || (rc = t->group_first.grow(n + 1)) ||
+        (rc = t->list_off.grow(n + 1)) || (rc = t->gstage.grow(n + 1)) || (rc = t->glocal.grow(n + 1)) ||
+        (rc = t->gpart.grow(offs)) || (rc = t->gbase.grow(offs)) || (rc = t->glen.grow(n + 1)))
+        return rc;
+    return 0;
+}
+
+int grow_nodes(htd_tree* t, int64_t cells, int64_t nodes) {
+    int rc = 0;
+    const int64_t M1 = std::max<int64_t>(nodes, 1);
+    if ((rc = t->cell.grow(cells)) || (rc = t->nm.grow(M1)) || (rc = t->nx.grow(3 * M1)) ||
+        (rc = t->nv.grow(3 * M1)) || (rc = t->na.grow(3 * M1)) || (rc = t->nj.grow(3 * M1)) ||
+        (rc = t->nlev.grow(M1)) || (rc = t->ncid.grow(M1)) || (rc = t->nraw.grow(13 * M1)) || (rc = t->nrec.grow(M1)) ||
+        (rc = t->npar.grow(M1)) || (rc = t->narr.grow(M1)) || (rc = t->nbeg.grow(M1)) || (rc = t->nend.grow(M1)))
         return rc;
     return 0;
 }
 
 // Work-groups of the list walk: one per group up to n_list_wg, fewer (down to
 // 64) where their scratch would pass 32 GB.
-int list_wgs(const htd_tree* t) {
+int64_t list_wgs(const htd_tree* t, int64_t groups) {
     const int64_t fit = (int64_t(32) << 30) / (4 * walk_words(t->cut_cap));
-    return static_cast<int>(std::min<int64_t>(t->G, std::min<int64_t>(t->n_list_wg, std::max<int64_t>(fit, 64))));
+    return std::min<int64_t>(groups, std::min<int64_t>(t->n_list_wg, std::max<int64_t>(fit, 64)));
 }
 
-int run_lists(htd_tree* t, const ListArgs& base, int32_t* max_cut, unsigned long long* staged) {
-    ListArgs A = base;
-    A.cut = t->cut.p;
-    A.cut_cap = t->cut_cap;
-    A.stage = t->stage.p;
-    A.stage_cap = t->stage.cap;
-    A.ctr = t->ctr.p;
-    HTD_HIP(hipMemsetAsync(t->ctr.p, 0, sizeof(Counters), t->stream));
-    lists_kernel<<<list_wgs(t), kListWG, 0, t->stream>>>(A);
+// What the cell and node arrays hold, up to a quarter above the last counts
+// (the kernels on nodes are launched for as many as may be there).
+Caps caps_of(const htd_tree* t) {
+    const int64_t arrays = std::min({t->nm.cap, t->nx.cap / 3, t->nv.cap / 3, t->na.cap / 3, t->nj.cap / 3, t->nlev.cap,
+                                     t->ncid.cap, t->nraw.cap / 13, t->nrec.cap, t->npar.cap, t->narr.cap, t->nbeg.cap,
+                                     t->nend.cap, int64_t(INT32_MAX)});
+    return {t->cell.cap, std::min(arrays, t->M + t->M / 4 + 16)};
+}
+
+// How much of the rest of a build to queue: everything from the cells on, the
+// lists on, or the copy into entries alone.
+enum class From { cells, lists, copy };
+
+// Queues it for what the arrays hold, with `groups` groups expected (any number
+// is done).  The kernels do nothing where the arrays turn out to be too small.
+int queue_rest(htd_tree* t, From from, int64_t n, int n_leaf, double theta, int64_t groups) {
+    hipStream_t s = t->stream;
+    Progress* pr = t->pr.p;
+    const Caps caps = caps_of(t);
+    const int64_t M = std::max<int64_t>(caps.nodes, 1);
+    if (from == From::cells) {
+        cells_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, n_leaf, t->key.p, t->word.p, t->cbase.p, caps, pr, t->cell.p,
+                                                        t->nlev.p, t->nbeg.p, t->nend.p, t->ncid.p, t->group_first.p);
+        node_recs_kernel<<<blocks_for(M, kWG), kWG, 0, s>>>(caps, pr, t->ncid.p, t->cell.p, t->nrec.p, t->npar.p,
+                                                            t->narr.p);
+        node_sums_kernel<<<blocks_for(16 * M, kWG), kWG, 0, s>>>(
+            caps, pr, t->npar.p, t->narr.p, t->sm.p, t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p, t->nrec.p,
+            NodeOut{t->nm.p, t->nx.p, t->nv.p, t->na.p, t->nj.p});
+    }
+    if (from != From::copy) {
+        ListArgs A{};
+        A.n = n;
+        A.cut_cap = t->cut_cap;
+        A.caps = caps;
+        A.pr = pr;
+        A.rec = t->nrec.p;
+        A.sx = t->sx.p;
+        A.group_first = t->group_first.p;
+        A.cut = t->cut.p;
+        A.stage = t->stage.p;
+        A.stage_cap = t->stage.cap;
+        A.glen = t->glen.p;
+        A.gstage = t->gstage.p;
+        A.theta2 = theta * theta;
+        lists_kernel<<<static_cast<unsigned>(list_wgs(t, groups)), kListWG, 0, s>>>(A);
+        offsets_kernel<<<blocks_for(groups, kOffWG), kOffWG, 0, s>>>(caps, t->stage.cap, pr, t->glen.p, t->glocal.p,
+                                                                     t->gpart.p, t->gbase.p, t->out);
+    }
+    if (t->entries.cap > 0)
+        csr_kernel<<<static_cast<unsigned>(std::min<int64_t>(groups, 4096)), kWG, 0, s>>>(
+            caps, t->stage.cap, t->entries.cap, pr, t->glen.p, t->glocal.p, t->gbase.p, t->gstage.p, t->stage.p,
+            t->list_off.p, t->entries.p);
     HTD_HIP(hipGetLastError());
-    Counters c{};
-    HTD_HIP(hipMemcpyAsync(&c, t->ctr.p, sizeof c, hipMemcpyDeviceToHost, t->stream));
-    HTD_HIP(hipStreamSynchronize(t->stream));
-    *max_cut = c.max_cut;
-    *staged = c.staged;
     return 0;
 }
 
 int build(htd_tree* t, int64_t n, const double* x, const double* v, const double* a, const double* jerk,
           const double* m, int n_leaf, int n_crit, double theta) {
     hipStream_t s = t->stream;
+    Progress* pr = t->pr.p;
     if (int rc = grow_particles(t, n)) return rc;
     if (int rc = reserve_tmp(t, n)) return rc;
     HTD_HIP(hipEventRecord(t->ev[0], s));
-    // 1. root cube, keys, sort, gather
-    const int nb = static_cast<int>(std::min<int64_t>(1024, std::max<int64_t>(1, blocks_for(n, kWG))));
-    bbox_partial_kernel<<<nb, kWG, 0, s>>>(n, x, t->part.p);
-    bbox_final_kernel<<<1, kWG, 0, s>>>(nb, t->part.p, t->root.p);
-    keys_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, x, t->root.p, t->key_in.p, t->idx_in.p);
+    // 1. root cube, keys, sort; 2. the particle state in key order, counts
+    bbox_kernel<<<std::min<unsigned>(kBoxWGs, blocks_for(n, kWG)), kWG, 0, s>>>(n, x, t->part.p, pr);
+    keys_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, x, pr, t->key_in.p, t->idx_in.p);
     HTD_HIP(hipGetLastError());
-    HTD_HIP(hipEventRecord(t->ev[1], s));
     {
         size_t bytes = static_cast<size_t>(t->tmp.cap);
         HTD_HIP(rocprim::radix_sort_pairs(t->tmp.p, bytes, t->key_in.p, t->key.p, t->idx_in.p, t->idx.p,
                                           static_cast<size_t>(n), 0, 63, s));
     }
-    HTD_HIP(hipEventRecord(t->ev[2], s));
-    gather_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, t->idx.p, t->key.p, x, v, a, jerk, m, t->perm.p, t->sx.p,
-                                                     t->sv.p, t->sa.p, t->sj.p, t->sm.p, t->lev.p);
-    // 2. cells, nodes and groups
-    count_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, n_leaf, n_crit, t->key.p, t->lev.p, t->ncell.p, t->nnode.p,
-                                                    t->gflag.p);
+    particles_kernel<<<blocks_for(n, kScanWG), kScanWG, 0, s>>>(
+        n, n_leaf, n_crit, t->idx.p, t->key.p, x, v, a, jerk, m, t->perm.p, t->sx.p, t->sv.p, t->sa.p, t->sj.p,
+        t->sm.p, t->word.p, t->cpart.p, t->cbase.p, pr, t->out);
     HTD_HIP(hipGetLastError());
-    if (int rc = scan_i32(t, t->ncell.p, t->cbase.p, n)) return rc;
-    if (int rc = scan_i32(t, t->nnode.p, t->nbase.p, n)) return rc;
-    if (int rc = scan_i32(t, t->gflag.p, t->gbase.p, n)) return rc;
-    totals_kernel<<<1, 64, 0, s>>>(n, t->ncell.p, t->cbase.p, t->nnode.p, t->nbase.p, t->gflag.p, t->gbase.p,
-                                   t->tot.p);
-    Totals tot{};
-    HTD_HIP(hipMemcpyAsync(&tot, t->tot.p, sizeof tot, hipMemcpyDeviceToHost, s));
-    HTD_HIP(hipMemcpyAsync(&t->root_h, t->root.p, sizeof(Root), hipMemcpyDeviceToHost, s));
-    HTD_HIP(hipStreamSynchronize(s));
-    t->C = tot.cells;
-    t->M = tot.nodes;
-    t->G = tot.groups;
-    if (t->C < 1 || t->G < 1) return fail(HTD_EHIP, "tree construction produced no cells");
-    int rc = 0;
-    const int64_t M1 = std::max<int64_t>(t->M, 1);
-    if ((rc = t->cell.grow(t->C)) || (rc = t->nm.grow(M1)) || (rc = t->nx.grow(3 * M1)) ||
-        (rc = t->nv.grow(3 * M1)) || (rc = t->na.grow(3 * M1)) || (rc = t->nj.grow(3 * M1)) ||
-        (rc = t->nlev.grow(M1)) || (rc = t->ncid.grow(M1)) || (rc = t->nraw.grow(13 * M1)) || (rc = t->nrec.grow(M1)) ||
-        (rc = t->npar.grow(M1)) || (rc = t->narr.grow(M1)) ||
-        (rc = t->nbeg.grow(M1)) || (rc = t->nend.grow(M1)))
-        return rc;
-    cells_kernel<<<blocks_for(n, kWG), kWG, 0, s>>>(n, n_leaf, t->key.p, t->lev.p, t->cbase.p, t->nbase.p,
-                                                    t->gflag.p, t->gbase.p, t->tot.p, t->cell.p, t->nlev.p,
-                                                    t->nbeg.p, t->nend.p, t->ncid.p, t->group_first.p);
-    HTD_HIP(hipGetLastError());
-    HTD_HIP(hipEventRecord(t->ev[3], s));
-    // 3. node moments
-    if (t->M > 0) {
-        const int32_t Mi = static_cast<int32_t>(t->M);
-        node_recs_kernel<<<blocks_for(Mi, kWG), kWG, 0, s>>>(Mi, t->ncid.p, t->cell.p, t->nrec.p, t->npar.p, t->narr.p);
-        node_sums_kernel<<<blocks_for(16 * int64_t(Mi), kWG), kWG, 0, s>>>(
-            Mi, t->npar.p, t->narr.p, t->sm.p, t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p, t->nrec.p,
-            NodeOut{t->nm.p, t->nx.p, t->nv.p, t->na.p, t->nj.p});
-        HTD_HIP(hipGetLastError());
-    }
-    HTD_HIP(hipEventRecord(t->ev[4], s));
-    // 4. lists
-    ListArgs A{};
-    A.n = n;
-    A.n_groups = static_cast<int32_t>(t->G);
-    A.m_nodes = static_cast<int32_t>(t->M);
-    A.rec = t->nrec.p;
-    A.sx = t->sx.p;
-    A.group_first = t->group_first.p;
-    A.glen = t->glen.p;
-    A.gstage = t->gstage.p;
-    A.theta2 = theta * theta;
-    for (int l = 0; l <= kDeepest; ++l) {
-        const double sl = std::ldexp(t->root_h.side, -l);
-        A.s2[l] = sl * sl;
-    }
-    if ((rc = t->cut.grow(list_wgs(t) * walk_words(t->cut_cap)))) return rc;
-    if ((rc = t->stage.grow(std::max<int64_t>(t->stage.cap, 64 * n)))) return rc;
+    // 3., 4. cells, node moments and lists.  Where the arrays of an earlier build are there, all of
+    // it is queued for what they hold before the host knows the counts; a part that does not fit
+    // is queued again with larger arrays.
+    if (int rc = t->stage.grow(std::max<int64_t>(t->stage.cap, 64 * n))) return rc;
+    const bool blind = t->G > 0 && n >= t->n / 2 && n / 2 <= t->n &&
+                       t->cut.cap >= list_wgs(t, t->G) * walk_words(t->cut_cap);
+    From from = From::cells;
     for (int attempt = 0;; ++attempt) {
-        int32_t max_cut = 0;
-        unsigned long long staged = 0;
-        if ((rc = run_lists(t, A, &max_cut, &staged))) return rc;
-        if (max_cut == 0 && staged <= static_cast<unsigned long long>(t->stage.cap)) {
-            t->L = static_cast<int64_t>(staged);
-            break;
+        if (attempt > 0 || blind) {
+            if (attempt > 0 && from != From::copy) {
+                if (int rc = t->cut.grow(list_wgs(t, t->G) * walk_words(t->cut_cap))) return rc;
+                HTD_HIP(hipMemsetAsync(&pr->ctr, 0, sizeof(Counters), s));
+            }
+            if (int rc = queue_rest(t, from, n, n_leaf, theta, t->G)) return rc;
+            HTD_HIP(hipEventRecord(t->ev[1], s));
+        }
+        HTD_HIP(hipStreamSynchronize(s));
+        const Outcome o = *t->out;
+        const Caps had = caps_of(t);
+        if (o.tot.cells < 1 || o.tot.groups < 1) return fail(HTD_EHIP, "tree construction produced no cells");
+        t->C = o.tot.cells;
+        t->M = o.tot.nodes;
+        t->G = o.tot.groups;
+        if (t->C > had.cells || t->M > had.nodes || (attempt == 0 && !blind)) {
+            if (int rc = grow_nodes(t, t->C, t->M)) return rc;
+            continue;
+        }
+        const int64_t staged = static_cast<int64_t>(o.ctr.staged);
+        if (o.ctr.max_cut == 0 && staged <= t->stage.cap) {
+            t->L = staged;
+            if (staged <= t->entries.cap) break;
+            if (int rc = t->entries.grow(std::max<int64_t>(staged, 1))) return rc;
+            from = From::copy;
+            continue;
         }
         if (attempt >= 32) return fail(HTD_ERANGE, "interaction lists did not fit after %d attempts", attempt + 1);
-        if (max_cut > 0) {
+        from = From::lists;
+        if (o.ctr.max_cut > 0) {
             // a group's opened cells outgrew the per-work-group scratch.  They were counted up to
             // the level that did not fit, so the next size at least doubles, up to all nodes.
-            if (int64_t(max_cut) > INT32_MAX / 2) return fail(HTD_ERANGE, "a group's list exceeds 2^30 entries");
-            t->cut_cap = static_cast<int32_t>(std::min<int64_t>(t->M, 2 * int64_t(max_cut)));
+            if (int64_t(o.ctr.max_cut) > INT32_MAX / 2) return fail(HTD_ERANGE, "a group's list exceeds 2^30 entries");
+            t->cut_cap = static_cast<int32_t>(std::min<int64_t>(t->M, 2 * int64_t(o.ctr.max_cut)));
             t->cut.release();
-            if ((rc = t->cut.grow(list_wgs(t) * walk_words(t->cut_cap)))) return rc;
         }
-        if (staged > static_cast<unsigned long long>(t->stage.cap)) {
+        if (staged > t->stage.cap) {
             t->stage.release();
-            if ((rc = t->stage.grow(static_cast<int64_t>(staged)))) return rc;
+            if (int rc = t->stage.grow(staged)) return rc;
         }
     }
-    HTD_HIP(hipEventRecord(t->ev[5], s));
-    const int32_t Gi = static_cast<int32_t>(t->G);
-    glen_to_off_kernel<<<blocks_for(int64_t(Gi) + 1, kWG), kWG, 0, s>>>(Gi, t->glen.p, t->glen64.p);
-    if ((rc = scan_i64(t, t->glen64.p, t->list_off.p, int64_t(Gi) + 1))) return rc;
-    if ((rc = t->entries.grow(std::max<int64_t>(t->L, 1)))) return rc;
-    csr_kernel<<<std::min(Gi, 4096), kWG, 0, s>>>(Gi, t->list_off.p, t->gstage.p, t->stage.p, t->entries.p);
-    HTD_HIP(hipGetLastError());
-    HTD_HIP(hipEventRecord(t->ev[6], s));
-    HTD_HIP(hipStreamSynchronize(s));
-    for (int i = 0; i < 6; ++i) HTD_HIP(hipEventElapsedTime(&t->phase_ms[i], t->ev[i], t->ev[i + 1]));
-    HTD_HIP(hipEventElapsedTime(&t->phase_ms[6], t->ev[0], t->ev[6]));
+    t->root_h = t->out->root;
+    float ms = 0;
+    HTD_HIP(hipEventElapsedTime(&ms, t->ev[0], t->ev[1]));
+    t->phase_ms[6] = t->phase_ms[5] = ms;
+    for (int i = 0; i < kStamps - 1; ++i) {
+        const auto ticks = static_cast<int64_t>(t->out->stamp[i + 1] - t->out->stamp[i]);
+        t->phase_ms[i] = static_cast<float>(static_cast<double>(std::max<int64_t>(ticks, 0)) * t->tick_ms);
+        t->phase_ms[5] -= t->phase_ms[i];
+    }
     t->n = n;
     t->built = true;
     return 0;
@@ -1066,7 +1201,17 @@ int htd_create(htd_tree** out, int32_t device, void* stream, int64_t n_max) {
             htd_destroy(t);
             return fail(HTD_EHIP, "hipEventCreate failed");
         }
-    if (int rc = grow_particles(t, n_max)) {
+    int khz = 0;
+    if (hipHostMalloc(&t->out, sizeof(Outcome)) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz < 1) {
+        htd_destroy(t);
+        return fail(HTD_EHIP, "pinned memory or the counter's rate is not available");
+    }
+    t->tick_ms = 1.0 / khz;
+    int rc = grow_particles(t, n_max);
+    if (rc == 0) rc = t->pr.grow(1);
+    if (rc == 0 && hipMemset(t->pr.p, 0, sizeof(Progress)) != hipSuccess) rc = fail(HTD_EHIP, "hipMemset failed");
+    if (rc) {
         htd_destroy(t);
         return rc;
     }
@@ -1082,14 +1227,15 @@ int htd_destroy(htd_tree* t) {
     for (auto& e : t->ev)
         if (e) (void)hipEventDestroy(e);
     t->key_in.release(); t->key.release(); t->idx_in.release(); t->idx.release(); t->perm.release();
-    t->sx.release(); t->sv.release(); t->sa.release(); t->sj.release(); t->sm.release(); t->lev.release();
-    t->ncell.release(); t->cbase.release(); t->nnode.release(); t->nbase.release(); t->gflag.release();
-    t->gbase.release(); t->tmp.release(); t->part.release(); t->root.release(); t->tot.release();
+    t->sx.release(); t->sv.release(); t->sa.release(); t->sj.release(); t->sm.release(); t->word.release();
+    t->cpart.release(); t->cbase.release(); t->tmp.release(); t->part.release(); t->pr.release();
     t->cell.release(); t->nm.release(); t->nx.release(); t->nv.release(); t->na.release(); t->nj.release();
     t->nlev.release(); t->ncid.release(); t->nraw.release(); t->nrec.release(); t->npar.release();
     t->narr.release(); t->nbeg.release();
-    t->nend.release(); t->group_first.release(); t->list_off.release(); t->gstage.release(); t->glen64.release();
-    t->glen.release(); t->cut.release(); t->stage.release(); t->entries.release(); t->ctr.release();
+    t->nend.release(); t->group_first.release(); t->list_off.release(); t->gstage.release(); t->glocal.release();
+    t->gpart.release(); t->gbase.release(); t->glen.release(); t->cut.release(); t->stage.release();
+    t->entries.release();
+    if (t->out) (void)hipHostFree(t->out);
     delete t;
     return 0;
 }
@@ -1178,13 +1324,12 @@ int htd_device_bytes(const htd_tree* t, size_t* bytes) {
     size_t b = 0;
     auto add = [&](const auto& buf) { b += sizeof(*buf.p) * static_cast<size_t>(buf.cap); };
     add(t->key_in), add(t->key), add(t->idx_in), add(t->idx), add(t->perm);
-    add(t->sx), add(t->sv), add(t->sa), add(t->sj), add(t->sm), add(t->lev);
-    add(t->ncell), add(t->cbase), add(t->nnode), add(t->nbase), add(t->gflag), add(t->gbase);
-    add(t->tmp), add(t->part), add(t->root), add(t->tot), add(t->cell);
+    add(t->sx), add(t->sv), add(t->sa), add(t->sj), add(t->sm), add(t->word), add(t->cpart), add(t->cbase);
+    add(t->tmp), add(t->part), add(t->pr), add(t->cell);
     add(t->nm), add(t->nx), add(t->nv), add(t->na), add(t->nj), add(t->nlev), add(t->ncid), add(t->nraw), add(t->nrec);
     add(t->npar), add(t->narr);
-    add(t->nbeg), add(t->nend), add(t->group_first), add(t->list_off), add(t->gstage), add(t->glen64);
-    add(t->glen), add(t->cut), add(t->stage), add(t->entries), add(t->ctr);
+    add(t->nbeg), add(t->nend), add(t->group_first), add(t->list_off), add(t->gstage), add(t->glocal), add(t->gpart), add(t->gbase);
+    add(t->glen), add(t->cut), add(t->stage), add(t->entries);
     *bytes = b;
     return 0;
 }
