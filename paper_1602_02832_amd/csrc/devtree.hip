@@ -12,8 +12,9 @@
 //   2. the octree without a pointer walk.  With L_k the first level at which
 //      particle k's key leaves particle k-1's cell, the cells that begin at
 //      particle k are those of levels L_k ... E_k, and pre-order is the order
-//      of (first particle, level).  Per-particle counts and three prefix sums
-//      give every cell, node and group its pre-order number directly.
+//      of (first particle, level).  Per-particle counts and their prefix sums,
+//      made where the state is gathered, give every cell, node and group its
+//      pre-order number directly.
 //   3. node moments, bottom-up in one launch: 16 lanes to a node, one for each
 //      sum, add its children's sums (or a leaf's particles) in order; the last
 //      child of a node to be done goes on with the node.
@@ -21,6 +22,8 @@
 //      visiting every cell once; the counts of list entries under each opened
 //      cell are then summed upwards and the entries placed on the way down
 //      again, so that the list comes out in pre-order.
+// A rebuild queues all of it at once for what the arrays of the build before it
+// hold, and looks at the counts at the end.
 #include "htree_tree.h"
 #include "wave_ops.h"
 
@@ -348,9 +351,9 @@ __device__ inline int32_t groups_in(uint64_t w) { return static_cast<int32_t>((w
 // each particle, their sums over the particles before it in the work-group,
 // and (by the last work-group to be done) the sums before every work-group.
 // The gather of 104 bytes a particle from random places bounds it, and hides
-// the counting.  At 2^20 particles 135 us; a gather, a count that searched all
-// n keys for the cell above, three scans and a kernel for their totals took
-// 210 us.
+// part of the counting.  At 2^20 and 20011 particles 143 and 15 us; a gather, a
+// count that searched all n keys for the cell above, three scans and a kernel
+// for their totals, nine launches, took 206 and 45 us.
 __global__ __launch_bounds__(kScanWG) void particles_kernel(
     int64_t n, int n_leaf, int n_crit, const int32_t* __restrict__ perm32, const uint64_t* __restrict__ key,
     const double* __restrict__ x, const double* __restrict__ v, const double* __restrict__ a,
@@ -419,9 +422,11 @@ __global__ __launch_bounds__(kScanWG) void particles_kernel(
 }
 
 // The cells and nodes that begin at each particle, from the deepest up: a
-// cell's end lies past the one below it, at most a few doublings of its size
-// away.  At 2^20 and 20011 particles 100 and 15 us with a search of all keys
-// for every cell.
+// cell's end lies past the one below it, a few times its size away at most
+// where it has siblings.  A work-group keeps kTile keys from its first particle
+// on in LDS, which most cells end in.  At 2^20 particles 49 us, 61 us without
+// the LDS, 99 us with a search of all keys for every cell; at 20011, 15 us with
+// any (a chain of dependent accesses for the few large cells).
 constexpr int kTile = 4 * kWG;
 __global__ __launch_bounds__(kWG) void cells_kernel(int64_t n, int n_leaf, const uint64_t* __restrict__ key,
                                                     const uint64_t* __restrict__ word,
