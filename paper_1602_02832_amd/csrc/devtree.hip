@@ -15,9 +15,10 @@
 //      of (first particle, level).  Per-particle counts and their prefix sums,
 //      made where the state is gathered, give every cell, node and group its
 //      pre-order number directly.
-//   3. node moments, bottom-up in one launch: 16 lanes to a node, one for each
-//      sum, add its children's sums (or a leaf's particles) in order; the last
-//      child of a node to be done goes on with the node.
+//   3. node moments, bottom-up in one launch: four lanes to a node add its
+//      children's sums (or a leaf's particles) in order, small subtrees within
+//      a work-group; above them the last child of a node to be done goes on
+//      with the node.
 //   4. lists: one work-group per group goes down the tree a level at a time,
 //      visiting every cell once; the counts of list entries under each opened
 //      cell are then summed upwards and the entries placed on the way down
@@ -514,19 +515,22 @@ __global__ __launch_bounds__(kWG) void node_recs_kernel(Caps caps, Progress* pr,
     for (int d = 0; d < 3; ++d) r.x[d] = 0.0;
     r.begin_level = static_cast<uint32_t>(c.begin) | static_cast<uint32_t>(c.level) << kBeginBits;
     r.end = static_cast<uint32_t>(c.end);
-    int32_t ch = c.split ? ci + 1 : c.skip;
+    int32_t ch = c.split ? ci + 1 : c.skip, below = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {   // a cell has at most eight children
         r.kid[k] = kNone;
         if (ch < c.skip) {
             const Cell cc = cell[ch];
             r.kid[k] = cc.node >= 0 ? ~cc.node : cc.begin;
-            if (cc.node >= 0) parent[cc.node] = q;
+            if (cc.node >= 0) {
+                parent[cc.node] = q;
+                ++below;
+            }
             ch = cc.skip;
         }
     }
     rec[q] = r;
-    arrived[q] = 0;
+    arrived[q] = -below;   // the last node child to be done gets -1
     if (q == 0) parent[0] = -1;
 }
 
@@ -537,79 +541,162 @@ __global__ __launch_bounds__(kWG) void node_recs_kernel(Caps caps, Progress* pr,
 // ascending order; the means are the sums divided by the mass.  No fused
 // multiply-add anywhere, so the bits match.  raw holds S, 13 doubles per node.
 //
-// Sixteen lanes (a DPP row) to a node, lane r < 13 for sum r.  The rows of the
-// nodes without node children begin; a row that has stored its node's sums
-// takes a ticket of the parent, and the one that takes the last goes on with
-// the parent, up to the root.  The sums go through to where every XCD sees
-// them (agent-scope stores and loads, which pass the L2s that are not coherent
-// with each other), and the ticket is taken once they are there.  The launch
-// is bound by that chain, a few dependent accesses per level, and at the large
-// sizes by the rows it keeps waiting.  At 2^20 and 20011 particles one launch
-// per level from the deepest up took 336 and 124 us, with 28 and 4 us for the
-// means after them; this one takes 254 and 41 us.  (Rows that take a new node
-// when they are done: 350 and 46 us.  Four lanes to a node: 270 and 51 us.  Whole subtrees in LDS first, tickets for
-// the nodes above them: 237 and 97 us.)
+// Four lanes (a DPP quad) to a node, one for each vector; every one sums the
+// mass as well.  A work-group takes about kStride nodes in pre-order.  The
+// nodes whose whole subtree is among them, most, are summed in it: every quad
+// loads its node's single particles at once and then waits in LDS for the sums
+// of its node children.  The others are the ancestors of the next work-group's
+// first node, which is chosen as the shallowest of 2 kSlack: they are summed
+// by whichever quad, of any work-group, finishes the last of their children
+// and so takes the last ticket.  Their children's sums go through to where
+// every XCD sees them (agent-scope stores and loads, which pass the L2s that
+// are not coherent with each other), and the ticket is taken once they are
+// there: about 3 us a level, which bounds the small sizes.  At 2^20 and 20011
+// particles one launch per level from the deepest up took 336 and 124 us, with
+// 28 and 4 us for the means after them; all sums through memory with sixteen
+// lanes to a node, 250 and 40 us, with four, 270 and 51 us; this, 183 and 41 us
+// (work-groups of 512 and 1024 threads: 193 and 233 us at 2^20).
 #pragma clang fp contract(off)
 struct NodeOut {
     double *m, *x, *v, *a, *j;
 };
-__global__ __launch_bounds__(kWG) void node_sums_kernel(Caps caps, const Progress* pr,
-                                                        const int32_t* __restrict__ parent,
-                                                        int32_t* __restrict__ arrived, const double* __restrict__ sm,
-                                                        const double* __restrict__ sx, const double* __restrict__ sv,
-                                                        const double* __restrict__ sa, const double* __restrict__ sj,
-                                                        double* __restrict__ raw, NodeRec* rec, NodeOut o) {
-    const int r = threadIdx.x & 15;
-    int32_t q = static_cast<int32_t>((blockIdx.x * int64_t(kWG) + threadIdx.x) >> 4);
-    if (q >= pr->tot.nodes || !fits(&pr->tot, caps)) return;
+constexpr int kSumWG = 256;
+constexpr int kQuads = kSumWG / 4;                // nodes that a work-group holds
+constexpr int kSlack = 8;
+constexpr int kStride = kQuads - 2 * kSlack;
+static_assert(2 * kSlack <= 32, "half a wave looks at the places for a cut");
+
+// A node's children's contributions: the single particles' as loaded, the node
+// children's from where their sums are.
+struct Kids {
     int32_t kid[8];
-    for (int c = 0; c < 8; ++c) kid[c] = rec[q].kid[c];
-    for (int c = 0; c < 8; ++c)
-        if (is_node(kid[c])) return;   // begun by the last of its children
-    const int d = (r + 2) % 3;         // component of the vector that lane r >= 1 sums
-    const double* src = r == 0 ? sm : (r < 4 ? sx : r < 7 ? sv : r < 10 ? sa : sj) + d;
-    double* dst = r == 0 ? o.m : (r < 4 ? o.x : r < 7 ? o.v : r < 10 ? o.a : o.j) + d;
-    auto product = [&](double mk, double f) { return r == 0 ? mk : mk * f; };
+    double m[8], f[8][3];
+
+    __device__ __forceinline__ void load(const NodeRec* rec, int32_t q) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) kid[c] = rec[q].kid[c];
+    }
+    __device__ __forceinline__ void load_particles(const double* sm, const double* src) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            m[c] = f[c][0] = f[c][1] = f[c][2] = 0.0;
+            if (kid[c] < 0) continue;
+            m[c] = sm[kid[c]];
+            for (int d = 0; d < 3; ++d) f[c][d] = src[3 * int64_t(kid[c]) + d];
+        }
+    }
+    // node_sum(q, k): sum k of node q, k = 0 the mass
+    template <class Sum>
+    __device__ __forceinline__ void add(double* M, double* s, Sum node_sum) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            if (!is_node(kid[c])) continue;
+            m[c] = node_sum(~kid[c], 0);
+            for (int d = 0; d < 3; ++d) f[c][d] = node_sum(~kid[c], 1 + d);
+        }
+        *M = s[0] = s[1] = s[2] = 0.0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            if (kid[c] == kNone) continue;
+            const bool node = is_node(kid[c]);
+            *M = *M + (node ? m[c] : 0.0 + m[c]);
+            for (int d = 0; d < 3; ++d) s[d] = s[d] + (node ? f[c][d] : 0.0 + m[c] * f[c][d]);
+        }
+    }
+};
+
+__global__ __launch_bounds__(kSumWG) void node_sums_kernel(Caps caps, const Progress* pr,
+                                                           const int32_t* __restrict__ parent, int32_t* arrived,
+                                                           const double* __restrict__ sm,
+                                                           const double* __restrict__ sx, const double* __restrict__ sv,
+                                                           const double* __restrict__ sa, const double* __restrict__ sj,
+                                                           double* raw, NodeRec* rec, NodeOut o) {
+    __shared__ int32_t s_left[kQuads];   // node children still to be summed, or kNone: not in this work-group
+    __shared__ double s_sum[kQuads][13];
+    const int32_t nodes = pr->tot.nodes;
+    if (!fits(&pr->tot, caps) || blockIdx.x * int64_t(kStride) >= nodes) return;
+    const int lane = threadIdx.x & 63, r = threadIdx.x & 3;
+    // cuts: lanes 0-31 look at the places for this work-group's first node, the others for the next's
+    const int64_t mark = (blockIdx.x + int64_t(lane >> 5)) * kStride;
+    int64_t at = mark - kSlack + (lane & 31);
+    const bool place = (lane & 31) < 2 * kSlack && at >= 0 && at < nodes;
+    int best = place ? static_cast<int>(rec[at].begin_level >> kBeginBits) * 32 + (lane & 31) : INT32_MAX;
+    for (int w = 16; w > 0; w >>= 1) best = min(best, __shfl_xor(best, w));
+    const int32_t cut = static_cast<int32_t>(mark <= 0 ? 0 : mark >= nodes ? nodes : mark - kSlack + (best & 31));
+    const int32_t q0 = wave_ops::read_lane(cut, 0), q1 = wave_ops::read_lane(cut, 32);
+    // a node's subtree follows it: it ends before q1 if node q1 begins past the node's particles
+    const int64_t beyond = q1 < nodes ? first_of(rec[q1]) : INT64_MAX;
+
+    const int slot = threadIdx.x >> 2;
+    int32_t q = q0 + slot;
+    const bool on = q < q1;
+    const double* src = r == 0 ? sx : r == 1 ? sv : r == 2 ? sa : sj;
+    double* dst = r == 0 ? o.x : r == 1 ? o.v : r == 2 ? o.a : o.j;
+    Kids K;
+    double M = 0.0, s[3] = {0.0, 0.0, 0.0};
+    int32_t p = -1;
+    bool todo = false;
+    if (on) {
+        K.load(rec, q);
+        p = parent[q];
+        todo = static_cast<int64_t>(rec[q].end) <= beyond;
+        int32_t below = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) below += is_node(K.kid[c]);
+        if (r == 0) s_left[slot] = todo ? below : kNone;
+    }
+    const bool mine = todo, leaf = mine && K.kid[0] == kNone;
+    if (leaf) {   // several particles
+        const int64_t e = rec[q].end;
+        for (int64_t k = first_of(rec[q]); k < e; ++k) {
+            const double mk = sm[k];
+            M = M + mk;
+            for (int d = 0; d < 3; ++d) s[d] = s[d] + mk * src[3 * k + d];
+        }
+    } else if (mine) {
+        K.load_particles(sm, src);
+    }
+    __syncthreads();
+    const bool up_here = mine && p >= q0 && s_left[p - q0] != kNone;
+    // Every turn sums the nodes whose children are done; a node's children are in this work-group,
+    // and one without any needs none, so that each wave's last turn comes.
+    while (__ballot(todo)) {
+        if (todo && __hip_atomic_load(&s_left[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) {
+            asm volatile("" ::: "memory");
+            if (!leaf) K.add(&M, s, [&](int32_t c, int k) { return s_sum[c - q0][k == 0 ? 0 : 3 * r + k]; });
+            if (r == 0) s_sum[slot][0] = M;
+            for (int d = 0; d < 3; ++d) s_sum[slot][1 + 3 * r + d] = s[d];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the sums are in LDS
+            if (r == 0 && up_here)
+                __hip_atomic_fetch_add(&s_left[p - q0], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            todo = false;
+        }
+    }
+    if (!mine) return;   // summed by the last of its children
     for (;;) {
-        double s = 0.0;
-        if (kid[0] == kNone) {   // a leaf of several particles
-            const int64_t e = rec[q].end;
-            for (int64_t k = first_of(rec[q]); k < e; ++k) s = s + product(sm[k], src[r == 0 ? k : 3 * k]);
-        } else {
-            double f[8], mk[8];   // every child's loads in flight before the first is added
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                f[c] = mk[c] = 0.0;
-                if (is_node(kid[c])) {
-                    if (r < 13)
-                        f[c] = get_agent(raw + 13 * int64_t(~kid[c]) + r);
-                } else if (kid[c] != kNone) {
-                    mk[c] = sm[kid[c]];
-                    f[c] = src[r == 0 ? int64_t(kid[c]) : 3 * int64_t(kid[c])];
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-                if (kid[c] != kNone) s = s + (is_node(kid[c]) ? f[c] : 0.0 + product(mk[c], f[c]));
-        }
-        if (r < 13) put_agent(raw + 13 * int64_t(q) + r, s);
-        const double M = wave_ops::first_of_row(s);
-        if (r < 13) {
-            const double mean = r == 0 ? M : s / M;
-            dst[r == 0 ? int64_t(q) : 3 * int64_t(q)] = mean;
-            if (r >= 1 && r < 4) rec[q].x[d] = mean;
-        }
-        const int32_t p = parent[q];
-        if (p < 0) return;
-        int32_t below = 0;   // node children of the parent
-        for (int c = 0; c < 8; ++c) kid[c] = rec[p].kid[c];
-        for (int c = 0; c < 8; ++c) below += is_node(kid[c]);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the sums are where every XCD sees them
+        const bool up = p >= 0 && !up_here;
         int32_t ticket = 0;
-        if (r == 0) ticket = __hip_atomic_fetch_add(arrived + p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (wave_ops::first_of_row(ticket) != below - 1) return;   // a sibling is still on its way
-        asm volatile("" ::: "memory");                             // the children's sums are read after the ticket
+        Kids P;
+        if (up) {
+            double* S = raw + 13 * int64_t(q);
+            if (r == 0) put_agent(S, M);
+            for (int d = 0; d < 3; ++d) put_agent(S + 1 + 3 * r + d, s[d]);
+            P.load(rec, p);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the sums are where every XCD sees them
+            if (r == 0) ticket = __hip_atomic_fetch_add(arrived + p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            P.load_particles(sm, src);
+        }
+        for (int d = 0; d < 3; ++d) {
+            const double mean = s[d] / M;
+            dst[3 * int64_t(q) + d] = mean;
+            if (r == 0) rec[q].x[d] = mean;
+        }
+        if (r == 0) o.m[q] = M;
+        if (!up || wave_ops::first_of_quad(ticket) != -1) return;   // nothing above, or a sibling is still on its way
+        asm volatile("" ::: "memory");                              // the children's sums are read after the ticket
+        P.add(&M, s, [&](int32_t c, int k) { return get_agent(raw + 13 * int64_t(c) + (k == 0 ? 0 : 3 * r + k)); });
         q = p;
+        p = parent[q];
     }
 }
 #pragma clang fp contract(on)
@@ -1061,7 +1148,7 @@ int queue_rest(htd_tree* t, From from, int64_t n, int n_leaf, double theta, int6
                                                         t->nlev.p, t->nbeg.p, t->nend.p, t->ncid.p, t->group_first.p);
         node_recs_kernel<<<blocks_for(M, kWG), kWG, 0, s>>>(caps, pr, t->ncid.p, t->cell.p, t->nrec.p, t->npar.p,
                                                             t->narr.p);
-        node_sums_kernel<<<blocks_for(16 * M, kWG), kWG, 0, s>>>(
+        node_sums_kernel<<<blocks_for(M, kStride), kSumWG, 0, s>>>(
             caps, pr, t->npar.p, t->narr.p, t->sm.p, t->sx.p, t->sv.p, t->sa.p, t->sj.p, t->nraw.p, t->nrec.p,
             NodeOut{t->nm.p, t->nx.p, t->nv.p, t->na.p, t->nj.p});
     }

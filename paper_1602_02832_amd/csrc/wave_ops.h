@@ -62,11 +62,10 @@ __device__ __forceinline__ V read_lane(V v, int l) {
     return by_halves(v, [l](uint32_t u) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(u, l)); });
 }
 
-// The value of the first lane of the same 16-lane row (all lanes of the row
-// must be active).
+// The value of the first of the same four lanes (all of which must be active).
 template <class V>
-__device__ __forceinline__ V first_of_row(V v) {
-    return by_halves(v, [](uint32_t u) { return __builtin_amdgcn_update_dpp(0u, u, 0x150, 0xf, 0xf, true); });   // row_newbcast:0
+__device__ __forceinline__ V first_of_quad(V v) {
+    return by_halves(v, [](uint32_t u) { return __builtin_amdgcn_update_dpp(0u, u, 0x000, 0xf, 0xf, true); });   // quad_perm:[0,0,0,0]
 }
 
 // Pairwise tree over a wave, lane k combining with lane k + OFF for OFF =
