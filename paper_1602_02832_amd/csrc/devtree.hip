@@ -88,7 +88,7 @@ __device__ inline bool fits(const Totals* t, const Caps& c) { return t->cells <=
 struct Counters {         // list phase
     unsigned long long staged;   // entries reserved in the staging array
     int32_t max_cut;             // most opened cells that did not fit a work-group's scratch
-    int32_t pad;
+    int32_t taken;               // groups that work-groups have gone on with after their first
 };
 
 struct Root {
@@ -898,6 +898,7 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
     __shared__ uint16_t s_okids[kLdsOpened];
     __shared__ WalkShared S;
     __shared__ double s_box[6][kListWaves];
+    __shared__ int32_t s_next;
     const int t = threadIdx.x;
     const Totals tot = A.pr->tot;
     if (t == 0 && blockIdx.x == 0) A.pr->stamp[4] = wall_clock64();
@@ -915,7 +916,7 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
         }
         return;
     }
-    for (int32_t g = blockIdx.x; g < tot.groups; g += gridDim.x) {
+    for (int32_t g = blockIdx.x; g < tot.groups; g = s_next) {
         const int64_t gb = A.group_first[g], ge = A.group_first[g + 1];
         // group box: componentwise min and max of the members' positions
         double lo[3], hi[3];
@@ -955,6 +956,7 @@ __global__ __launch_bounds__(kListWG, 4) void lists_kernel(ListArgs A) {
                 A.gstage[g] = -1;
             }
         }
+        if (t == 0) s_next = static_cast<int32_t>(gridDim.x) + atomicAdd(&A.pr->ctr.taken, 1);
         __syncthreads();
     }
 }
@@ -1071,7 +1073,7 @@ struct htd_tree {
     DevBuf<int64_t> group_first, list_off, gstage, glocal, gpart, gbase;
     DevBuf<int32_t> glen, cut, stage, entries;
     int32_t cut_cap = 1 << 15;
-    int n_list_wg = 1024;
+    int n_list_wg = 512;
     // results of the last build
     int64_t n = 0, C = 0, M = 0, G = 0, L = 0;
     Root root_h{};
