@@ -1,7 +1,7 @@
 """Rebuilds on one device tree (include/htree_tree.h): a build that finds the
 arrays of the one before it queues everything for what they hold, and has to
 notice where the counts turn out larger.  Each sequence goes through sizes at
-the edges of the kernels' tiles (512 particles, 1024 groups, 1024 keys) and
+the edges of the kernels' tiles (512 particles, 1024 groups, 1024 keys, 32768 particles' sort) and
 through steps that outgrow the cells, the nodes, the groups, the lists' staging
 or the entries.  Bit-exact against the oracle's tree, as index work has to be.
 """
@@ -28,6 +28,8 @@ SEQUENCES = {
     "tile_edges": [(uniform(n), 1, 8, 0.5) for n in (511, 512, 513, 1023, 1024, 1025, 256, 1, 2)],
     "cells_and_nodes": [(uniform(600), 1, 64, 0.6), (pairs(600), 1, 64, 0.6), (pairs(601), 2, 64, 0.6)],
     "groups": [(uniform(3000), 1, 3000, 0.6), (uniform(3000), 1, 1, 0.9), (uniform(2049), 3, 1, 0.9)],
+    "sort": [(uniform(n), 1, 512, 0.9) for n in (12345, 32768, 32769)] +
+            [(np.floor(3.0 * uniform(n)), 2, 64, 0.7) for n in (1300, 700)],   # 27 keys in all, shared over runs
     "lists": [(uniform(1500), 1, 32, 1.2), (uniform(1500), 1, 32, 0.2), (uniform(1500), 1, 1, 0.0),
               (uniform(1500), 40, 100, 0.5)],
 }
@@ -36,7 +38,7 @@ SEQUENCES = {
 @pytest.mark.parametrize("name", SEQUENCES)
 def test_rebuilds_match_oracle(oracle, name):
     import torch
-    tree = B.DeviceTree(n_max=4096)
+    tree = B.DeviceTree(n_max=40000)
     try:
         for k, (x, n_leaf, n_crit, theta) in enumerate(SEQUENCES[name]):
             n = len(x)
