@@ -9,7 +9,8 @@
 //
 //  * A work-group of 256 threads (four wave64) holds an i-tile of T active
 //    particles of one group (T a power of two, 1..256) and splits the list
-//    into S = 256 / T j-streams: thread t owns i-slot t % T and j-stream t / T.
+//    into S = 256 / T j-streams: thread t owns i-slot t % T and j-stream t / T
+//    (for T of 128 and 256, two i-slots and S twice as many streams).
 //  * The list range is walked in rounds of 256 entries.  In each round every
 //    thread gathers one entry of the combined memory, predicts it to the
 //    block time in registers (or reads the eagerly predicted arrays) and
@@ -18,8 +19,9 @@
 //    entry, which LDS broadcasts.
 //  * Partial sums of the S j-streams are reduced through LDS in a fixed order.
 //    Long lists of small tiles are split over several items (more parallel
-//    work for sparse block steps); their partials are summed in split order
-//    by a second kernel, so results never depend on scheduling.
+//    work for sparse block steps); their partials are summed in split order by
+//    the tile's last item to be done (by a second kernel where there are very
+//    many), so results never depend on scheduling.
 //
 // The pair sum is not a dense contraction (one rsqrt per pair), so it runs
 // on the vector ALUs; no matrix-core instructions are used.
@@ -628,22 +630,27 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
 }
 
 // The sums over nsplit splits, in split order, of `vals` values that lie next
-// to each other in every split (slot by slot from active position o0 on; splits
-// are `stride` values apart), into the outputs.  They come through LDS, as many
-// splits at a time as buf holds, so that the dependent adds wait on no memory.
-// The work-group's threads take at most kOut values each.
-template <int HOLD, class Load>
-__device__ __forceinline__ void sum_slots(const Desc& c, int64_t o0, int vals, int nsplit, int64_t stride, double* buf,
-                                          int tid, Load load) {
+// to each other in every split (slot by slot from active position o0 on), into
+// the outputs.  They come through LDS, as many splits at a time as buf holds,
+// so that the dependent adds wait on no memory: load(s, k) is value k of the
+// values of split s and those after it.  The work-group's threads take at most
+// kOut values each.
+template <int HOLD, int AHEAD, class Load>
+__device__ __forceinline__ void sum_slots(const Desc& c, int64_t o0, int vals, int nsplit, double* buf, int tid,
+                                          Load load) {
     const int per = HOLD / vals;
     double sum[kOut];
     for (int s0 = 0; s0 < nsplit; s0 += per) {
         const int m = nsplit - s0 < per ? nsplit - s0 : per;
         __syncthreads();
-#pragma unroll 4
-        for (int k = tid; k < m * vals; k += kWG) {
-            const int s = k / vals;
-            buf[k] = load((s0 + s) * stride + (k - s * vals));
+        for (int k0 = tid; k0 < m * vals; k0 += AHEAD * kWG) {
+            double v[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                if (k0 + u * kWG < m * vals) v[u] = load(s0, k0 + u * kWG);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                if (k0 + u * kWG < m * vals) buf[k0 + u * kWG] = v[u];
         }
         __syncthreads();
 #pragma unroll
@@ -670,7 +677,11 @@ __device__ __forceinline__ void sum_slots(const Desc& c, int64_t o0, int vals, i
 // An item of a split tile is done: the last one sums the tile's partials.  (A
 // launch of its own for these sums costs 4 to 11 us of a small step and 3.5 us
 // of the host's time.  Fences instead of agent-scope stores cost 7 us: they
-// write back and invalidate the whole L2.)
+// write back and invalidate the whole L2.)  The sum is the tail of its tile:
+// with four loads of a thread in flight and a division for each, tiles of many
+// splits made it longer than the launch it saves (a step of 225 active of
+// 448438 particles 26 us, 20 us with the launch), with sixteen 19 us.
+constexpr int kFoldAhead = 16;
 template <class P>
 __device__ __forceinline__ void fold_splits(const Desc& c, const Item& it, RTile* rtiles, LdsAll<P>& lds) {
     __shared__ int s_last;
@@ -687,8 +698,9 @@ __device__ __forceinline__ void fold_splits(const Desc& c, const Item& it, RTile
     if (!s_last) return;
     asm volatile("" ::: "memory");
     const int vals = it.n_i * kOut;
-    sum_slots<sizeof(LdsAll<P>) / sizeof(double)>(c, it.act_begin, vals, nsplit, vals, reinterpret_cast<double*>(&lds),
-                                                  tid, [&](int64_t k) { return agent_load(src + k); });
+    sum_slots<sizeof(LdsAll<P>) / sizeof(double), kFoldAhead>(
+        c, it.act_begin, vals, nsplit, reinterpret_cast<double*>(&lds), tid,
+        [&](int s, int k) { return agent_load(src + static_cast<int64_t>(s) * vals + k); });
 }
 
 __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g, bool rtile) {
@@ -792,8 +804,11 @@ __global__ __launch_bounds__(kWG) void reduce_kernel(const Entry* __restrict__ t
     if (s0 >= rt.n_i) return;
     const int slots = rt.n_i - s0 < n_slots ? rt.n_i - s0 : n_slots;
     const double* src = tab[cl].d.partial + (rt.pbase + s0) * kOut;
-    sum_slots<kRedLds>(tab[cl].d, rt.act_begin + s0, slots * kOut, rt.nsplit, static_cast<int64_t>(rt.n_i) * kOut, buf,
-                       threadIdx.x, [&](int64_t k) { return src[k]; });
+    const int vals = slots * kOut;
+    sum_slots<kRedLds, 4>(tab[cl].d, rt.act_begin + s0, vals, rt.nsplit, buf, threadIdx.x, [&](int s, int k) {
+        const int d = k / vals;
+        return src[static_cast<int64_t>(s + d) * rt.n_i * kOut + (k - d * vals)];
+    });
 }
 
 // Predict the whole combined memory into the EAGER records.
