@@ -198,11 +198,12 @@ int ht_step_async(ht_ctx *ctx, int32_t n_upd, const int32_t *d_idx, const double
                   double *d_pot);
 
 /* ht_step_async replayed through a HIP graph: the same arguments and the same
- * results, bit for bit.  The step's three launches (plan delivery with the
- * update, force, split reduction) are captured once per context into four
- * graphs (one per header slot, used in turn) whose kernels read the step's sizes from memory (a pinned header the
- * host rewrites before each replay, and the plan) and run on fixed grids, so
- * every replay is one hipGraphLaunch on the context's stream.  Needs
+ * results, bit for bit.  The step's two launches (plan delivery with the
+ * update; force, which also sums the split tiles) are captured once per
+ * context into four graphs (one per header slot, used in turn) whose kernels
+ * read the step's sizes from memory (a pinned header the host rewrites before
+ * each replay, and the plan) and run on fixed grids, so every replay is one
+ * hipGraphLaunch on the context's stream.  Needs
  * HT_PREDICT_FUSED; kernel timing (ht_set_timing) brackets the whole graph. */
 int ht_step_graph(ht_ctx *ctx, int32_t n_upd, const int32_t *d_idx, const double *d_t0, const double *d_m,
                   const double *d_x, const double *d_v, const double *d_a, const double *d_jerk, double t,
@@ -263,11 +264,12 @@ int ht_dev_step(ht_ctx *ctx, double eta, double dt_tree);
  * needs no nodes or lists, and no rebuild at tree times. */
 int ht_dev_step_direct(ht_ctx *ctx, double eta, double dt_tree);
 /* Resident mode: up to max_steps block steps (Section 2, steps 2 and 4a-6)
- * queued back to back with no host round trip between them.  Each step runs
- * the scheduler, a device work planner that builds the host planner's work
- * items (so the forces, and the run, have the same bits as step-by-step
- * ht_dev_next_block + ht_dev_step), the force and reduce launches on fixed
- * grids, and the corrector.  The loop stops before the first block time after
+ * queued back to back with no host round trip between them.  Each step is
+ * three launches: the scheduler with a device work planner that builds the
+ * host planner's work items (so the forces, and the run, have the same bits as
+ * step-by-step ht_dev_next_block + ht_dev_step), the force on a fixed grid,
+ * and the corrector, which also sums the split tiles and finds the next block
+ * time.  The loop stops before the first block time after
  * t_stop, and after the step at t_stop (a tree time, where the caller
  * rebuilds).  Synchronises once, at the end; *steps, *t_last (block time of
  * the last step taken) and *particle_steps report what was done.  Needs fused

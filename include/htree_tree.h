@@ -88,8 +88,9 @@ int htd_get(const htd_tree *t, int64_t *perm, uint64_t *keys, double *node_m, do
 /* Device pointers to the last build's results. */
 int htd_device_view(const htd_tree *t, htd_view *out);
 
-/* Device time of the last build's phases in ms: keys, sort, cells (with the
- * size read-back), moments, lists, CSR assembly, and the total. ms[7]. */
+/* Device time of the last build's phases in ms: root cube and keys (up to
+ * 32768 particles the keys are made by the sort), sort, cells (with the state
+ * in key order), moments, lists, CSR assembly, and the total. ms[7]. */
 int htd_phase_ms(const htd_tree *t, double *ms);
 
 /* Device bytes the builder holds now (its arrays grow with the largest tree
