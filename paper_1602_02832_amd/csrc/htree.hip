@@ -1895,19 +1895,22 @@ __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* _
         e.brest[b] = rest;
         agent_store(e.s.bcount + b, cnt_b);
     }
-    if (n_due > 1) {   // on to the plan in the last of the due blocks
+    const bool in_lds = n_due == 1 && cnt_b <= kPlanWG;
+    if (!in_lds) {   // the plan reads the counts and particles from memory, also where they are this block's alone
         stores_done();
         __syncthreads();
-        if (t == 0) {
-            S.last = __hip_atomic_fetch_add(&L->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_due - 1;
-            if (S.last) agent_store(&L->ticket, 0);
+        if (n_due > 1) {   // on to the plan in the last of the due blocks
+            if (t == 0) {
+                S.last = __hip_atomic_fetch_add(&L->ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_due - 1;
+                if (S.last) agent_store(&L->ticket, 0);
+            }
+            __syncthreads();
+            if (!S.last) return;
         }
-        __syncthreads();
-        if (!S.last) return;
         asm volatile("" ::: "memory");
     }
     LoopSum sum;
-    plan_step(e, L, z, S, t_next, n_due, due0, due1, n_due == 1 && cnt_b <= kPlanWG ? cnt_b : -1, launch + k, &sum);
+    plan_step(e, L, z, S, t_next, n_due, due0, due1, in_lds ? cnt_b : -1, launch + k, &sum);
     if (n_tab == 1) {
         if (t == 0) {
             launch->first_item = 0;

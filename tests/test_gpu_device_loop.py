@@ -1,0 +1,55 @@
+"""Edges of the device loops (ht_dev_run, ht_batch_dev_run) where the selection
+launch takes another way.  Bit for bit against the same steps taken one at a
+time.
+"""
+import numpy as np
+import pytest
+
+from paper_1602_02832_amd import driver
+from paper_1602_02832_amd import workloads as W
+
+from parity_util import say
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("t0", "dt", "x", "v", "a", "j", "pot")
+
+
+def test_one_block_due_alone_with_more_particles_than_a_work_group():
+    """Above 524288 particles a scheduler block holds more than the 512 that the
+    planner keeps in LDS.  Where such a block is the only one due, the planner
+    reads its count and particles from memory, written in the same work-group."""
+    say("device loop: one block of up to 547 particles due alone")
+    n = 560000
+    chunk = (n + 1023) // 1024                          # particles of a scheduler block
+    assert chunk == 547
+    top = 1.0 / 256
+    x, v, m = W.plummer(n, 91)
+    sim = driver.Simulation(x, v, m, eps2=1e-6, dt_tree=top, eta=0.1, theta=0.6, n_crit=1024, precision="mixed",
+                            resident=True)
+    ctx = sim.ctx
+    t0 = np.zeros(n)
+    # (block, how many of its particles are due first): the counts of one case are not those of the next
+    for due in ([(900, 100)], [(900, 512)], [(900, 513)], [(900, 547)], [(3, 547)], [(900, 530), (901, 547)],
+                [(1022, 547)]):
+        dt = np.full(n, top)
+        for b, k in due:
+            first = b * chunk + (chunk - k) // 2
+            dt[first:first + k] = top * 2.0 ** -20      # the first steps double: all of them stay due together
+        state = (t0, dt, sim.m, sim.x, sim.v, sim.a, sim.j, sim.pot)
+        ctx.state_set(*state)
+        times, count = [], 0
+        for _ in range(3):
+            t, active = ctx.dev_next_block()
+            ctx.dev_step(0.1, top)
+            times.append(t)
+            count += active.size
+        want = ctx.state_get()
+        ctx.state_set(*state)
+        steps, t_last, psteps = ctx.dev_run(0.1, top, top / 2, 3)
+        got = ctx.state_get()
+        assert (steps, t_last, psteps) == (3, times[-1], count), due
+        assert count >= sum(k for _, k in due), due
+        for f, p, q in zip(FIELDS, got, want):
+            assert np.array_equal(p, q), (due, f)
+    sim.close()
