@@ -1911,7 +1911,7 @@ __global__ __launch_bounds__(kPlanWG) void loop_select_kernel(const LoopEntry* _
     }
     LoopSum sum;
     plan_step(e, L, z, S, t_next, n_due, due0, due1, in_lds ? cnt_b : -1, launch + k, &sum);
-    if (n_tab == 1) {
+    if (!ts) {   // a context of its own (a batch of one keeps the batch's counts and step times)
         if (t == 0) {
             launch->first_item = 0;
             cnt->items = sum.items;

@@ -5,7 +5,9 @@ time.
 import numpy as np
 import pytest
 
+from paper_1602_02832_amd import binding as B
 from paper_1602_02832_amd import driver
+from paper_1602_02832_amd import engine as E
 from paper_1602_02832_amd import workloads as W
 
 from parity_util import say
@@ -53,3 +55,46 @@ def test_one_block_due_alone_with_more_particles_than_a_work_group():
         for f, p, q in zip(FIELDS, got, want):
             assert np.array_equal(p, q), (due, f)
     sim.close()
+
+
+def resident(n, seed, stream, **kw):
+    x, v, m = W.plummer(n, seed)
+    return driver.Simulation(x, v, m, eps2=1e-4, dt_tree=1.0 / 64, eta=0.02, theta=0.5, n_crit=64, precision="mixed",
+                             resident=True, stream=stream.cuda_stream, **kw)
+
+
+def batch_of(k, stream):
+    return B.Batch(stream=stream.cuda_stream, max_clusters=k, max_items=1 << 15, max_active=1 << 13, max_rows=1 << 13)
+
+
+def test_batch_of_one_reports_its_engine_steps():
+    """A wall time for every engine step, also where the batch holds one context."""
+    import torch
+    say("batched device loop: one context")
+    stream = torch.cuda.Stream()
+    alone, batched = (resident(1500, 92, stream) for _ in range(2))
+    batch = batch_of(1, stream)
+    handles = np.array([batched.ctx.handle.value], np.uint64)
+    for most in (1, 7, 40):
+        k, t, p = alone.ctx.dev_run(0.02, 1.0 / 64, 1.0 / 64, most)
+        steps, t_last, psteps, pairs, step_ms = batch.dev_run(handles, [0.02], [1.0 / 64], [1.0 / 64], [most], 64)
+        assert (steps[0], t_last[0], psteps[0]) == (k, t, p) and pairs[0] == alone.ctx.last_stats()[0]
+        assert len(step_ms) == k > 0 and (step_ms > 0.0).all()
+    for q, w in zip(batched.ctx.state_get(), alone.ctx.state_get()):
+        assert np.array_equal(q, w)
+    for s in (alone, batched, batch):
+        s.close()
+
+
+def test_engine_with_one_cluster_counts_its_steps():
+    """The engine's step counts and times, of which its percentiles are taken."""
+    say("engine: device loop with one cluster")
+    eng = E.Engine(max_clusters=2, max_active=1 << 13, max_items=1 << 15, max_rows=1 << 13, resident=True,
+                   device_tree=True, tree_n_max=2000, device_loop=True, loop_steps=16)
+    c = eng.new_cluster(E.RunSpec(key=0, n=1200, seed=93, steps=40, n_crit=64))
+    eng.add(c)
+    while not c.done:
+        eng.step()
+    eng.drain()
+    assert c.steps_done == 40 and eng.engine_steps == 40 and len(eng.step_ms) == 40
+    eng.close()
