@@ -1944,8 +1944,9 @@ __global__ __launch_bounds__(kWG) void loop_correct_kernel(const LoopEntry* __re
     const LoopEntry& e = tab[k];
     const int b = blockIdx.x - e.first_block;
     const DevLoop& L = loops[k];
-    const double t1 = L.t_cur, eta = L.eta, dt_tree = L.dt_tree, own = e.s.bmin[b];
-    if (L.n_corr == 0 || own != t1) return;
+    const double t1 = L.t_cur, eta = L.eta, dt_tree = L.dt_tree;
+    if (L.n_corr == 0) return;   // before any access to the context's state: it may sit out and have none
+    if (e.s.bmin[b] != t1) return;
     const int32_t cnt = e.s.bcount[b], q0 = e.boff[b];
     const uint64_t* due = e.due + static_cast<int64_t>(b) * e.chunk;
     double first = e.brest[b];

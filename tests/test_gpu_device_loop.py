@@ -98,3 +98,31 @@ def test_engine_with_one_cluster_counts_its_steps():
     eng.drain()
     assert c.steps_done == 40 and eng.engine_steps == 40 and len(eng.step_ms) == 40
     eng.close()
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_context_that_sits_out_needs_no_state(first):
+    """No kernel of a call touches a context with max_steps = 0, so it may be
+    one without device state, particles or lists."""
+    import torch
+    say(f"batched device loop: a context without state sits out (first: {first})")
+    stream = torch.cuda.Stream()
+    alone, batched = (resident(1300, 94, stream) for _ in range(2))
+    bare = B.Context(n_max=64, node_max=16, group_max=1, list_max=16, active_max=64, eps2=1e-4, precision="mixed",
+                     stream=stream.cuda_stream)
+    batch = batch_of(2, stream)
+    order = [bare, batched.ctx] if first else [batched.ctx, bare]
+    handles = np.array([c.handle.value for c in order], np.uint64)
+    k, t, p = alone.ctx.dev_run(0.02, 1.0 / 64, 1.0 / 64, 25)
+    steps, t_last, psteps, pairs, step_ms = batch.dev_run(handles, [0.02] * 2, [1.0 / 64] * 2, [1.0 / 64] * 2,
+                                                          [0 if c is bare else 25 for c in order], 32)
+    runs, sits = order.index(batched.ctx), order.index(bare)
+    assert (steps[runs], t_last[runs], psteps[runs]) == (k, t, p) and len(step_ms) == k > 0
+    assert (steps[sits], psteps[sits], pairs[sits]) == (0, 0, 0) and np.isnan(t_last[sits])
+    for q, w in zip(batched.ctx.state_get(), alone.ctx.state_get()):
+        assert np.array_equal(q, w)
+    # nobody runs: no step, nothing touched
+    steps, _, _, _, step_ms = batch.dev_run(handles, [0.02] * 2, [1.0 / 64] * 2, [1.0 / 64] * 2, [0, 0], 32)
+    assert not steps.any() and len(step_ms) == 0
+    for s in (alone, batched, bare, batch):
+        s.close()
