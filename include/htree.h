@@ -451,7 +451,7 @@ int ht_sync(ht_ctx *ctx);
  * of T = 1, 2, 4, ..., 256 slots; a tile over a list of L entries is costed
  * rounds*(gather_cost+T) with rounds = ceil(L/256), a group gets the tiles of
  * least total cost, and tiles are split into list ranges only while the call
- * has fewer than about target_items items.  Defaults: 12, 2048.  Results
+ * has fewer than about target_items items.  Defaults: 12, 1024.  Results
  * stay within the stated tolerances for any values (only the summation order
  * changes). */
 int ht_set_tuning(ht_ctx *ctx, double gather_cost, double target_items);

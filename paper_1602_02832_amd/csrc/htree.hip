@@ -75,16 +75,6 @@ __host__ __device__ constexpr int round_mult(int T) { return T <= 8 ? 2 : 1; }
 constexpr int kRoundMax = 2 * kRound;
 constexpr int kOut = 7;       // acc[3], jerk[3], pot
 
-// The cost of an item that a plan's splits aim at: tiles come out with a part
-// of an item each, so that half of target_items items a call leave about that
-// many at the most, and an item that hands over its sums costs as much as a
-// round more.  Against aiming at target_items (2048 by default): steps of 559
-// and 6313 active of 2^20 particles 27.3 -> 23.7 and 161 -> 154 us (59 against
-// 72 us for the first alone), of 225 of 448438 19.2 -> 17.0 us, of 259 of 100034
-// in FP64 27.8 -> 25.2 us; smaller ones, which have one round an item either
-// way, direct sums and all-particle steps as before.
-__host__ __device__ inline double split_quantum(double total, double target_items) { return 2.0 * total / target_items; }
-
 constexpr int kMaxBatch = 1024;   // clusters per batched launch
 
 // j-memory record of one particle or node: everything the predictor needs in
@@ -1703,7 +1693,7 @@ __device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& 
         __syncthreads();
     }
     // 4. splits: the quantum doubles until the plan fits, as on the host
-    double quantum = split_quantum(total, e.target_items);
+    double quantum = total / e.target_items;
     int attempt = 0;
     // how tile T is split: per entries a split (0: one item), into ns items
     auto split = [&](const DTile& T, int64_t* per) {
@@ -2047,7 +2037,14 @@ int ceil_log2(int64_t v) {
 }
 
 constexpr double kGatherCostDefault = 12.0;    // work-plan cost of one round's gather, in pairs per lane (measured best 8-16)
-constexpr double kTargetItemsDefault = 2048.0; // work items a call has at most, about (2 per resident slot)
+// Work items that a call is split towards (1 per resident slot): tiles come out
+// with a part of an item each, so that a call has about twice as many at most,
+// and an item that hands over its sums costs as much as a round more.  Against
+// 2048: steps of 559 and 6313 active of 2^20 particles 27.3 -> 23.7 and 161 ->
+// 154 us (72 -> 59 us for the first alone), of 225 of 448438 19.2 -> 17.0 us, of
+// 259 of 100034 in FP64 27.8 -> 25.2 us; smaller ones, which have one round an
+// item either way, direct sums and all-particle steps the same.
+constexpr double kTargetItemsDefault = 1024.0;
 constexpr int kStageRows = 1 << 16;  // rows per host->device upload chunk
 constexpr int kMaxBins = 16;         // runs of a placed plan (one per XCD)
 
@@ -2348,7 +2345,7 @@ bool check_vectors(const double* const* ptrs, int count) {
 // filled 256 (gc + 256), while 3 stays one tile of 4.  Tiles are
 // only split (into list ranges whose partials are summed afterwards) when the
 // call has too little work to fill the chip: each tile gets about
-// cost / split_quantum(total, target_items) items.  Items are then ordered by decreasing
+// cost / (total / target_items) items.  Items are then ordered by decreasing
 // cost: the hardware hands work-groups out in index order as slots free up,
 // which makes that a longest-first schedule.  The plan depends only on this
 // context's lists, active set and tuning, so a context gives the same bits
@@ -2478,7 +2475,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
         g = static_cast<size_t>(g1 - 1);
         k = e;
     }
-    double quantum = split_quantum(total, c->target_items);
+    double quantum = total / c->target_items;
     for (int attempt = 0;; ++attempt) {
         items.clear();
         rtiles.clear();
