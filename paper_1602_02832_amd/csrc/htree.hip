@@ -148,7 +148,7 @@ struct Item {
     int64_t j_begin;    // first list entry (or first particle, direct sum)
     int64_t j_end;
     int64_t out;        // -1: final results; otherwise partial slot of i-slot 0
-    int32_t rtile;      // the split tile whose partials the last of its items sums, or -1
+    int32_t rtile;      // the split tile that it is a part of, or -1
     int32_t act_begin;  // active-array position of i-slot 0
     int16_t n_i;        // valid i-slots (1..T)
     int16_t tile_log2;  // T = 1 << (tile_log2 & kTileMask); kSelfTerm: the item holding the start of its
@@ -395,7 +395,7 @@ constexpr int kWideTile = 128;
 __host__ __device__ constexpr int per_thread(int T) { return T >= kWideTile ? 2 : 1; }
 
 template <class P, bool EAGER, bool DIRECT, bool RUNS, int T, class RL, bool UNI = false>
-__device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t run0, LdsAll<P>& lds, RL& rl) {
+__device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t run0, LdsAll<P>& lds, RL& rl, int fold) {
     constexpr int G = round_mult(T);    // entries gathered per thread and round
     constexpr int R = kRound * G;       // entries per round
     constexpr int IB = per_thread(T);   // i-slots per thread: islot, islot + TT
@@ -619,7 +619,7 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
             write_out(c, it.act_begin + slot, A[b].v);
         } else {
             double* p = c.partial + (it.out + slot) * kOut;
-            if (it.rtile >= 0) {
+            if (fold) {
 #pragma unroll
                 for (int q = 0; q < kOut; ++q) agent_store(p + q, A[b].v[q]);
             } else {
@@ -628,6 +628,15 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
             }
         }
     }
+}
+
+// Value v of the values of active positions o0 and after.
+__device__ __forceinline__ void store_value(const Desc& c, int64_t o0, int v, double sum) {
+    const int64_t o = o0 + v / kOut;
+    const int q = v % kOut;
+    if (q < 3) c.acc[3 * o + q] = sum;
+    else if (q < 6) c.jerk[3 * o + q - 3] = sum;
+    else c.pot[o] = sum;
 }
 
 // The sums over nsplit splits, in split order, of `vals` values that lie next
@@ -667,11 +676,7 @@ __device__ __forceinline__ void sum_slots(const Desc& c, int64_t o0, int vals, i
     for (int u = 0; u < kOut; ++u) {
         const int v = tid + u * kWG;
         if (v >= vals) break;
-        const int64_t o = o0 + v / kOut;
-        const int q = v % kOut;
-        if (q < 3) c.acc[3 * o + q] = sum[u];
-        else if (q < 6) c.jerk[3 * o + q - 3] = sum[u];
-        else c.pot[o] = sum[u];
+        store_value(c, o0, v, sum[u]);
     }
 }
 
@@ -737,7 +742,7 @@ __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g
 template <class P, bool EAGER, bool DIRECT, bool WIDE = true, bool RUNS = false, bool UNI = false>
 __global__ __launch_bounds__(kWG, (WIDE ? 3 : 4)) void force_kernel(const Entry* __restrict__ tab,
                                                                                    int n_tab, int64_t n_items,
-                                                                                   const int64_t* counts,
+                                                                                   const int64_t* counts, int fold,
                                                                                    const int64_t* bins = nullptr,
                                                                                    int n_bins = 1) {
     __shared__ LdsAll<P> lds;
@@ -757,7 +762,7 @@ __global__ __launch_bounds__(kWG, (WIDE ? 3 : 4)) void force_kernel(const Entry*
         const Item it = tab[cl].items[k];
         const int64_t r0 = RUNS ? c.item_runs[k] : 0;
         auto item_of = [&](auto tile) {
-            run_item<P, EAGER, DIRECT, RUNS, decltype(tile)::value, decltype(rl), UNI>(c, it, r0, lds, rl);
+            run_item<P, EAGER, DIRECT, RUNS, decltype(tile)::value, decltype(rl), UNI>(c, it, r0, lds, rl, fold);
         };
         const int tl = it.tile_log2 & kTileMask;
         bool wide = false;
@@ -780,10 +785,11 @@ __global__ __launch_bounds__(kWG, (WIDE ? 3 : 4)) void force_kernel(const Entry*
                 default: item_of(std::integral_constant<int, 1>{}); break;
             }
         }
-        {   // the item is read again, so that nothing of it stays in registers over the pair loops
+        if (fold) {   // the item is read again, so that nothing of it stays in registers over the pair loops
             int64_t h = g;
-            asm volatile("" : "+s"(h));
-            const Entry& te = tab[find_entry(tab, n_tab, h, false)];
+            int again = cl;
+            asm volatile("" : "+s"(h), "+s"(again));
+            const Entry& te = tab[again];
             const Item done = te.items[h - te.first_item];
             if (done.rtile >= 0) fold_splits<P>(te.d, done, const_cast<RTile*>(te.rtiles), lds);
         }
@@ -791,9 +797,40 @@ __global__ __launch_bounds__(kWG, (WIDE ? 3 : 4)) void force_kernel(const Entry*
     }
 }
 
-// Sum the split partials in a launch of its own (plans with many of them): a
-// work-group takes n_slots slots of a tile.  Direct sums (at 2^20 particles and
-// 559 active 380 splits of 256 slots) took 257 us as one work-group a tile.
+// Sum the split partials in a launch of their own (launches with many of them).
+// Up to kFewSplits splits a tile, a thread sums a value's, kSumBatch loads in
+// flight: no LDS, so that the many small tiles of a batch have places and its few
+// large ones (gridDim.y work-groups share a tile's values) are no long tail.
+// 32 contexts of 16384 particles, 197 and 2000 active each: 6.7 and 18.6 us, 14.8
+// and 25.5 us as a work-group a tile through LDS, in which all the splits of the
+// larger tiles had no room.
+constexpr int kFewSplits = 64;
+constexpr int kSumBatch = 8;   // split partials loaded together
+
+__global__ __launch_bounds__(kWG) void reduce_few_kernel(const Entry* __restrict__ tab, int n_tab) {
+    const int64_t g = blockIdx.x;
+    const int cl = find_entry(tab, n_tab, g, true);
+    const RTile rt = tab[cl].rtiles[g - tab[cl].first_rtile];
+    const int vals = rt.n_i * kOut;
+    for (int v = blockIdx.y * kWG + threadIdx.x; v < vals; v += gridDim.y * kWG) {
+        const double* p = tab[cl].d.partial + rt.pbase * kOut + v;
+        double sum = p[0];
+        int b = 1;
+        for (; b + kSumBatch <= rt.nsplit; b += kSumBatch) {
+            double w[kSumBatch];
+#pragma unroll
+            for (int u = 0; u < kSumBatch; ++u) w[u] = p[static_cast<int64_t>(b + u) * vals];
+#pragma unroll
+            for (int u = 0; u < kSumBatch; ++u) sum += w[u];
+        }
+        for (; b < rt.nsplit; ++b) sum += p[static_cast<int64_t>(b) * vals];
+        store_value(tab[cl].d, rt.act_begin, v, sum);
+    }
+}
+
+// With more splits a work-group takes n_slots slots of a tile through LDS: direct
+// sums (at 2^20 particles and 559 active 380 splits of 256 slots) took 257 us as
+// one work-group a tile.
 constexpr int kRedLds = 6144;   // doubles of LDS
 
 __global__ __launch_bounds__(kWG) void reduce_kernel(const Entry* __restrict__ tab, int n_tab, int n_slots) {
@@ -1268,8 +1305,6 @@ __global__ __launch_bounds__(kWG) void dev_correct_kernel(CorrEntry e0, const Co
         if (correct_particle<P>(e.s, e.rec, e.s.active[q], e.t1, e.eta, e.dt_tree, F) == 0.0) e.out->below_floor = 1;
     }
 }
-
-constexpr int kSumBatch = 8;   // split partials loaded together
 
 // F = the sum of n split partials, kOut values each, `step` values apart, in
 // split order; kSumBatch splits' loads are in flight at once (one at a time,
@@ -2099,15 +2134,24 @@ struct Timing {
     int64_t pairs = 0;
 };
 
-// Split tiles that the reduce launch sums (none: the items do), and the most
-// slots and splits of one.
-struct Reduce {
-    int64_t n = 0;
+// The split tiles of a plan or a batch of plans: how many, their items and
+// partial slots, and the most slots and splits of one.
+struct Splits {
+    int64_t n = 0, items = 0, slots = 0;
     int32_t most_slots = 0, most_splits = 0;
-    void add(const Reduce& r) {
-        n += r.n;
-        most_slots = std::max(most_slots, r.most_slots);
-        most_splits = std::max(most_splits, r.most_splits);
+    void add(const RTile& r) {
+        n += 1;
+        items += r.nsplit;
+        slots += static_cast<int64_t>(r.nsplit) * r.n_i;
+        most_slots = std::max(most_slots, r.n_i);
+        most_splits = std::max(most_splits, r.nsplit);
+    }
+    void add(const Splits& q) {
+        n += q.n;
+        items += q.items;
+        slots += q.slots;
+        most_slots = std::max(most_slots, q.most_slots);
+        most_splits = std::max(most_splits, q.most_splits);
     }
 };
 
@@ -2165,7 +2209,7 @@ struct ht_ctx {
     // last call statistics
     int64_t last_pairs = 0;
     int32_t last_items = 0;
-    Reduce reduce;       // the last plan's sums of split tiles
+    Splits splits;       // the last plan's split tiles
     bool wide = false;   // it holds a tile of kWideTile or more
     Timing tm;
     // per-call scratch: marks for repeated update indices (generation-stamped)
@@ -2351,11 +2395,19 @@ bool check_vectors(const double* const* ptrs, int count) {
 // context's lists, active set and tuning, so a context gives the same bits
 // alone and in a batched launch.
 
-// Partial slots of a plan up to which the items sum them.  Taking the ticket
-// holds an item's place on the chip for about 2 us and the sum for some more,
-// which a launch of 2300 items of an all-particle step (130 thousand slots)
-// feels more (20 us of 300) than the launch of its own (8 us).
+// Partial slots of a launch, and for a batch the items of its split tiles, up to
+// which the items sum them.  Taking the ticket holds an item's place on the chip
+// for about 2 us and the sum for some more.  A launch of 2300 items of an
+// all-particle step (130 thousand slots) feels that more (20 us of 300) than the
+// launch of its own (8 us), and so does a batched launch of more than three items
+// for every place, each of them a round or two long: 32 contexts of 16384
+// particles and 197 active each, 15760 items, 188 us against 154 us with a launch,
+// 16 of them, 7880 items in FP64, 98 against 82 us, 8 of them, 3940 items, 48.5
+// against 44 us, 16 with 40 active, 2808 items, 33 against 37 us.  One context's
+// plan of that many items has longer ones: 6313 active of 2^20 particles 152 us
+// against 157 us with a launch.
 constexpr int64_t kFoldSlots = 16384;
+constexpr int64_t kFoldItems = 3 * 1024;
 
 struct Tile {
     int64_t jb, je;
@@ -2390,13 +2442,14 @@ void tile_table(double gather_cost, int8_t* first_tile) {
     }
 }
 
-int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool place = false, bool fold = false) {
+int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool place = false) {
     auto& items = c->items;
     auto& rtiles = c->rtiles;
     static thread_local std::vector<Tile> tiles;
     tiles.clear();
     int64_t pairs = 0;
     double total = 0.0;
+    c->wide = false;
     // the tiles of least modelled cost over a list of len entries for the
     // active positions [tb, e), and what they cost
     auto cover_cost = [c](int32_t n, int64_t len) {
@@ -2417,6 +2470,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
             const int64_t rounds = (je - jb + kRound - 1) / kRound;
             const double cost = static_cast<double>(rounds) * (c->gather_cost + static_cast<double>(1 << tl));
             tiles.push_back(Tile{jb, je, tb, ni, tl, cost, uni});
+            c->wide |= (1 << tl) >= kWideTile;
             total += cost;
             tb += ni;
         }
@@ -2479,7 +2533,8 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
     for (int attempt = 0;; ++attempt) {
         items.clear();
         rtiles.clear();
-        int64_t pslots = 0;
+        Splits& sp = c->splits = Splits{};
+        const int64_t& pslots = sp.slots;
         for (const Tile& t : tiles) {
             const int64_t rsz = static_cast<int64_t>(kRound) * round_mult(1 << t.tl);   // the kernel's round
             const int64_t rounds = (t.je - t.jb + rsz - 1) / rsz;
@@ -2499,27 +2554,11 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
                                      static_cast<int16_t>((nsu == 0 ? t.tl | kSelfTerm : t.tl) |
                                                           (t.uni ? kUnion : 0))});
             rtiles.push_back(RTile{pslots, t.tb, t.ni, nsu, 0});
-            pslots += static_cast<int64_t>(nsu) * t.ni;
+            sp.add(rtiles.back());
         }
         if (static_cast<int64_t>(items.size()) <= c->L.items_max && pslots <= c->L.partial_max) break;
         if (attempt > 60) return fail(HT_ERANGE, "work plan exceeds the context's item capacity");
         quantum *= 2.0;
-    }
-    // The last item of a split tile sums the tile's partials, unless there are
-    // so many that a launch of their own is better (fold: the caller has none).
-    c->wide = false;
-    for (const Tile& t : tiles) c->wide |= (1 << t.tl) >= kWideTile;
-    c->reduce = Reduce{};
-    int64_t slots = 0;
-    for (const RTile& r : rtiles) slots += static_cast<int64_t>(r.nsplit) * r.n_i;
-    if (!fold && slots > kFoldSlots) {
-        Reduce& rd = c->reduce;
-        rd.n = static_cast<int64_t>(rtiles.size());
-        for (const RTile& r : rtiles) {
-            rd.most_slots = std::max(rd.most_slots, r.n_i);
-            rd.most_splits = std::max(rd.most_splits, r.nsplit);
-        }
-        for (Item& it : items) it.rtile = -1;
     }
     // Placement (more than one run requested, list items): the items, still in
     // group order, i.e. in space-filling order of their groups, are cut into
@@ -2693,10 +2732,10 @@ int copy_plan(ht_ctx* c, size_t end) {
 
 template <class P>
 int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab, int n_tab, int64_t n_items,
-                 const Reduce& reduce, bool wide, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
+                 const Splits& splits, bool wide, bool direct, int64_t pairs, bool runs = false, const int64_t* d_bins = nullptr,
                  int n_bins = 1, int64_t bin_max = 0, bool uni = false) {
     const int grid = d_bins ? static_cast<int>(n_bins * bin_max) : grid_for(n_items);
-    using Kern = void (*)(const Entry*, int, int64_t, const int64_t*, const int64_t*, int);
+    using Kern = void (*)(const Entry*, int, int64_t, const int64_t*, int, const int64_t*, int);
     Kern kern;
     if (runs) kern = force_kernel<P, false, false, true, true>;
     else if (uni) kern = force_kernel<P, false, false, true, false, true>;
@@ -2705,6 +2744,8 @@ int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab,
     else kern = direct ? (eager ? force_kernel<P, true, true, false> : force_kernel<P, false, true, false>)
                        : (eager ? force_kernel<P, true, false, false> : force_kernel<P, false, false, false>);
     const int64_t* counts = nullptr;
+    const bool by_launch = splits.slots > kFoldSlots || (n_tab > 1 && splits.items > kFoldItems);
+    int fold = splits.n > 0 && !by_launch;
     if (tm.enabled) {
         // Timing: the extended launch stamps the two events with the kernel's
         // own start and end, so the time excludes the dispatch around it.
@@ -2716,19 +2757,24 @@ int launch_force(hipStream_t stream, bool eager, Timing& tm, const Entry* d_tab,
         hipEvent_t ev_a = tm.pool[tm.used], ev_b = tm.pool[tm.used + 1];
         tm.used += 2;
         tm.pairs += pairs;
-        void* args[] = {&d_tab, &n_tab, &n_items, &counts, &d_bins, &n_bins};
+        void* args[] = {&d_tab, &n_tab, &n_items, &counts, &fold, &d_bins, &n_bins};
         HT_HIP(hipExtLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid), dim3(kWG), args, 0, stream, ev_a,
                                   ev_b, 0));
     } else {
-        kern<<<grid, kWG, 0, stream>>>(d_tab, n_tab, n_items, counts, d_bins, n_bins);
+        kern<<<grid, kWG, 0, stream>>>(d_tab, n_tab, n_items, counts, fold, d_bins, n_bins);
         HT_HIP(hipGetLastError());
     }
-    if (reduce.n > 0) {
-        // as many slots a work-group as LDS holds the splits of at once, at least four
-        const int fit = kRedLds / (kOut * std::max(reduce.most_splits, 1));
-        const int n_slots = std::min(std::max(fit, 4), kWG);
-        reduce_kernel<<<dim3(static_cast<unsigned>(reduce.n), (reduce.most_slots + n_slots - 1) / n_slots), kWG, 0,
-                        stream>>>(d_tab, n_tab, n_slots);
+    if (splits.n > 0 && by_launch) {
+        const auto n = static_cast<unsigned>(splits.n);
+        if (splits.most_splits <= kFewSplits) {
+            const int64_t shares = (splits.most_slots * kOut + kWG - 1) / kWG;
+            reduce_few_kernel<<<dim3(n, static_cast<unsigned>(std::min<int64_t>(shares, std::max<int64_t>(1, 8192 / n)))),
+                                kWG, 0, stream>>>(d_tab, n_tab);
+        } else {
+            // as many slots a work-group as LDS holds the splits of at once, at least four
+            const int n_slots = std::min(std::max(kRedLds / (kOut * splits.most_splits), 4), kWG);
+            reduce_kernel<<<dim3(n, (splits.most_slots + n_slots - 1) / n_slots), kWG, 0, stream>>>(d_tab, n_tab, n_slots);
+        }
         HT_HIP(hipGetLastError());
     }
     return HT_OK;
@@ -2842,9 +2888,9 @@ int enqueue_step(ht_ctx* c, const DevRows& u, bool predict_eager, int32_t n_acti
     const bool eager = c->cfg.predict_mode == HT_PREDICT_EAGER;
     const bool runs = c->list_form == HT_LISTS_RUNS && !direct;
     rc = c->cfg.precision == HT_PREC_FP64
-             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, c->wide, direct, c->last_pairs, runs,
+             ? launch_force<PrecFp64>(c->stream, eager, c->tm, d_tab, 1, ni, c->splits, c->wide, direct, c->last_pairs, runs,
                                       d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct)
-             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, c->reduce, c->wide, direct, c->last_pairs, runs,
+             : launch_force<PrecMixed>(c->stream, eager, c->tm, d_tab, 1, ni, c->splits, c->wide, direct, c->last_pairs, runs,
                                        d_bins, c->n_bins, c->bin_max, c->union_items > 0 && !direct);
     if (rc) return rc;
     // The prep launch is the slot's only reader; marking the slot after the
@@ -3428,7 +3474,7 @@ int build_step_graph(ht_ctx* c, int k) {
     prep_graph_kernel<P><<<kGraphCopyBlocks + kGraphScatterBlocks, kWG, 0, s>>>(c->h_hdr + k, d_plan,
                                                                              c->ws + c->L.off_rec,
                                                                              kGraphCopyBlocks);
-    force_kernel<P, false, false><<<kGraphForceGrid, kWG, 0, s>>>(d_tab, 1, -1, &d_tab->n_items);
+    force_kernel<P, false, false><<<kGraphForceGrid, kWG, 0, s>>>(d_tab, 1, -1, &d_tab->n_items, 1);
     const hipError_t launch = hipGetLastError();
     hipGraph_t g = nullptr;
     const hipError_t end = hipStreamEndCapture(s, &g);
@@ -3467,7 +3513,7 @@ int ht_step_graph(ht_ctx* c, int32_t n_upd, const int32_t* d_idx, const double* 
     }
     c->t_pred = t;
     c->predicted = true;
-    rc = plan(c, n_active, ids, false, false, true);
+    rc = plan(c, n_active, ids, false);
     if (rc) return rc;
     rc = c->slot_acquire();
     if (rc) return rc;
@@ -3904,7 +3950,7 @@ void queue_loop_step(const LoopRun& r, const LoopMem& m, hipStream_t s) {
     const int n_tab = static_cast<int>(r.n_tab);
     loop_select_kernel<<<r.blocks, kPlanWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.loops, m.launch, m.sums, m.cnt, m.ts,
                                                     m.ts_max);
-    force_kernel<P, false, false><<<r.force_grid, kWG, 0, s>>>(m.launch, n_tab, -1, &m.cnt->items);
+    force_kernel<P, false, false><<<r.force_grid, kWG, 0, s>>>(m.launch, n_tab, -1, &m.cnt->items, 0);
     loop_correct_kernel<P><<<r.blocks, kWG, 0, s>>>(m.tab, m.block_ctx, n_tab, m.loops);
 }
 
@@ -4064,7 +4110,7 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     std::vector<Entry> tab;
     tab.reserve(n_ctx);
     int64_t n_items = 0, pairs = 0;
-    Reduce reduce;
+    Splits splits;
     bool wide = false;
     int rc = c0->slot_acquire();
     if (rc) return rc;
@@ -4089,9 +4135,9 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
             if (rc) return rc;
         }
         e.first_item = n_items;
-        e.first_rtile = reduce.n;
+        e.first_rtile = splits.n;
         n_items += static_cast<int64_t>(c->items.size());
-        reduce.add(c->reduce);
+        splits.add(c->splits);
         wide |= c->wide;
         pairs += c->last_pairs;
         tab.push_back(e);
@@ -4108,8 +4154,8 @@ int ht_force_batch_async(int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* n_ac
     const int nt = static_cast<int>(tab.size());
     const bool eager = c0->cfg.predict_mode == HT_PREDICT_EAGER;
     if (c0->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
-    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
+        return launch_force<PrecFp64>(c0->stream, eager, c0->tm, d_tab, nt, n_items, splits, wide, false, pairs);
+    return launch_force<PrecMixed>(c0->stream, eager, c0->tm, d_tab, nt, n_items, splits, wide, false, pairs);
 }
 
 }  // extern "C"
@@ -4428,7 +4474,7 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     char* dv = b->ws;
     b->tab.clear();
     int64_t n_items = 0, pairs = 0;
-    Reduce reduce;
+    Splits splits;
     bool wide = false;
     size_t at = static_cast<size_t>(n_ctx) * sizeof(Entry);
     for (int32_t k = 0; k < n_ctx; ++k) {
@@ -4445,9 +4491,9 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
         Entry e{};
         at = pack_plan_into(c, hs, dv, at, n_active[k], ids[k], d_acc[k], d_jerk[k], d_pot[k], e);
         e.first_item = n_items;
-        e.first_rtile = reduce.n;
+        e.first_rtile = splits.n;
         n_items += static_cast<int64_t>(c->items.size());
-        reduce.add(c->reduce);
+        splits.add(c->splits);
         wide |= c->wide;
         pairs += c->last_pairs;
         b->tab.push_back(e);
@@ -4472,8 +4518,8 @@ int batch_force(ht_batch* b, int32_t n_ctx, ht_ctx* const* ctxs, const int32_t* 
     const int nt = static_cast<int>(b->tab.size());
     const bool eager = ctxs[0]->cfg.predict_mode == HT_PREDICT_EAGER;
     if (ctxs[0]->cfg.precision == HT_PREC_FP64)
-        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
-    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, reduce, wide, false, pairs);
+        return launch_force<PrecFp64>(b->stream, eager, b->tm, d_tab, nt, n_items, splits, wide, false, pairs);
+    return launch_force<PrecMixed>(b->stream, eager, b->tm, d_tab, nt, n_items, splits, wide, false, pairs);
 }
 
 }  // namespace
