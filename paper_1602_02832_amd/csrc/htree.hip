@@ -147,7 +147,7 @@ struct Desc {
 struct Item {
     int64_t j_begin;    // first list entry (or first particle, direct sum)
     int64_t j_end;
-    int64_t out;        // -1: final results; otherwise partial slot of i-slot 0
+    int32_t out;        // -1: final results; otherwise partial slot of i-slot 0
     int32_t rtile;      // the split tile that it is a part of, or -1
     int32_t act_begin;  // active-array position of i-slot 0
     int16_t n_i;        // valid i-slots (1..T)
@@ -156,6 +156,7 @@ struct Item {
                         // range is in the union lists, and a pair counts only where the entry's mask
                         // holds the i-slot's member bit
 };
+static_assert(sizeof(Item) == 32, "items are read from the host's memory for every step");
 constexpr int16_t kTileMask = 0xff;
 constexpr int16_t kSelfTerm = 0x100;
 constexpr int16_t kUnion = 0x200;
@@ -618,7 +619,7 @@ __device__ __forceinline__ void run_item(const Desc& c, const Item& it, int64_t 
         if (it.out < 0) {
             write_out(c, it.act_begin + slot, A[b].v);
         } else {
-            double* p = c.partial + (it.out + slot) * kOut;
+            double* p = c.partial + (static_cast<int64_t>(it.out) + slot) * kOut;
             if (fold) {
 #pragma unroll
                 for (int q = 0; q < kOut; ++q) agent_store(p + q, A[b].v[q]);
@@ -1787,7 +1788,7 @@ __device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& 
         }
         for (int32_t k = begin; k < static_cast<int32_t>(nsq); k += step) {
             const int64_t b = T.jb + k * pq;
-            it[k] = Item{b, b + pq < T.je ? b + pq : T.je, slot + static_cast<int64_t>(k) * T.ni, -1, T.tb, ni,
+            it[k] = Item{b, b + pq < T.je ? b + pq : T.je, static_cast<int32_t>(slot) + k * T.ni, -1, T.tb, ni,
                          static_cast<int16_t>(k == 0 ? tl | kSelfTerm : tl)};
         }
     };
@@ -2111,7 +2112,8 @@ bool layout_of(const ht_config& c, Layout& L) {
     L.off_prec = take(eager ? L.jcap * 64 : 0);
     L.off_entries = take(static_cast<size_t>(c.list_max) * 4);
     L.items_max = 4 * (static_cast<int64_t>(c.group_max) + c.active_max / 256 + 1) + 4096;
-    L.partial_max = 2 * static_cast<int64_t>(c.active_max) + 65536;
+    // slots are numbered in 32 bits (at 2^31 the partial sums alone are 120 GB)
+    L.partial_max = std::min<int64_t>(2 * static_cast<int64_t>(c.active_max) + 65536, INT32_MAX);
     L.plan_bytes = align_up(kMaxBatch * sizeof(Entry)) + align_up(static_cast<size_t>(L.items_max) * sizeof(Item)) +
                    align_up(static_cast<size_t>(L.items_max) * sizeof(RTile)) +
                    align_up(static_cast<size_t>(c.active_max) * 4) +
@@ -2548,7 +2550,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
             const int64_t per = (rounds + ns - 1) / ns * rsz;   // entries per split, whole rounds
             int32_t nsu = 0;
             for (int64_t b = t.jb; b < t.je; b += per, ++nsu)
-                items.push_back(Item{b, std::min(t.je, b + per), pslots + static_cast<int64_t>(nsu) * t.ni,
+                items.push_back(Item{b, std::min(t.je, b + per), static_cast<int32_t>(pslots + static_cast<int64_t>(nsu) * t.ni),
                                      static_cast<int32_t>(rtiles.size()), t.tb,
                                      static_cast<int16_t>(t.ni),
                                      static_cast<int16_t>((nsu == 0 ? t.tl | kSelfTerm : t.tl) |
