@@ -931,8 +931,10 @@ __global__ __launch_bounds__(kWG) void scatter_kernel(Desc dst, int n, const int
                                                       const double* x, const double* v, const double* a,
                                                       const double* jerk, int32_t lim, int32_t* err) {
     typename P::Rec* rec = static_cast<typename P::Rec*>(const_cast<void*>(dst.rec));
-    for (int k = blockIdx.x * kWG + threadIdx.x; k < n; k += gridDim.x * kWG) {
-        const int32_t j = idx ? idx[k] : base + k;
+    // 64 bits: a whole state (ht_state_set) may have more than 2^31 / 3 particles
+    for (int64_t k = blockIdx.x * static_cast<int64_t>(kWG) + threadIdx.x; k < n;
+         k += static_cast<int64_t>(gridDim.x) * kWG) {
+        const int32_t j = idx ? idx[k] : base + static_cast<int32_t>(k);
         if (idx && !row_index_ok(j, lim, err)) continue;
         store_rec<P>(rec, j, t0 ? t0[k] : t0_all, m[k], x + 3 * k, v + 3 * k, a + 3 * k, jerk + 3 * k);
     }
