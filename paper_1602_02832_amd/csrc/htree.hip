@@ -1587,10 +1587,11 @@ __device__ inline void plan_step(const LoopEntry& e, DevLoop* L, const DevLoop& 
         const int32_t c0 = due0 ? agent_load(e.s.bcount + 2 * t) : 0, c1 = due1 ? agent_load(e.s.bcount + 2 * t + 1) : 0;
         // the first particles of the due blocks come with the counts, not after them
         uint64_t w0[kEarly], w1[kEarly];
+        const int64_t b0 = int64_t(2 * t) * e.chunk, b1 = b0 + e.chunk;
 #pragma unroll
-        for (int u = 0; u < kEarly; ++u) {
-            w0[u] = due0 && u < e.chunk ? agent_load(e.due + int64_t(2 * t) * e.chunk + u) : 0;
-            w1[u] = due1 && u < e.chunk ? agent_load(e.due + int64_t(2 * t + 1) * e.chunk + u) : 0;
+        for (int u = 0; u < kEarly; ++u) {   // within the block, and the last one may be short
+            w0[u] = due0 && u < e.chunk && b0 + u < e.n ? agent_load(e.due + b0 + u) : 0;
+            w1[u] = due1 && u < e.chunk && b1 + u < e.n ? agent_load(e.due + b1 + u) : 0;
         }
         int32_t v[2] = {c0 + c1, c0 > kEarly || c1 > kEarly}, tot[2];
         plan_scan(v, tot, S);

@@ -17,26 +17,20 @@ pytestmark = pytest.mark.gpu
 FIELDS = ("t0", "dt", "x", "v", "a", "j", "pot")
 
 
-def test_one_block_due_alone_with_more_particles_than_a_work_group():
-    """Above 524288 particles a scheduler block holds more than the 512 that the
-    planner keeps in LDS.  Where such a block is the only one due, the planner
-    reads its count and particles from memory, written in the same work-group."""
-    say("device loop: one block of up to 547 particles due alone")
-    n = 560000
-    chunk = (n + 1023) // 1024                          # particles of a scheduler block
-    assert chunk == 547
+def against_single_steps(n, chunk, cases):
+    """Three steps of the loop, in which the given particles are due first: for
+    each case, (block, how many of its particles) pairs, blocks of chunk particles."""
     top = 1.0 / 256
     x, v, m = W.plummer(n, 91)
     sim = driver.Simulation(x, v, m, eps2=1e-6, dt_tree=top, eta=0.1, theta=0.6, n_crit=1024, precision="mixed",
                             resident=True)
     ctx = sim.ctx
     t0 = np.zeros(n)
-    # (block, how many of its particles are due first): the counts of one case are not those of the next
-    for due in ([(900, 100)], [(900, 512)], [(900, 513)], [(900, 547)], [(3, 547)], [(900, 530), (901, 547)],
-                [(1022, 547)]):
+    for due in cases:
         dt = np.full(n, top)
         for b, k in due:
-            first = b * chunk + (chunk - k) // 2
+            size = min(chunk, n - b * chunk)
+            first = b * chunk + (size - k) // 2
             dt[first:first + k] = top * 2.0 ** -20      # the first steps double: all of them stay due together
         state = (t0, dt, sim.m, sim.x, sim.v, sim.a, sim.j, sim.pot)
         ctx.state_set(*state)
@@ -55,6 +49,26 @@ def test_one_block_due_alone_with_more_particles_than_a_work_group():
         for f, p, q in zip(FIELDS, got, want):
             assert np.array_equal(p, q), (due, f)
     sim.close()
+
+
+def test_one_block_due_alone_with_more_particles_than_a_work_group():
+    """Above 524288 particles a scheduler block holds more than the 512 that the
+    planner keeps in LDS.  Where such a block is the only one due, the planner
+    reads its count and particles from memory, written in the same work-group."""
+    say("device loop: one block of up to 547 particles due alone")
+    n = 560000
+    assert (n + 1023) // 1024 == 547                    # particles of a scheduler block
+    # the counts of one case are not those of the next
+    against_single_steps(n, 547, ([(900, 100)], [(900, 512)], [(900, 513)], [(900, 547)], [(3, 547)],
+                                  [(900, 530), (901, 547)], [(1022, 547)]))
+
+
+def test_last_block_with_one_particle():
+    """The planner loads the first particles of every due block with the counts;
+    the last block may have fewer."""
+    say("device loop: last block of one particle")
+    n = 600 * 512 + 1
+    against_single_steps(n, 512, ([(600, 1)], [(0, 3), (600, 1)], [(599, 512), (600, 1)], [(599, 4), (600, 1)]))
 
 
 def resident(n, seed, stream, **kw):
