@@ -726,7 +726,8 @@ __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g
 // VGPRs, 4 waves per SIMD, which hides their gathers better: a step of 559
 // active of 2^20 particles takes 28 us, and 30 us with the line at tiles of 64,
 // which lone crowded groups of such steps reach.  The arithmetic of a tile is
-// the same in both kernels.
+// the same in both kernels.  Captured steps and device loops, whose launches are
+// fixed before the plan is known, and batches with one such tile run the wide one.
 // Work-group g takes items g, g + grid, ...  The grid is normally the item
 // count; graph replays and device loops launch a fixed grid and pass
 // n_items < 0, and the count is read from counts[0] (the items of the whole
@@ -1417,7 +1418,7 @@ struct LoopSum {
 
 // Device words of a loop call.
 struct LoopCounts {
-    int64_t items, rows;   // this step: work items and active particles of all contexts
+    int64_t items;         // this step: work items of all contexts
     int64_t step;          // steps in which some context stepped
     int64_t expect;        // contexts that run this step
     int32_t ticket, pad;   // contexts planned in this step
@@ -1853,7 +1854,6 @@ __device__ inline void place_items(int n_tab, Entry* launch, const LoopSum* sums
     if (threadIdx.x != 0) return;
     LoopCounts z = *cnt;
     z.items = tot[0];
-    z.rows = tot[1];
     z.expect = tot[2];
     z.ticket = 0;
     if (tot[1] > 0) {
@@ -2875,7 +2875,7 @@ int enqueue_step(ht_ctx* c, const DevRows& u, bool predict_eager, int32_t n_acti
         e.first_item = 0;
         e.first_rtile = 0;
         e.n_items = static_cast<int64_t>(c->items.size());
-            std::memcpy(c->plan_host(), &e, sizeof(Entry));
+        std::memcpy(c->plan_host(), &e, sizeof(Entry));
     } else {
         c->last_pairs = 0;
         c->last_items = 0;
