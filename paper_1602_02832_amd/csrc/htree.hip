@@ -720,12 +720,12 @@ __device__ __forceinline__ int find_entry(const Entry* tab, int n_tab, int64_t g
     return lo;
 }
 
-// Register budget.  Two i-slots a thread take 164 VGPRs or so: 3 waves per SIMD
+// Register budget.  Two i-slots a thread take 160 to 164 VGPRs: 3 waves per SIMD
 // (4 with spills are 1 to 3% slower).  Plans without a tile of kWideTile or
-// more, most small steps, run a kernel without those cases (WIDE false) in 106
-// VGPRs, 4 waves per SIMD, which hides their gathers better: a step of 559
-// active of 2^20 particles takes 28 us, and 30 us with the line at tiles of 64,
-// which lone crowded groups of such steps reach.  The arithmetic of a tile is
+// more, most small steps, run a kernel without those cases (WIDE false) in 100 to
+// 104 VGPRs, 4 waves per SIMD, which hides their gathers better: a step of 559
+// active of 2^20 particles took 28 us, and 30 us with the line at tiles of 64,
+// which lone crowded groups of such steps reach (24 us since, by the plan).  The arithmetic of a tile is
 // the same in both kernels.  Captured steps and device loops, whose launches are
 // fixed before the plan is known, and batches with one such tile run the wide one.
 // Work-group g takes items g, g + grid, ...  The grid is normally the item
@@ -2454,7 +2454,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
     tiles.clear();
     int64_t pairs = 0;
     double total = 0.0;
-    c->wide = false;
+    bool wide = false;
     // the tiles of least modelled cost over a list of len entries for the
     // active positions [tb, e), and what they cost
     auto cover_cost = [c](int32_t n, int64_t len) {
@@ -2475,7 +2475,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
             const int64_t rounds = (je - jb + kRound - 1) / kRound;
             const double cost = static_cast<double>(rounds) * (c->gather_cost + static_cast<double>(1 << tl));
             tiles.push_back(Tile{jb, je, tb, ni, tl, cost, uni});
-            c->wide |= (1 << tl) >= kWideTile;
+            wide |= (1 << tl) >= kWideTile;
             total += cost;
             tb += ni;
         }
@@ -2538,7 +2538,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
     for (int attempt = 0;; ++attempt) {
         items.clear();
         rtiles.clear();
-        Splits& sp = c->splits = Splits{};
+        Splits sp;
         const int64_t& pslots = sp.slots;
         for (const Tile& t : tiles) {
             const int64_t rsz = static_cast<int64_t>(kRound) * round_mult(1 << t.tl);   // the kernel's round
@@ -2561,6 +2561,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
             rtiles.push_back(RTile{pslots, t.tb, t.ni, nsu, 0});
             sp.add(rtiles.back());
         }
+        c->splits = sp;
         if (static_cast<int64_t>(items.size()) <= c->L.items_max && pslots <= c->L.partial_max) break;
         if (attempt > 60) return fail(HT_ERANGE, "work plan exceeds the context's item capacity");
         quantum *= 2.0;
@@ -2650,6 +2651,7 @@ int plan(ht_ctx* c, int32_t n_active, const int32_t* ids, bool direct, bool plac
     c->union_items = 0;
     if (uni)
         for (const Item& it : items) c->union_items += (it.tile_log2 & kUnion) ? 1 : 0;
+    c->wide = wide;
     c->last_pairs = pairs;
     c->last_items = static_cast<int32_t>(items.size());
     return HT_OK;
