@@ -55,11 +55,11 @@ METRIC_ENSEMBLE = "batched ensemble (64 Plummer clusters, N 4096-65536): Hermite
 # only for the kernel source and the window (steps, warmup) it was taken on:
 # anything else makes the figure null until the counters are taken again.
 TRAFFIC = {
-    "kernel_source_sha256": "ec4a15718c4b7581a4a33bbb5cb0a1ad291bdf85bf4e4ac5c84d1f31643f6af3",
+    "kernel_source_sha256": "3981d2b16573c4d5ab5e426a200d305f1d3a1e442606e99f5b666983c5d1790a",
     "steps": 20,
     "warmup": 5,
-    "fetch_bytes_per_launch": 1.148e8,   # FETCH_SIZE 56054.9 KiB x 2.000
-    "write_bytes_per_launch": 4.3733e5,    # WRITE_SIZE 427.1 KiB x 1.000
+    "fetch_bytes_per_launch": 1.1470e8,   # FETCH_SIZE 56007.2 KiB x 2.000
+    "write_bytes_per_launch": 4.3732e5,    # WRITE_SIZE 427.1 KiB x 1.000
     "fetch_scale": 2.000,                  # 1 GiB read by a plain copy reads 524294.5 KiB
     "write_scale": 1.000,                  # 1 GiB written reads 1048576 KiB
     "profile": "profiles/force_kernel_mixed_plummer1m_traffic.md",
